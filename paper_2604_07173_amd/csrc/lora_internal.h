@@ -36,11 +36,19 @@ constexpr int kFusedMaxChunks = 64;    // widest group, in 128-column chunks per
 constexpr int kFusedMaxTiles = 64;     // largest batch, as the host's upper bound of the tile count
 constexpr int kFusedMinChunks = 16;    // 128-column chunks a workgroup expands at least
 constexpr int kFusedWorkgroups = 1024; // workgroups aimed at
-// Cache hints of the activation streams of the decode kernels, measured on MI355X with the Mixtral
-// shapes (512 to 2900 tokens, top-2): input rows that are read once are streamed from 64 MiB on
-// (a quarter of the 256 MiB memory-side cache), the output rows of one call from 256 MiB on.
+// Cache hints of the activation streams of the decode kernels, measured on MI355X.  Input rows that
+// are read once are streamed from kStreamXMiB on, and at ranks 8 and 16 fetched as whole lines.
+// Layer call in us, cacheable / streamed, by where the activations are when it starts (in HBM only;
+// just written by the kernels before; left in the memory-side cache by the previous call):
+//   Mixtral shapes, 512 tokens (28 MiB)   117.7 / 107.3    113.9 / 113.8    105.8 / 106.5
+//   llama shapes, 1024 rows (8 and 28 MiB), rank 8   103.6 / 97.6    98.7 / 99.0    92.6 / 96.1
+//     rank 64   305.8 / 292.8    292.5 / 299.6    269.9 / 275.9 (half lines: hence the higher limit)
+//   llama shapes, 512 rows (4 and 14 MiB; 2 MiB as the limit)   81.1 / 84.1    82.7 / 84.7    80.9 / 84.0
+// The output rows of one call are streamed from kStreamYMiB on: just-written ones would lose what
+// those in HBM gain (Mixtral shapes, 2048 tokens, 235 MiB: 246.8 / 259.1 against 258.9 / 247.4).
 constexpr int kLongMinRowsTimesRank = 1 << 17;   // long-segment kernels from this many rows x rank on
-constexpr int kStreamXMiB = 64;
+constexpr int kStreamXMiB = 8;
+constexpr int kStreamXHighRankMiB = 16;   // ranks 32 and 64
 constexpr int kStreamYMiB = 256;
 constexpr int kMaxFused = 3;         // projections that share an input in one launch (q/k/v, gate/up)
 
