@@ -221,6 +221,7 @@ int pick_tile_rows(const lora_pool *p, int P)
 
 struct KSplit {
     int n_parts, kb_per_part;
+    int ws_parts;            // parts the workspace is sized for (>= n_parts)
     bool wave_per_tile;
 };
 
@@ -244,15 +245,35 @@ KSplit ksplit_of(const lora_pool *p, int proj, int P)
         if (wpt == 1 || (wpt < 0 && tub >= wpt_tiles && p->d.proj[proj].h_in <= wpt_k)) {
             KSplit k;
             k.kb_per_part = kblocks;
-            k.n_parts = 1;
+            k.n_parts = k.ws_parts = 1;
             k.wave_per_tile = true;
             return k;
         }
-        int n = std::max(1, (kblocks + kb_target - 1) / kb_target);
-        n = std::max<int>(n, (int)std::min<int64_t>((want_wgs + tub - 1) / tub, kblocks / 4));
-        n = std::min(std::max(n, 1), max_parts);
-        int per = ((kblocks + n - 1) / n + 3) / 4 * 4;
+        const int by_size = std::max(1, (kblocks + kb_target - 1) / kb_target);
+        auto parts_for = [&](int wgs) {
+            const int n = std::max<int>(by_size, (int)std::min<int64_t>((wgs + tub - 1) / tub, kblocks / 4));
+            return std::min(std::max(n, 1), max_parts);
+        };
         KSplit k;
+        int n = parts_for(want_wgs);
+        int per = ((kblocks + n - 1) / n + 3) / 4 * 4;
+        k.ws_parts = (kblocks + per - 1) / per;
+        // With three workgroups per CU and more the chip is full, and more parts only cost: at ranks
+        // 8 and 16 three workgroups per CU are enough, and a short part is a whole number of rounds of
+        // the workgroup's four waves (a wave takes shrink_wave_units() K-blocks per step): one and a
+        // half rounds take as long as two.  Llama shapes at rank 16, 2048 rows of which 1792 share an
+        // adapter: 181 -> 164 us for the layer, 1024 rows 124 -> 113.5.  Not at ranks 32 and 64, where
+        // a part is two and four times the bytes (1024 rows: 171 against 178 us, 280 against 288), and
+        // not from two rounds on (448 K-blocks in eight parts of 56 against seven of 64: Mixtral
+        // shapes, 2048 tokens, 255 against 263 us).  The workspace keeps room for the finer split,
+        // so that a buffer sized for a batch also takes every smaller one.
+        static const int full = tune_int("LORA_DEC_SHRINK_FULL", 768, 1, 1 << 20);
+        const int round = 4 * shrink_wave_units(p->d.rank);
+        if (p->d.rank <= 16 && tub * k.ws_parts >= full) {
+            n = parts_for(full);
+            per = ((kblocks + n - 1) / n + 3) / 4 * 4;
+            if (per < 2 * round) per = (per + round - 1) / round * round;
+        }
         k.kb_per_part = per;
         k.n_parts = (kblocks + per - 1) / per;
         k.wave_per_tile = false;
@@ -271,7 +292,7 @@ KSplit ksplit_of(const lora_pool *p, int proj, int P)
     per = (per + 3) / 4 * 4;
     KSplit k;
     k.kb_per_part = per;
-    k.n_parts = (kblocks + per - 1) / per;
+    k.n_parts = k.ws_parts = (kblocks + per - 1) / per;
     k.wave_per_tile = false;
     return k;
 }
@@ -1072,7 +1093,7 @@ size_t lora_v_bytes(const lora_pool *pool, int proj, int P)
 {
     if (check_pool(pool) != LORA_OK || proj < 0 || proj >= pool->d.n_proj || P < 0) return 0;
     const KSplit ks = ksplit_of(pool, proj, P);
-    size_t n = parts_bytes(pool, ks.n_parts, P);
+    size_t n = parts_bytes(pool, ks.ws_parts, P);
     // long-segment batches: the expand keeps its operand images behind the K parts
     if (pick_tile_rows(pool, P) == kTileRows)
         n += align_up(expand_image_bytes(pool->d.rank, tiles_upper_bound(pool, P, kTileRows)), 256);

@@ -55,6 +55,8 @@ constexpr int kMaxFused = 3;         // projections that share an input in one l
 // ---- packed layout sizes ---------------------------------------------------------------
 inline int kunit_of(int rank) { return rank == 8 ? 64 : kKBlock; }   // K values per packed A block
 inline int kblocks_of(int h_in, int rank) { return (h_in + kunit_of(rank) - 1) / kunit_of(rank); }
+// K-blocks a wave of the decode shrink takes per step: 128 K values at ranks 8 and 16, 64 and 32 above
+constexpr int shrink_wave_units(int rank) { return rank == 8 ? 2 : rank == 16 ? 4 : rank == 32 ? 2 : 1; }
 inline int chunks_of(int h_out) { return (h_out + kColChunk - 1) / kColChunk; }
 inline size_t packed_A_bytes(int h_in, int rank) { return (size_t)kblocks_of(h_in, rank) * kunit_of(rank) * rank * 2; }
 inline size_t packed_B_bytes(int h_out, int rank) { return (size_t)chunks_of(h_out) * kColChunk * rank * 2; }

@@ -34,7 +34,7 @@ struct ShrinkWave {
     static constexpr int XN = R == 8 ? 2 : 1;                  // x operands per K unit
     static constexpr int NACC = R == 8 ? 2 : NB;               // accumulators per projection
     static constexpr int KU = R == 8 ? 64 : 32;                // K values per unit
-    static constexpr int KB = R <= 16 ? (R == 8 ? 2 : 4) : (R == 32 ? 2 : 1);   // units per step
+    static constexpr int KB = shrink_wave_units(R);            // units per step
     static_assert(!LINES || KB * KU == 128, "whole-line rows: a step is 256 bytes of a row");
 
     int lane, g, i16, h_in;
