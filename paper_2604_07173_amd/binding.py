@@ -57,6 +57,7 @@ class _Segments(C.Structure):
 
 
 _lib = None
+_pycall = None           # the extension module that converts the layer calls' arguments (csrc/pycall.cpp)
 
 
 def lib_path() -> str:
@@ -165,8 +166,21 @@ def load_library():
     lib.lora_provision_min_cache.argtypes = [dp, i32, C.c_double, C.c_double, C.POINTER(C.c_int), dp]
     lib.lora_provision_memory_bytes.restype = C.c_int64
     lib.lora_provision_memory_bytes.argtypes = [i32, C.c_int64]
+    global _pycall
+    if not os.path.exists(os.path.join(os.path.dirname(path), "_pycall.so")):
+        raise RuntimeError("_pycall.so is not built; run `python -m paper_2604_07173_amd.build`")
+    from . import _pycall as calls
+    calls.bind({name: C.cast(getattr(lib, name), vp).value for name in EXPORTED_SYMBOLS}, _stream)
+    _pycall = calls
     _lib = lib
     return lib
+
+
+def _calls():
+    """The layer calls of the extension module (loads the library on first use)."""
+    if _pycall is None:
+        load_library()
+    return _pycall
 
 
 def lora_strerror(status: int) -> str:
@@ -194,7 +208,10 @@ def _addr(t) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
-        return int(torch.cuda.current_stream().cuda_stream) or None
+        current = int(torch.cuda.current_stream().cuda_stream) or None
+        if _pycall is not None:      # the device is initialised now: from here on without Stream objects
+            _pycall.use_current_stream(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        return current
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
@@ -283,9 +300,9 @@ def lora_pool_load_unit(pool, adapter, layer, expert, proj, A, B, stream=None):
 
 
 def lora_pool_load_adapter_layer(pool, adapter, layer, src, stream=None):
-    _check(load_library().lora_pool_load_adapter_layer(_h(pool), adapter, layer, _addr(src),
-                                                       _stream(stream)),
-           "lora_pool_load_adapter_layer")
+    rc = _calls().load_adapter_layer(pool, adapter, layer, src, stream)
+    if rc:
+        _check(rc, "lora_pool_load_adapter_layer")
 
 
 def lora_pool_adapter_layer_bytes(pool, adapter) -> int:
@@ -384,10 +401,9 @@ class Segments:
 
 
 def lora_build_segments(pool, adapter_id, expert_id, P: int, seg: Segments, stream=None):
-    _check(load_library().lora_build_segments(_h(pool), _addr(adapter_id), _addr(expert_id), P,
-                                              C.byref(seg.c), _addr(seg.ws),
-                                              seg.ws.numel(), _stream(stream)),
-           "lora_build_segments")
+    rc = _calls().build_segments(pool, adapter_id, expert_id, P, seg, stream)
+    if rc:
+        _check(rc, "lora_build_segments")
 
 
 def lora_v_bytes(pool, proj: int, P: int) -> int:
@@ -407,9 +423,9 @@ def lora_expand(pool, layer, proj, v, seg: Segments, y, ldy, out_dtype=LORA_DTYP
 
 def lora_apply(pool, layer, proj, x, ldx, src_row, seg: Segments, y, ldy, v,
                out_dtype=LORA_DTYPE_BF16, stream=None):
-    _check(load_library().lora_apply(_h(pool), layer, proj, _addr(x), ldx, _addr(src_row),
-                                     C.byref(seg.c), _addr(y), ldy, out_dtype, _addr(v),
-                                     _stream(stream)), "lora_apply")
+    rc = _calls().apply(pool, layer, proj, x, ldx, src_row, seg, y, ldy, v, out_dtype, stream)
+    if rc:
+        _check(rc, "lora_apply")
 
 
 def lora_group_ws_bytes(pool, proj0: int, n_proj: int, P: int) -> int:
@@ -428,25 +444,18 @@ def lora_group_launches(pool, proj0: int, n_proj: int, P: int, seg: Segments,
 def lora_apply_group(pool, layer, proj0, x, ldx, src_row, seg: Segments, ys, ldys, ws,
                      out_dtype=LORA_DTYPE_BF16, stream=None):
     """ys / ldys: one output tensor and row stride per projection of the group."""
-    n = len(ys)
-    y_arr = (C.c_void_p * n)(*[_addr(y) for y in ys])
-    ld_arr = (C.c_int64 * n)(*[int(v) for v in ldys])
-    _check(load_library().lora_apply_group(_h(pool), layer, proj0, n, _addr(x), ldx, _addr(src_row),
-                                           C.byref(seg.c), y_arr, ld_arr, out_dtype, _addr(ws),
-                                           ws.numel() * ws.element_size(), _stream(stream)),
-           "lora_apply_group")
+    rc = _calls().apply_group(pool, layer, proj0, x, ldx, src_row, seg, ys, ldys, ws, out_dtype, stream)
+    if rc:
+        _check(rc, "lora_apply_group")
 
 
 def lora_build_apply_group(pool, layer, proj0, x, ldx, src_row, adapter_id, expert_id, P: int,
                            seg: Segments, ys, ldys, ws, out_dtype=LORA_DTYPE_BF16, stream=None):
     """lora_build_segments + lora_apply_group in one call (the first group of a layer call)."""
-    n = len(ys)
-    y_arr = (C.c_void_p * n)(*[_addr(y) for y in ys])
-    ld_arr = (C.c_int64 * n)(*[int(v) for v in ldys])
-    _check(load_library().lora_build_apply_group(
-        _h(pool), layer, proj0, n, _addr(x), ldx, _addr(src_row), _addr(adapter_id), _addr(expert_id), P,
-        C.byref(seg.c), _addr(seg.ws), seg.ws.numel(), y_arr, ld_arr, out_dtype, _addr(ws),
-        ws.numel() * ws.element_size(), _stream(stream)), "lora_build_apply_group")
+    rc = _calls().build_apply_group(pool, layer, proj0, x, ldx, src_row, adapter_id, expert_id, P, seg, ys, ldys, ws,
+                                    out_dtype, stream)
+    if rc:
+        _check(rc, "lora_build_apply_group")
 
 
 def lora_build_apply_launches(pool, proj0: int, n_proj: int, P: int, out_dtype=LORA_DTYPE_BF16) -> int:
@@ -463,22 +472,17 @@ def lora_moe_ws_bytes(pool, P: int) -> int:
 def lora_moe_build_apply(pool, layer, which, inp, ld_in, token_of_pair, adapter_id, expert_id, P: int,
                          seg: Segments, y0, y1, ldy, ws, ws_bytes=None, stream=None):
     """lora_build_segments + lora_moe_apply in one call."""
-    if ws_bytes is None:
-        ws_bytes = ws.numel() * ws.element_size()
-    _check(load_library().lora_moe_build_apply(
-        _h(pool), layer, which, _addr(inp), ld_in, _addr(token_of_pair), _addr(adapter_id),
-        _addr(expert_id), P, C.byref(seg.c), _addr(seg.ws), seg.ws.numel(), _addr(y0), _addr(y1), ldy,
-        _addr(ws), ws_bytes, _stream(stream)), "lora_moe_build_apply")
+    rc = _calls().moe_build_apply(pool, layer, which, inp, ld_in, token_of_pair, adapter_id, expert_id, P, seg, y0, y1,
+                                  ldy, ws, ws_bytes, stream)
+    if rc:
+        _check(rc, "lora_moe_build_apply")
 
 
 def lora_moe_apply(pool, layer, which, inp, ld_in, token_of_pair, seg: Segments, y0, y1, ldy,
                    ws, ws_bytes=None, stream=None):
-    if ws_bytes is None:
-        ws_bytes = ws.numel() * ws.element_size()
-    _check(load_library().lora_moe_apply(_h(pool), layer, which, _addr(inp), ld_in,
-                                         _addr(token_of_pair), C.byref(seg.c), _addr(y0),
-                                         _addr(y1), ldy, _addr(ws), ws_bytes, _stream(stream)),
-           "lora_moe_apply")
+    rc = _calls().moe_apply(pool, layer, which, inp, ld_in, token_of_pair, seg, y0, y1, ldy, ws, ws_bytes, stream)
+    if rc:
+        _check(rc, "lora_moe_apply")
 
 
 def lora_moe_apply_static(pool, layer, which, inp, ld_in, token_of_pair, seg: Segments, y0, y1, ldy,
@@ -513,12 +517,10 @@ def lora_moe_combine_ws_bytes(pool, P: int) -> int:
 
 def lora_moe_down_combine(pool, layer, hmid, ld_in, adapter_id, expert_id, seg: Segments, route_w,
                           top_k, y_tok, ldy, ws, ws_bytes=None, stream=None):
-    if ws_bytes is None:
-        ws_bytes = ws.numel() * ws.element_size()
-    _check(load_library().lora_moe_down_combine(_h(pool), layer, _addr(hmid), ld_in, _addr(adapter_id),
-                                                _addr(expert_id), C.byref(seg.c), _addr(route_w),
-                                                int(top_k), _addr(y_tok), ldy, _addr(ws), ws_bytes,
-                                                _stream(stream)), "lora_moe_down_combine")
+    rc = _calls().moe_down_combine(pool, layer, hmid, ld_in, adapter_id, expert_id, seg, route_w, int(top_k), y_tok,
+                                   ldy, ws, ws_bytes, stream)
+    if rc:
+        _check(rc, "lora_moe_down_combine")
 
 
 # ---- cache provisioning (include/lora_provision.h): host arrays in, numbers out ----------------

@@ -5,10 +5,12 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "liblora.so")
+PYCALL_PATH = os.path.join(PKG_DIR, "_pycall.so")           # the binding's argument conversion (csrc/pycall.cpp)
 SOURCES = ["api.hip", "pack.hip", "segments.hip", "segments_large.hip", "shrink.hip", "expand.hip",
            "shrink_decode.hip", "expand_decode.hip", "fused_decode.hip", "combine.hip", "provision.cpp"]
 HEADERS = ["lora_internal.h", "lora_layout.h", "lora_device.h", "expand_common.h", "expand_item.h", "shrink_wave.h", "segments_common.h", "segments_inline.h", os.path.join("..", "..", "include", "lora.h"),
@@ -33,10 +35,10 @@ def hipcc() -> str:
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(PYCALL_PATH):
         return True
-    t = os.path.getmtime(LIB_PATH)
-    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
+    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(PYCALL_PATH))
+    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS + ["pycall.cpp"]]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
@@ -51,6 +53,12 @@ def build(verbose: bool = False, jobs: int = 7, extra_flags=(), out: str = LIB_P
     os.makedirs(objdir, exist_ok=True)
     procs = []
     objs = []
+    if out == LIB_PATH:
+        cmd = ["g++", *HOST_FLAGS, "-shared", "-I", sysconfig.get_paths()["include"],
+               os.path.join(CSRC, "pycall.cpp"), "-o", PYCALL_PATH]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        procs.append(("pycall.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
     for src in SOURCES:
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
         objs.append(obj)
@@ -74,7 +82,7 @@ def _drain(procs):
         # the host pass does not know the target feature and says so; that is harmless
         text = "\n".join(l for l in text.splitlines() if "packed-fp32-ops" not in l)
         if pr.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{text}")
+            raise RuntimeError(f"compilation of {src} failed:\n{text}")
         if text.strip():
             print(text, file=sys.stderr)
     procs.clear()

@@ -226,12 +226,12 @@ struct KSplit {
 };
 
 // How the K range of a shrink is cut into parts: enough work items to fill the chip when the
-// batch has few tiles, and no part longer than kPartKBlocks K-blocks.  Depends only on the
-// pool and P, so lora_shrink, lora_expand and lora_v_bytes agree.
-KSplit ksplit_of(const lora_pool *p, int proj, int P)
+// batch has few tiles, and no part longer than kPartKBlocks K-blocks.  Depends only on the pool,
+// P and the tile height, so lora_shrink, lora_expand and lora_v_bytes agree.
+KSplit ksplit_of(const lora_pool *p, int proj, int P, int tile_rows)
 {
     const int kblocks = kblocks_of(p->d.proj[proj].h_in, p->d.rank);
-    if (pick_tile_rows(p, P) == kDecodeTileRows) {
+    if (tile_rows == kDecodeTileRows) {
         // decode: parts of about kb_target K-blocks, more of them when the batch has so few
         // tiles that the chip would not be filled otherwise, at most max_parts
         static const int kb_target = tune_int("LORA_DEC_KB_PER_PART", 32, 4, 4096);
@@ -328,6 +328,22 @@ size_t parts_bytes(const lora_pool *pool, int n_parts, int P)
     return align_up((size_t)n_parts * std::max(P, 1) * pool->d.rank * sizeof(float), 256);
 }
 
+// bytes of one projection's intermediate
+size_t v_bytes(const lora_pool *pool, int proj, int P, int tile_rows)
+{
+    size_t n = parts_bytes(pool, ksplit_of(pool, proj, P, tile_rows).ws_parts, P);
+    // long-segment batches: the expand keeps its operand images behind the K parts
+    if (tile_rows == kTileRows)
+        n += align_up(expand_image_bytes(pool->d.rank, tiles_upper_bound(pool, P, kTileRows)), 256);
+    return n;
+}
+
+// bytes of the workspace of a MoE application
+size_t moe_ws_bytes(const lora_pool *pool, int P, int tile_rows)
+{
+    return std::max(2 * v_bytes(pool, 0, P, tile_rows), v_bytes(pool, 2, P, tile_rows));
+}
+
 // launch parameters of the shrink of a group (decode kernels: complete; long kernels: all but
 // the per-launch projection fields)
 // Cache hints of the activation streams (the weights are always streamed: they are read once).
@@ -358,7 +374,7 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
                            const int32_t *src_row, const lora_segments *seg)
 {
     const lora_proj_desc &pd = pool->d.proj[g.proj0];
-    const KSplit ks = ksplit_of(pool, g.proj0, seg->P);
+    const KSplit ks = ksplit_of(pool, g.proj0, seg->P, seg->tile_rows);
     ShrinkParams sp;
     memset(&sp, 0, sizeof sp);
     sp.units = pool->device_table() + pool->table_index(layer, 0, 0, 0);
@@ -441,7 +457,7 @@ int do_expand(const lora_pool *pool, int layer, const Group &g, const lora_segme
 int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_segments *seg,
                   int out_dtype, ExpandParams &ep)
 {
-    const KSplit ks = ksplit_of(pool, g.proj0, seg->P);
+    const KSplit ks = ksplit_of(pool, g.proj0, seg->P, seg->tile_rows);
     memset(&ep, 0, sizeof ep);
     ep.units = pool->device_table() + pool->table_index(layer, 0, 0, 0);
     ep.n_proj = pool->d.n_proj;
@@ -600,7 +616,7 @@ bool inline_build_ok(const lora_pool *pool, const Group &g, const lora_segments 
         return false;
     if (seg->tile_rows != kDecodeTileRows) return false;
     // the one-launch kernel and the K-split shrink can; the wave-per-tile shrink cannot
-    return fused_plan(pool, g, seg, out_dtype, nullptr, nullptr) || !ksplit_of(pool, g.proj0, seg->P).wave_per_tile;
+    return fused_plan(pool, g, seg, out_dtype, nullptr, nullptr) || !ksplit_of(pool, g.proj0, seg->P, seg->tile_rows).wave_per_tile;
 }
 
 // shrink then expand of a group: one launch where that is possible, else two.  `build`: the
@@ -1073,7 +1089,7 @@ static int prepare_segments(const lora_pool *pool, const int32_t *adapter_id, co
     sp.counts = seg->counts;
     sp.status = seg->status;
     seg->P = P;
-    seg->tile_rows = pick_tile_rows(pool, P);
+    seg->tile_rows = sp.tile_rows;
     seg->n_keys = pool->d.n_adapters * pool->d.n_experts;
     seg->reserved = 0;
     return LORA_OK;
@@ -1092,12 +1108,7 @@ int lora_build_segments(const lora_pool *pool, const int32_t *adapter_id, const 
 size_t lora_v_bytes(const lora_pool *pool, int proj, int P)
 {
     if (check_pool(pool) != LORA_OK || proj < 0 || proj >= pool->d.n_proj || P < 0) return 0;
-    const KSplit ks = ksplit_of(pool, proj, P);
-    size_t n = parts_bytes(pool, ks.ws_parts, P);
-    // long-segment batches: the expand keeps its operand images behind the K parts
-    if (pick_tile_rows(pool, P) == kTileRows)
-        n += align_up(expand_image_bytes(pool->d.rank, tiles_upper_bound(pool, P, kTileRows)), 256);
-    return n;
+    return v_bytes(pool, proj, P, pick_tile_rows(pool, P));
 }
 
 int lora_shrink(const lora_pool *pool, int layer, int proj, const void *x, int64_t ldx,
@@ -1193,12 +1204,12 @@ static int apply_group_impl(const lora_pool *pool, int layer, int proj0, int n_p
     if (rc != LORA_OK) return rc;
     if (!ws) return LORA_ERR_INVALID_ARG;
     if (!aligned(ws, 16)) return LORA_ERR_MISALIGNED;
-    if (ws_bytes < lora_group_ws_bytes(pool, proj0, n_proj, seg->P)) return LORA_ERR_BUFFER_TOO_SMALL;
+    const size_t vb = v_bytes(pool, proj0, seg->P, seg->tile_rows);
+    if (ws_bytes < (size_t)n_proj * vb) return LORA_ERR_BUFFER_TOO_SMALL;
     Group g;
     memset(&g, 0, sizeof g);
     g.proj0 = proj0;
     g.n = n_proj;
-    const size_t vb = lora_v_bytes(pool, proj0, seg->P);
     for (int j = 0; j < n_proj; ++j) {
         rc = check_act(y[j], ldy[j], d.proj[proj0 + j].h_out, out_dtype == LORA_DTYPE_F32 ? 4 : 2);
         if (rc != LORA_OK) return rc;
@@ -1273,7 +1284,7 @@ int lora_group_launches(const lora_pool *pool, int proj0, int n_proj, int out_dt
 size_t lora_moe_ws_bytes(const lora_pool *pool, int P)
 {
     if (check_pool(pool) != LORA_OK || pool->d.n_proj < 3 || P < 0) return 0;
-    return std::max(2 * lora_v_bytes(pool, 0, P), lora_v_bytes(pool, 2, P));
+    return moe_ws_bytes(pool, P, pick_tile_rows(pool, P));
 }
 
 }  // extern "C"
@@ -1295,7 +1306,7 @@ int moe_common_checks(const lora_pool *pool, int layer, int which, const lora_se
     if (seg->P == 0) return LORA_OK;
     if (!ws) return LORA_ERR_INVALID_ARG;
     if (!aligned(ws, 16)) return LORA_ERR_MISALIGNED;
-    if (ws_bytes < lora_moe_ws_bytes(pool, seg->P)) return LORA_ERR_BUFFER_TOO_SMALL;
+    if (ws_bytes < moe_ws_bytes(pool, seg->P, seg->tile_rows)) return LORA_ERR_BUFFER_TOO_SMALL;
     return LORA_OK;
 }
 
@@ -1330,7 +1341,7 @@ Group moe_group(const lora_pool *pool, int which, const lora_segments *seg, void
     if (which == LORA_MOE_UPGATE) {
         g.proj0 = 0;
         g.n = 2;
-        g.v[1] = reinterpret_cast<float *>(static_cast<char *>(ws) + lora_v_bytes(pool, 0, seg->P));
+        g.v[1] = reinterpret_cast<float *>(static_cast<char *>(ws) + v_bytes(pool, 0, seg->P, seg->tile_rows));
         g.y[1] = y1;
         g.ldy[1] = ldy;
     } else {
@@ -1470,7 +1481,7 @@ int lora_moe_down_combine(const lora_pool *pool, int layer, const void *hmid, in
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int h_out = d.proj[2].h_out;
     uint16_t *pair = reinterpret_cast<uint16_t *>(static_cast<char *>(ws) +
-                                                  align_up(lora_moe_ws_bytes(pool, seg->P), 256));
+                                                  align_up(moe_ws_bytes(pool, seg->P, seg->tile_rows), 256));
     // 1. shrink of the down projection, as in lora_moe_apply
     rc = moe_shrink_launch(pool, layer, LORA_MOE_DOWN, hmid, ld_in, nullptr, seg, ws, st);
     if (rc != LORA_OK) return rc;
