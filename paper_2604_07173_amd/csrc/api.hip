@@ -1,6 +1,7 @@
 // C-ABI entry points: argument checks, pool bookkeeping, launch geometry.
 // Every check that can be made on the host happens before the first HIP call, so a bad
 // call costs nothing on the device and can be exercised on a machine without a GPU.
+#include <limits.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -556,51 +557,37 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
 // Shrink and expand of a group as one launch (fused_decode.hip): every workgroup repeats the
 // shrink of its tile and projection and expands a slice of the output columns, so the launch
 // needs no hand-off between workgroups but reads A once per slice (from the L2 after the first).
-// Worth it only for small decode batches with short inputs: few tiles (the repeated reads stay
-// small against the bytes of B and y, and a second launch would cost more than it moves) and a
-// K range that four waves get through quickly.  Returns false if the group is not eligible;
-// otherwise fills the slicing of ep (n_slices, cps, slice0) and the grid.
+// Worth it only for small decode batches with short inputs: few tiles and a K range that the waves
+// of a workgroup get through quickly (kFusedMaxWork).  Returns false if the group is not
+// eligible; otherwise fills the slicing of ep (slice0) and the grid.
 bool fused_plan(const lora_pool *pool, const Group &g, const lora_segments *seg, int out_dtype,
                 ShrinkParams *sp, ExpandParams *ep)
 {
     static const int enabled = tune_int("LORA_FUSED", 1, 0, 1);
     static const int max_k = tune_int("LORA_FUSED_MAX_K", kFusedMaxK, 8, 1 << 20);
     static const int max_tiles = tune_int("LORA_FUSED_MAX_TILES", kFusedMaxTiles, 1, 1 << 20);
-    static const int min_chunks = tune_int("LORA_FUSED_MIN_CHUNKS", kFusedMinChunks, 1, 1 << 20);
-    static const int want_wgs = tune_int("LORA_FUSED_WGS", kFusedWorkgroups, 1, 1 << 20);
+    static const int max_chunks = tune_int("LORA_FUSED_MAX_CHUNKS", kFusedMaxChunks, 1, 1 << 20);
     if (!enabled || seg->tile_rows != kDecodeTileRows || out_dtype != LORA_DTYPE_BF16 || g.overwrite)
         return false;
     if (pool->d.proj[g.proj0].h_in > max_k) return false;
-    {
-        static const int max_chunks = tune_int("LORA_FUSED_MAX_CHUNKS", kFusedMaxChunks, 1, 1 << 20);
-        int chunks = 0;
-        for (int j = 0; j < g.n; ++j) chunks += chunks_of(pool->d.proj[g.proj0 + j].h_out);
-        if (chunks > max_chunks) return false;
-    }
-    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(pool, seg->P, kDecodeTileRows));
-    if (tub > max_tiles) return false;
-    if (!sp || !ep) return true;
-    // slices per projection: enough workgroups to occupy the chip, but at least min_chunks
-    // chunks per slice (a workgroup repeats a whole shrink for them)
-    int total_chunks = 0;
-    for (int j = 0; j < g.n; ++j) total_chunks += chunks_of(pool->d.proj[g.proj0 + j].h_out);
-    const double per_tile = std::max(1.0, (double)want_wgs / (double)tub);
-    ep->slice0[0] = 0;
+    int slice0[kMaxFused + 1] = {0}, chunks = 0;          // workgroup items of a tile: a chunk per wave
     for (int j = 0; j < g.n; ++j) {
         const int n = chunks_of(pool->d.proj[g.proj0 + j].h_out);
-        int slices = (int)std::lround(per_tile * n / total_chunks);
-        slices = std::max(1, std::min(slices, std::max(1, n / min_chunks)));
-        int cps = (n + slices - 1) / slices;
-        cps = std::min(n, (cps + 1) & ~1);                      // even: two chunks are in flight
-        ep->cps[j] = cps;
-        ep->n_slices[j] = (n + cps - 1) / cps;
-        ep->slice0[j + 1] = ep->slice0[j] + ep->n_slices[j];
+        chunks += n;
+        slice0[j + 1] = slice0[j] + (n + kFusedWaves - 1) / kFusedWaves;
     }
-    for (int j = g.n; j < kMaxFused; ++j) ep->slice0[j + 1] = ep->slice0[g.n];
+    if (chunks > max_chunks) return false;
+    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(pool, seg->P, kDecodeTileRows));
+    if (tub > max_tiles) return false;
+    static const int max_work = tune_int("LORA_FUSED_MAX_WORK", (int)kFusedMaxWork, 1, INT_MAX);
+    if (tub * slice0[g.n] * pool->d.rank * pool->d.proj[g.proj0].h_in > (int64_t)max_work * (pool->d.rank == 8 ? 2 : 1))
+        return false;
+    if (!sp || !ep) return true;
+    for (int j = 0; j <= kMaxFused; ++j) ep->slice0[j] = slice0[std::min(j, g.n)];
     sp->n_parts = 1;
     sp->kb_per_part = kblocks_of(pool->d.proj[g.proj0].h_in, pool->d.rank);
     ep->n_parts = 1;
-    sp->grid = (int)std::min<int64_t>(tub * ep->slice0[g.n], (int64_t)cu_count() * 8);
+    sp->grid = (int)(tub * slice0[g.n]);
     return true;
 }
 

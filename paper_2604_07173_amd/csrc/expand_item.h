@@ -1,6 +1,6 @@
-// The wave-level work of the decode expand (tiles of at most 16 rows), shared by the expand
-// kernel and the kernel that runs shrink and expand in one launch: one wave adds scale * v * B
-// to the rows of one tile over a run of 128-column chunks.
+// The wave-level work of the decode expand (tiles of at most 16 rows): one wave adds scale * v * B
+// to the rows of one tile over a run of 128-column chunks.  (The kernel that runs shrink and expand
+// in one launch uses ExpandWave on its own.)
 //
 // Prologue: the wave adds the K parts of the tile's v in a fixed order, applies the adapter's
 // scale and splits the result into bf16 hi + lo planes held in MFMA operand registers (hi = v
@@ -129,14 +129,9 @@ struct ExpandWave {
     }
 };
 
-// vlds: null = v comes from the K parts in global memory (p.v[pj]); otherwise the tile's summed v
-// already sits in LDS as [16][R] floats (the kernel that runs shrink and expand in one launch).
-// perm_lds: null = the sorted order comes from p.perm; otherwise from LDS (the kernel that also
-// builds the segments).
 template <int R, bool F32, int NI, bool OVW, bool YNT = false>
 __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, const Unit &unit, int pj,
-                                   int c0, int c1, int lane, const float *vlds = nullptr,
-                                   const uint16_t *perm_lds = nullptr)
+                                   int c0, int c1, int lane)
 {
     using Tile = ExpandTile<R>;
     constexpr int KS = Tile::KS, KV = Tile::KV, ESZ = F32 ? 4 : 2;
@@ -152,7 +147,7 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
         const int r = 4 * i + w.g;                       // row of result register i
         w.rok[i] = r < t.n_rows;
         const int at = t.row0 + min(r, t.n_rows - 1);
-        const int dst = perm_lds ? (int)perm_lds[at] : p.perm[at];       // wave-uniform choice
+        const int dst = p.perm[at];
         w.yrow[i] = static_cast<char *>(p.y[pj]) + (int64_t)dst * p.ldy[pj] * ESZ;
     }
 
@@ -194,18 +189,7 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
         }
     };
     typename ExpandWave<R, F32, NI, OVW, YNT>::Stage st[ExpandWave<R, F32, NI, OVW, YNT>::D];
-    if (vlds) {                                                  // wave-uniform
-        w.prefetch(c0, c1, st);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int h = 0; h < KV / 4; ++h) {
-                const f32x4 x = *reinterpret_cast<const f32x4 *>(vlds + (valid ? row : 0) * R +
-                                                                 Tile::jbase(w.g, ks) + 4 * h);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) s[ks][4 * h + q] = x[q];
-            }
-    } else if (p.n_parts == 1) {                                 // a single part: one load, no batch
+    if (p.n_parts == 1) {                                 // a single part: one load, no batch
         f32x4 one[KS][KV / 4];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -242,14 +226,13 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
 // quads is picked here (wave-uniform)
 template <int R, bool F32, bool OVW, bool YNT = false>
 __device__ inline void expand_tile_chunks(const ExpandParams &p, const lora_tile &t, const Unit &unit,
-                                          int pj, int c0, int c1, int lane, const float *vlds = nullptr,
-                                          const uint16_t *perm_lds = nullptr)
+                                          int pj, int c0, int c1, int lane)
 {
     switch ((t.n_rows + 3) >> 2) {
-    case 1: expand_item<R, F32, 1, OVW, YNT>(p, t, unit, pj, c0, c1, lane, vlds, perm_lds); break;
-    case 2: expand_item<R, F32, 2, OVW, YNT>(p, t, unit, pj, c0, c1, lane, vlds, perm_lds); break;
-    case 3: expand_item<R, F32, 3, OVW, YNT>(p, t, unit, pj, c0, c1, lane, vlds, perm_lds); break;
-    default: expand_item<R, F32, 4, OVW, YNT>(p, t, unit, pj, c0, c1, lane, vlds, perm_lds); break;
+    case 1: expand_item<R, F32, 1, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
+    case 2: expand_item<R, F32, 2, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
+    case 3: expand_item<R, F32, 3, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
+    default: expand_item<R, F32, 4, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
     }
 }
 

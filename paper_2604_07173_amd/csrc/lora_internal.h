@@ -26,16 +26,17 @@ constexpr int kKBlock = 32;          // K elements per MFMA step (v_mfma_f32_16x
 constexpr int kColChunk = 128;       // output columns one wave owns in expand
 constexpr int kPartKBlocks = 32;     // K-blocks one shrink workgroup reduces (1024 inputs)
 constexpr int kMaxParts = 64;
-// Shrink and expand in one launch (fused_decode.hip): limits and work split, measured on MI355X
-// with the Llama-3-8B query/key/value and output projections (rank 16, 4096 inputs): one launch
-// takes 10.3-10.5 us against 13.2-14.1 us for two up to 27 tiles, 12.7 against 14.2 at 41 tiles,
-// and the two are equal at 54 tiles; wide outputs (gate and up, 224 chunks) and long inputs
-// (down, 14336) are slower in one launch at every size.
+// Shrink and expand in one launch (fused_decode.hip): limits and work split, measured on MI355X.
+constexpr int kFusedWaves = 8;         // waves of a workgroup = 128-column chunks of a work item
 constexpr int kFusedMaxK = 4096;       // longest input
 constexpr int kFusedMaxChunks = 64;    // widest group, in 128-column chunks per tile
 constexpr int kFusedMaxTiles = 64;     // largest batch, as the host's upper bound of the tile count
-constexpr int kFusedMinChunks = 16;    // 128-column chunks a workgroup expands at least
-constexpr int kFusedWorkgroups = 1024; // workgroups aimed at
+// Work items x rank x inputs, that is half the bytes of A that all items together read.  A workgroup
+// fetches the whole A of its item at what one CU can pull, so one launch loses to two as that grows
+// (whole call in us, one launch / two; 4096 -> 4096, rank 16: 1 row 6.7 / 7.7, 8 rows, 2.1 M: 7.4 /
+// 8.4, 24 rows, 6.5 M: 8.8 / 8.6; rank 8, 24 rows, 3.3 M: 7.1 / 8.5; rank 64, 8 rows, 8.4 M: 16.2 /
+// 10.7; query/key/value of the Llama shapes, 8 rows, 3.1 M: two launches win by 2 us).
+constexpr int64_t kFusedMaxWork = 21ll << 17;      // twice that at rank 8, whose A is half the bytes of rank 16
 // Cache hints of the activation streams of the decode kernels, measured on MI355X.  Input rows that
 // are read once are streamed from kStreamXMiB on, and at ranks 8 and 16 fetched as whole lines.
 // Layer call in us, cacheable / streamed, by where the activations are when it starts (in HBM only;
@@ -181,7 +182,7 @@ struct CombineParams {
 // shrink and expand of a decode batch in one launch
 struct FusedParams {
     ShrinkParams s;          // n_parts = 1; v unused
-    ExpandParams e;          // n_slices / cps / slice0: workgroup items of a tile; v unused
+    ExpandParams e;          // slice0: workgroup items of a tile; v, cps unused
 };
 
 hipError_t launch_pack_A(const PackParams &p, hipStream_t s);

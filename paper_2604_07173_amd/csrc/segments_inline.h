@@ -11,7 +11,7 @@
 // writes the result to the caller's lora_segments for the launches that follow.
 //
 // Limits: kInlineMaxRows rows, kInlineMaxKeys keys, tiles of kDecodeTileRows rows, workgroups
-// of kInlineThreads threads.
+// of four waves and more (thread k < kInlineMaxKeys owns key k).
 //
 // Stability without order-defining atomics: the batch is cut into groups of 64 consecutive
 // rows, one wave handles a group at a time and ranks equal keys inside it by lane order (ballot
@@ -27,12 +27,9 @@ namespace lora {
 
 constexpr int kInlineMaxRows = 2048;
 constexpr int kInlineMaxKeys = 256;
-constexpr int kInlineThreads = 256;
-constexpr int kInlineWaves = kInlineThreads / 64;
 constexpr int kInlineGroups = kInlineMaxRows / 64;
-constexpr int kInlineGroupsPerWave = kInlineGroups / kInlineWaves;
 constexpr int kInlineMaxTiles = kInlineMaxRows / kDecodeTileRows + kInlineMaxKeys;
-static_assert(kInlineMaxKeys == kInlineThreads, "one key per thread");
+constexpr int kInlineKeyWaves = kInlineMaxKeys / 64;             // waves whose threads own a key
 
 typedef uint16_t InlineCounts[kInlineGroups][kInlineMaxKeys];     // 16 KiB, free again after the build
 
@@ -40,25 +37,28 @@ struct InlineSegments {                 // lives in LDS for the whole kernel
     uint16_t perm[kInlineMaxRows];
     lora_tile tiles[kInlineMaxTiles];
     unsigned key_start[kInlineMaxKeys];
-    unsigned wave_sums[kInlineWaves][3];
+    unsigned wave_sums[kInlineKeyWaves][3];
     unsigned status;
     int n_tiles;
 };
 
-// GPW: groups of 64 rows per wave that the code is unrolled for (batches of up to 256 * GPW rows)
-template <int GPW>
+// G: groups of 64 rows that the code is unrolled for (batches of up to 64 * G rows); NW: waves of the
+// workgroup
+template <int NW, int G>
 __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts &counts, InlineSegments &L,
                                                bool write_global)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int P = sp.P;
-    constexpr int G = GPW * kInlineWaves;               // groups looked at; those beyond the batch are empty
+    constexpr int GPW = (G + NW - 1) / NW;              // groups per wave; those beyond the batch are empty
+    static_assert(NW >= kInlineKeyWaves, "a thread per key");
+    static_assert(G % NW == 0 || G < NW, "the waves' groups are the first G");
 
-    // ids of this wave's groups (wave w takes groups w, w + 4, ...): all loads first
+    // ids of this wave's groups (wave w takes groups w, w + NW, ...): all loads first
     int a[GPW], e[GPW];
 #pragma unroll
     for (int u = 0; u < GPW; ++u) {
-        const int row = (w + kInlineWaves * u) * 64 + lane;
+        const int row = (w + NW * u) * 64 + lane;
         const int r = min(row, P - 1);                      // unconditional loads (P >= 1), then selects
         a[u] = sp.adapter_id[r];
         e[u] = sp.expert_id ? sp.expert_id[r] : 0;
@@ -67,7 +67,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     {
         const u32x4 zero = {0u, 0u, 0u, 0u};
         u32x4 *c4 = reinterpret_cast<u32x4 *>(&counts[0][0]);
-        for (int i = tid; i < G * (kInlineMaxKeys * 2 / 16); i += kInlineThreads) c4[i] = zero;
+        for (int i = tid; i < G * (kInlineMaxKeys * 2 / 16); i += 64 * NW) c4[i] = zero;
         if (tid == 0) L.status = 0;
     }
     __syncthreads();
@@ -97,7 +97,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     }
 #pragma unroll
     for (int u = 0; u < GPW; ++u) {
-        const int g = w + kInlineWaves * u;                 // wave-uniform
+        const int g = w + NW * u;                           // wave-uniform
         below[u] = lanes_below(m[u]);
         if (key[u] != kNoKey && below[u] == 0) counts[g][key[u]] = (uint16_t)(__popc(m[u].lo) + __popc(m[u].hi));
     }
@@ -105,8 +105,9 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     __syncthreads();
 
     // thread k: counts of key k per group -> rows of the key in earlier groups; its total
-    unsigned total = 0;
-    {
+    const bool owner = w < kInlineKeyWaves;             // wave-uniform
+    unsigned total = 0, my_tiles = 0, occ = 0, ir = 0, is = 0, it = 0;
+    if (owner) {
         unsigned c[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) c[g] = counts[g][tid];
@@ -115,19 +116,19 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
             counts[g][tid] = (uint16_t)total;
             total += c[g];
         }
-    }
-    const unsigned my_tiles = (total + kDecodeTileRows - 1) / kDecodeTileRows;
-    const unsigned occ = total ? 1u : 0u;
-    const unsigned ir = wave_incl_sum(total), is = wave_incl_sum(occ), it = wave_incl_sum(my_tiles);
-    if (lane == 63) {
-        L.wave_sums[w][0] = ir;
-        L.wave_sums[w][1] = is;
-        L.wave_sums[w][2] = it;
+        my_tiles = (total + kDecodeTileRows - 1) / kDecodeTileRows;
+        occ = total ? 1u : 0u;
+        ir = wave_incl_sum(total), is = wave_incl_sum(occ), it = wave_incl_sum(my_tiles);
+        if (lane == 63) {
+            L.wave_sums[w][0] = ir;
+            L.wave_sums[w][1] = is;
+            L.wave_sums[w][2] = it;
+        }
     }
     __syncthreads();
     unsigned row0 = ir - total, seg = is - occ, tile0 = it - my_tiles, P_act = 0, S = 0, n_tiles = 0;
 #pragma unroll
-    for (int k = 0; k < kInlineWaves; ++k) {
+    for (int k = 0; k < kInlineKeyWaves; ++k) {
         const unsigned r = L.wave_sums[k][0], s = L.wave_sums[k][1], t = L.wave_sums[k][2];
         P_act += r;
         S += s;
@@ -136,9 +137,9 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
         seg += k < w ? s : 0u;
         tile0 += k < w ? t : 0u;
     }
-    L.key_start[tid] = row0;
+    if (owner) L.key_start[tid] = row0;
     if (tid == 0) L.n_tiles = (int)n_tiles;
-    // tiles and segment record of my key
+    // tiles and segment record of my key (a thread without a key has no rows)
     for (unsigned j = 0; j < my_tiles; ++j) {
         lora_tile t;
         t.key = tid;
@@ -156,15 +157,15 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     // rows to their positions
 #pragma unroll
     for (int u = 0; u < GPW; ++u) {
-        const int g = w + kInlineWaves * u;
+        const int g = w + NW * u;
         if (key[u] != kNoKey)
             L.perm[L.key_start[key[u]] + counts[g][key[u]] + below[u]] = (uint16_t)(g * 64 + lane);
     }
     __syncthreads();
 
     if (write_global) {
-        for (unsigned i = tid; i < P_act; i += kInlineThreads) sp.perm[i] = (int32_t)L.perm[i];
-        for (unsigned i = tid; i < n_tiles; i += kInlineThreads) sp.tiles[i] = L.tiles[i];
+        for (unsigned i = tid; i < P_act; i += 64 * NW) sp.perm[i] = (int32_t)L.perm[i];
+        for (unsigned i = tid; i < n_tiles; i += 64 * NW) sp.tiles[i] = L.tiles[i];
         if (tid == 0) {
             sp.seg_start[S] = (int32_t)P_act;
             sp.counts[0] = (int32_t)S;
@@ -176,13 +177,14 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     }
 }
 
+template <int NW>
 __device__ inline void build_segments_inline(const SegParams &sp, InlineCounts &counts, InlineSegments &L,
                                              bool write_global)
 {
-    if (sp.P <= 256) build_segments_inline_n<1>(sp, counts, L, write_global);
-    else if (sp.P <= 512) build_segments_inline_n<2>(sp, counts, L, write_global);
-    else if (sp.P <= 1024) build_segments_inline_n<4>(sp, counts, L, write_global);
-    else build_segments_inline_n<kInlineGroupsPerWave>(sp, counts, L, write_global);
+    if (sp.P <= 256) build_segments_inline_n<NW, 4>(sp, counts, L, write_global);
+    else if (sp.P <= 512) build_segments_inline_n<NW, 8>(sp, counts, L, write_global);
+    else if (sp.P <= 1024) build_segments_inline_n<NW, 16>(sp, counts, L, write_global);
+    else build_segments_inline_n<NW, kInlineGroups>(sp, counts, L, write_global);
 }
 
 }  // namespace lora

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     w.xt = xt_all + (LINES ? wave * 256 : 0);
     int n_tiles;
     if constexpr (BUILD) {
-        build_segments_inline(p.seg, scratch.counts, built, blockIdx.x == 0);   // `built` is complete behind its last barrier
+        build_segments_inline<4>(p.seg, scratch.counts, built, blockIdx.x == 0);   // `built` is complete behind its last barrier
         n_tiles = built.n_tiles;
     } else {
         n_tiles = counts[2];
@@ -83,8 +83,14 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
         const int tile_ix = item / p.n_parts;
         const int part = item - tile_ix * p.n_parts;
         lora_tile t;
-        if constexpr (BUILD) t = built.tiles[tile_ix];
-        else t = tiles[tile_ix];
+        if constexpr (BUILD) {
+            t = built.tiles[tile_ix];                 // the same for every lane: scalars from here on
+            t.key = __builtin_amdgcn_readfirstlane(t.key);
+            t.row0 = __builtin_amdgcn_readfirstlane(t.row0);
+            t.n_rows = __builtin_amdgcn_readfirstlane(t.n_rows);
+        } else {
+            t = tiles[tile_ix];
+        }
 #pragma unroll
         for (int pj = 0; pj < NPROJ; ++pj)
             w.Ap[pj] = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].A;

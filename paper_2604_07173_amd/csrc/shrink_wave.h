@@ -134,13 +134,25 @@ struct ShrinkWave {
     // the contiguous range [kb_begin, kb_end)), two steps in flight
     __device__ inline void run(int kb_begin, int kb_end, int stride = KB)
     {
+        run(kb_begin, kb_end, stride, [] {});
+    }
+
+    // `between` issues loads of the caller's behind those of the first step, so that they are in flight
+    // while the wave works through its range
+    template <typename F>
+    __device__ inline void run(int kb_begin, int kb_end, int stride, F between)
+    {
 #pragma unroll
         for (int pj = 0; pj < NPROJ; ++pj)
 #pragma unroll
             for (int a = 0; a < NACC; ++a) acc[pj][a] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (kb_begin >= kb_end) return;
+        if (kb_begin >= kb_end) {
+            between();
+            return;
+        }
         Step s0, s1;
         load(kb_begin, kb_end, s0);
+        between();
         int kb0 = kb_begin;
         for (; kb0 + 2 * stride < kb_end; kb0 += 2 * stride) {
             load(kb0 + stride, kb_end, s1);
