@@ -30,7 +30,9 @@ namespace lora {
 // read (used when the update goes to a buffer of its own rather than into base rows).
 // YNT: the output rows are read and written with the streaming hint (for callers whose outputs
 // are not in a cache when the call starts, or are too large to be).
-template <int R, bool F32, int NI, bool OVW, bool YNT = false>
+// BNT: B is loaded with the streaming hint (it is read once), else left in the L2 for the other tiles
+// of the segment.
+template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true>
 struct ExpandWave {
     using Tile = ExpandTile<R>;
     static constexpr int KS = Tile::KS;
@@ -49,7 +51,7 @@ struct ExpandWave {
 
     __device__ inline void load(int c, typename Tile::B &b, YBuf &y) const
     {
-        Tile::template load_b<true>(Bp, c, lane, b);
+        Tile::template load_b<BNT>(Bp, c, lane, b);
         const int col = c * kColChunk + i16 * 8;
         const int colc = col < h_out ? col : 0;
 #pragma unroll
@@ -129,13 +131,14 @@ struct ExpandWave {
     }
 };
 
-template <int R, bool F32, int NI, bool OVW, bool YNT = false>
+template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true>
 __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, const Unit &unit, int pj,
                                    int c0, int c1, int lane)
 {
     using Tile = ExpandTile<R>;
     constexpr int KS = Tile::KS, KV = Tile::KV, ESZ = F32 ? 4 : 2;
-    ExpandWave<R, F32, NI, OVW, YNT> w;
+    using Wave = ExpandWave<R, F32, NI, OVW, YNT, BNT>;
+    Wave w;
     w.lane = lane;
     w.g = lane >> 4;
     w.i16 = lane & 15;
@@ -188,7 +191,7 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
                     for (int q = 0; q < 4; ++q) s[ks][4 * h + q] += in ? buf[u][ks][h][q] : 0.f;
         }
     };
-    typename ExpandWave<R, F32, NI, OVW, YNT>::Stage st[ExpandWave<R, F32, NI, OVW, YNT>::D];
+    typename Wave::Stage st[Wave::D];
     if (p.n_parts == 1) {                                 // a single part: one load, no batch
         f32x4 one[KS][KV / 4];
 #pragma unroll
@@ -232,7 +235,13 @@ __device__ inline void expand_tile_chunks(const ExpandParams &p, const lora_tile
     case 1: expand_item<R, F32, 1, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
     case 2: expand_item<R, F32, 2, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
     case 3: expand_item<R, F32, 3, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
-    default: expand_item<R, F32, 4, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
+    default:
+        // a full tile is most likely one of several of its segment: its B is worth keeping in the L2
+        if (p.share_b && t.n_rows == kDecodeTileRows)
+            expand_item<R, F32, 4, OVW, YNT, false>(p, t, unit, pj, c0, c1, lane);
+        else
+            expand_item<R, F32, 4, OVW, YNT>(p, t, unit, pj, c0, c1, lane);
+        break;
     }
 }
 
