@@ -261,19 +261,21 @@ KSplit ksplit_of(const lora_pool *p, int proj, int P, int tile_rows)
         k.ws_parts = (kblocks + per - 1) / per;
         // With three workgroups per CU and more the chip is full, and more parts only cost: at ranks
         // 8 and 16 three workgroups per CU are enough, and a short part is a whole number of rounds of
-        // the workgroup's four waves (a wave takes shrink_wave_units() K-blocks per step): one and a
-        // half rounds take as long as two.  Llama shapes at rank 16, 2048 rows of which 1792 share an
-        // adapter: 181 -> 164 us for the layer, 1024 rows 124 -> 113.5.  Not at ranks 32 and 64, where
-        // a part is two and four times the bytes (1024 rows: 171 against 178 us, 280 against 288), and
-        // not from two rounds on (448 K-blocks in eight parts of 56 against seven of 64: Mixtral
-        // shapes, 2048 tokens, 255 against 263 us).  The workspace keeps room for the finer split,
-        // so that a buffer sized for a batch also takes every smaller one.
+        // the workgroup's four waves (a wave takes shrink_wave_units() K-blocks per step) where that
+        // saves a part: one and a half rounds take as long as two.  Llama shapes at rank 16, 2048 rows
+        // of which 1792 share an adapter: 181 -> 164 us for the layer, 1024 rows 124 -> 113.5.  Not
+        // for tiles of a row or two, whose v is small (Mixtral shapes, 64 tokens: 46.6 against 46.9 us),
+        // nor at ranks 32 and 64, where a part is two and four times the bytes (1024 rows: 171
+        // against 178 us, 280 against 288), nor from two rounds on (448 K-blocks in eight parts of 56
+        // against seven of 64: Mixtral shapes, 2048 tokens, 255 against 263 us).  The workspace keeps
+        // room for the finer split, so that a buffer sized for a batch also takes every smaller one.
         static const int full = tune_int("LORA_DEC_SHRINK_FULL", 768, 1, 1 << 20);
         const int round = 4 * shrink_wave_units(p->d.rank);
-        if (p->d.rank <= 16 && tub * k.ws_parts >= full) {
+        if (p->d.rank <= 16 && P >= 4 * tub && tub * k.ws_parts >= full) {
             n = parts_for(full);
             per = ((kblocks + n - 1) / n + 3) / 4 * 4;
-            if (per < 2 * round) per = (per + round - 1) / round * round;
+            const int whole = (per + round - 1) / round * round;
+            if (per < 2 * round && (kblocks + whole - 1) / whole < (kblocks + per - 1) / per) per = whole;
         }
         k.kb_per_part = per;
         k.n_parts = (kblocks + per - 1) / per;
