@@ -481,7 +481,6 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         static const int cpi_max = tune_int("LORA_DEC_CHUNKS_PER_ITEM", 8, 1, 4096);
         static const int item_bytes = tune_int("LORA_DEC_ITEM_BYTES", 12288, 1024, 1 << 24);
         static const int want_items = tune_int("LORA_DEC_EXPAND_ITEMS", 4096, 1, 1 << 22);
-        static const int per_cu = tune_int("LORA_DEC_EXPAND_WGS_PER_CU", 16, 1, 64);
         ep.proj0 = g.proj0;
         ep.n_fused = g.n;
         ep.overwrite = g.overwrite && out_dtype == LORA_DTYPE_BF16;
@@ -534,6 +533,14 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         // is streamed at every length (cached: 255 -> 264 us for 2048 tokens).
         ep.share_b = long_segments;
         const int64_t wave_items = (tub + ep.tile_group - 1) / ep.tile_group * ep.tile_group * ep.slice0[g.n];
+        // The hardware hands workgroups out as others finish, which evens out tiles of different heights
+        // better than a workgroup's walk over several items, and costs a launch of its own each: worth it
+        // where an item is long.  16 / 32 / 64 workgroups per CU: rank 64, 1024 tokens over 512 adapters
+        // 940 / 932 / 924 us; long segments at rank 16 (Mixtral shapes, 2048 tokens) 247 / 244 / 245, at
+        // rank 8 212 / 209 / 210; 512 tokens 104.4 / 105.2 / 105.2; rank 32, 2048 tokens 356 / 357 / 359.
+        static const int per_cu_env = tune_int("LORA_DEC_EXPAND_WGS_PER_CU", 0, 0, 64);
+        const int per_cu = per_cu_env ? per_cu_env
+                                      : pool->d.rank == 64 ? 64 : long_segments && pool->d.rank <= 16 ? 32 : 16;
         ep.grid = (int)std::min<int64_t>((wave_items + ep.waves - 1) / ep.waves,
                                          (int64_t)cu_count() * per_cu);
         return LORA_OK;
