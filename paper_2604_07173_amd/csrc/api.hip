@@ -204,6 +204,12 @@ int64_t tiles_upper_bound(const lora_pool *p, int P, int tile_rows)
 
 // Rows per tile for a batch: decode batches (few rows per adapter/expert cell) get the
 // 16-row tiles of the decode kernels, batches with long segments the 32-row tiles.
+bool long_batch(const lora_pool *p, int P)
+{
+    const int64_t keys = (int64_t)p->d.n_adapters * p->d.n_experts;
+    return (int64_t)P >= 32 * keys && (int64_t)P * p->d.rank >= kLongMinRowsTimesRank;
+}
+
 int pick_tile_rows(const lora_pool *p, int P)
 {
     if (p->d.rank == 8) return kDecodeTileRows;      // the 32-row shrink has no rank-8 form
@@ -216,8 +222,22 @@ int pick_tile_rows(const lora_pool *p, int P)
     // 1024 and 2048 rows: the long-segment kernels pay off from rows x rank = 2^17 on (their two
     // extra launches and 128-row work items need that much to amortise), if the segments are
     // long enough to fill 32-row tiles at all.
+    return long_batch(p, P) ? kTileRows : kDecodeTileRows;
+}
+
+// Which kernels a batch of 32-row tiles runs on: the long-segment kernels, or the decode kernels on the
+// halves of its tiles.  At rank 16 the decode kernels are ahead below kLongMinRowsRank16 rows and below
+// kLongRowsPerKeyRank16 rows per key, where the long shrink's blocks of 128 rows are not filled.  Layer
+// call in us, decode / long: Mixtral shapes, 256 keys, 4096 tokens (32 rows per key) 392 / 464, 6144
+// tokens 546 / 565, 8192 tokens 698 / 738; llama shapes, 64 keys, 8192 rows 165 / 169, 16384 rows
+// 310 / 288; 8192 rows of 16 requests 140 / 150.  At ranks 32 and 64 the long-segment kernels win
+// wherever they are picked at all (32 rows per key, Mixtral shapes, 4096 tokens: 497 / 421 and 746 / 516).
+bool long_kernels(const lora_pool *p, int P, int tile_rows)
+{
+    if (tile_rows != kTileRows) return false;
+    if (!long_batch(p, P)) return true;              // 32-row tiles by the test switch: for the long-segment kernels
     const int64_t keys = (int64_t)p->d.n_adapters * p->d.n_experts;
-    return ((int64_t)P >= 32 * keys && (int64_t)P * p->d.rank >= kLongMinRowsTimesRank) ? kTileRows : kDecodeTileRows;
+    return p->d.rank != 16 || (P >= kLongMinRowsRank16 && P >= kLongRowsPerKeyRank16 * keys);
 }
 
 struct KSplit {
@@ -229,75 +249,105 @@ struct KSplit {
 // How the K range of a shrink is cut into parts: enough work items to fill the chip when the
 // batch has few tiles, and no part longer than kPartKBlocks K-blocks.  Depends only on the pool,
 // P and the tile height, so lora_shrink, lora_expand and lora_v_bytes agree.
-KSplit ksplit_of(const lora_pool *p, int proj, int P, int tile_rows)
+KSplit ksplit_decode(const lora_pool *p, int proj, int P)
 {
     const int kblocks = kblocks_of(p->d.proj[proj].h_in, p->d.rank);
-    if (tile_rows == kDecodeTileRows) {
-        // decode: parts of about kb_target K-blocks, more of them when the batch has so few
-        // tiles that the chip would not be filled otherwise, at most max_parts
-        static const int kb_target = tune_int("LORA_DEC_KB_PER_PART", 32, 4, 4096);
-        static const int max_parts = tune_int("LORA_DEC_MAX_PARTS", 8, 1, kMaxParts);
-        static const int want_wgs = tune_int("LORA_DEC_SHRINK_ITEMS", 1024, 1, 1 << 20);
-        const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(p, P, kDecodeTileRows));
-        // thousands of tiles over a short K range: one wave per tile, K not split at all
-        static const int wpt = tune_int("LORA_DEC_WAVE_PER_TILE", -1, -1, 1);
-        static const int wpt_tiles = tune_int("LORA_DEC_WAVE_PER_TILE_MIN_TILES", 4096, 1, 1 << 20);
-        static const int wpt_k = tune_int("LORA_DEC_WAVE_PER_TILE_MAX_K", 4096, 32, 1 << 20);
-        if (wpt == 1 || (wpt < 0 && tub >= wpt_tiles && p->d.proj[proj].h_in <= wpt_k)) {
-            KSplit k;
-            k.kb_per_part = kblocks;
-            k.n_parts = k.ws_parts = 1;
-            k.wave_per_tile = true;
-            return k;
-        }
-        const int by_size = std::max(1, (kblocks + kb_target - 1) / kb_target);
-        auto parts_for = [&](int wgs) {
-            const int n = std::max<int>(by_size, (int)std::min<int64_t>((wgs + tub - 1) / tub, kblocks / 4));
-            return std::min(std::max(n, 1), max_parts);
-        };
+    // decode: parts of about kb_target K-blocks, more of them when the batch has so few
+    // tiles that the chip would not be filled otherwise, at most max_parts
+    static const int kb_target = tune_int("LORA_DEC_KB_PER_PART", 32, 4, 4096);
+    static const int max_parts = tune_int("LORA_DEC_MAX_PARTS", 8, 1, kMaxParts);
+    static const int want_wgs = tune_int("LORA_DEC_SHRINK_ITEMS", 1024, 1, 1 << 20);
+    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(p, P, kDecodeTileRows));
+    // thousands of tiles over a short K range: one wave per tile, K not split at all
+    static const int wpt = tune_int("LORA_DEC_WAVE_PER_TILE", -1, -1, 1);
+    static const int wpt_tiles = tune_int("LORA_DEC_WAVE_PER_TILE_MIN_TILES", 4096, 1, 1 << 20);
+    static const int wpt_k = tune_int("LORA_DEC_WAVE_PER_TILE_MAX_K", 4096, 32, 1 << 20);
+    if (wpt == 1 || (wpt < 0 && tub >= wpt_tiles && p->d.proj[proj].h_in <= wpt_k)) {
         KSplit k;
-        int n = parts_for(want_wgs);
-        int per = ((kblocks + n - 1) / n + 3) / 4 * 4;
-        k.ws_parts = (kblocks + per - 1) / per;
-        // With three workgroups per CU and more the chip is full, and more parts only cost: at ranks
-        // 8 and 16 three workgroups per CU are enough, and a short part is a whole number of rounds of
-        // the workgroup's four waves (a wave takes shrink_wave_units() K-blocks per step) where that
-        // saves a part: one and a half rounds take as long as two.  Llama shapes at rank 16, 2048 rows
-        // of which 1792 share an adapter: 181 -> 164 us for the layer, 1024 rows 124 -> 113.5.  Not
-        // for tiles of a row or two, whose v is small (Mixtral shapes, 64 tokens: 46.6 against 46.9 us),
-        // nor at ranks 32 and 64, where a part is two and four times the bytes (1024 rows: 171
-        // against 178 us, 280 against 288), nor from two rounds on (448 K-blocks in eight parts of 56
-        // against seven of 64: Mixtral shapes, 2048 tokens, 255 against 263 us).  The workspace keeps
-        // room for the finer split, so that a buffer sized for a batch also takes every smaller one.
-        static const int full = tune_int("LORA_DEC_SHRINK_FULL", 768, 1, 1 << 20);
-        const int round = 4 * shrink_wave_units(p->d.rank);
-        if (p->d.rank <= 16 && P >= 4 * tub && tub * k.ws_parts >= full) {
-            n = parts_for(full);
-            per = ((kblocks + n - 1) / n + 3) / 4 * 4;
-            const int whole = (per + round - 1) / round * round;
-            if (per < 2 * round && (kblocks + whole - 1) / whole < (kblocks + per - 1) / per) per = whole;
-        }
-        k.kb_per_part = per;
-        k.n_parts = (kblocks + per - 1) / per;
-        k.wave_per_tile = false;
+        k.kb_per_part = kblocks;
+        k.n_parts = k.ws_parts = 1;
+        k.wave_per_tile = true;
         return k;
     }
-    // long segments: work items are groups of tiles; enough K parts to fill the chip
-    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(p, P, kTileRows));
-    const int64_t groups = (tub + shrink_long_tiles() - 1) / shrink_long_tiles();
-    static const int target = tune_int("LORA_SHRINK_ITEMS", 512, 1, 1 << 20);
-    int want = (int)std::min<int64_t>((target + groups - 1) / groups, kMaxParts);
-    int by_size = (kblocks + kPartKBlocks - 1) / kPartKBlocks;
-    int n = std::max(want, by_size);
-    n = std::min(n, std::max(1, kblocks / 4));
-    n = std::min(n, kMaxParts);
-    int per = (kblocks + n - 1) / n;
-    per = (per + 3) / 4 * 4;
+    const int by_size = std::max(1, (kblocks + kb_target - 1) / kb_target);
+    auto parts_for = [&](int wgs) {
+        const int n = std::max<int>(by_size, (int)std::min<int64_t>((wgs + tub - 1) / tub, kblocks / 4));
+        return std::min(std::max(n, 1), max_parts);
+    };
     KSplit k;
+    int n = parts_for(want_wgs);
+    int per = ((kblocks + n - 1) / n + 3) / 4 * 4;
+    k.ws_parts = (kblocks + per - 1) / per;
+    // With three workgroups per CU and more the chip is full, and more parts only cost: at ranks
+    // 8 and 16 three workgroups per CU are enough, and a short part is a whole number of rounds of
+    // the workgroup's four waves (a wave takes shrink_wave_units() K-blocks per step) where that
+    // saves a part: one and a half rounds take as long as two.  Llama shapes at rank 16, 2048 rows
+    // of which 1792 share an adapter: 181 -> 164 us for the layer, 1024 rows 124 -> 113.5.  Not
+    // for tiles of a row or two, whose v is small (Mixtral shapes, 64 tokens: 46.6 against 46.9 us),
+    // nor at ranks 32 and 64, where a part is two and four times the bytes (1024 rows: 171
+    // against 178 us, 280 against 288), nor from two rounds on (448 K-blocks in eight parts of 56
+    // against seven of 64: Mixtral shapes, 2048 tokens, 255 against 263 us).  The workspace keeps
+    // room for the finer split, so that a buffer sized for a batch also takes every smaller one.
+    static const int full = tune_int("LORA_DEC_SHRINK_FULL", 768, 1, 1 << 20);
+    const int round = 4 * shrink_wave_units(p->d.rank);
+    if (p->d.rank <= 16 && P >= 4 * tub && tub * k.ws_parts >= full) {
+        n = parts_for(full);
+        per = ((kblocks + n - 1) / n + 3) / 4 * 4;
+        const int whole = (per + round - 1) / round * round;
+        if (per < 2 * round && (kblocks + whole - 1) / whole < (kblocks + per - 1) / per) per = whole;
+    }
     k.kb_per_part = per;
-    k.n_parts = k.ws_parts = (kblocks + per - 1) / per;
+    k.n_parts = (kblocks + per - 1) / per;
     k.wave_per_tile = false;
     return k;
+}
+
+KSplit ksplit_long(const lora_pool *p, int proj, int P)
+{
+    const int kblocks = kblocks_of(p->d.proj[proj].h_in, p->d.rank);
+    // work items are blocks of rows of one segment; the workspace has room for the finest split used
+    const int tiles_per_item = shrink_long_rows() / kTileRows;
+    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(p, P, kTileRows));
+    const int64_t groups = (tub + tiles_per_item - 1) / tiles_per_item;
+    static const int target = tune_int("LORA_SHRINK_ITEMS", 512, 1, 1 << 20);
+    const int want = (int)std::min<int64_t>((target + groups - 1) / groups, kMaxParts);
+    const int by_size = (kblocks + kPartKBlocks - 1) / kPartKBlocks;
+    auto whole = [&](int n) { return ((kblocks + n - 1) / n + 3) / 4 * 4; };
+    const int most = std::min(std::min(std::max(want, by_size), std::max(1, kblocks / 4)), kMaxParts);
+    KSplit k;
+    k.wave_per_tile = false;
+    k.ws_parts = (kblocks + whole(most) - 1) / whole(most);
+    // Two items fit a CU at a time, and all of them run for about as long, so a second round that is
+    // nearly empty costs a whole one: as many parts as one round of the chip takes.  Few blocks need
+    // less than a full round (more parts are more fp32 sums to write and read); many take several
+    // rounds, by how well those fill.  prefill of 16384 rows in 8 uneven requests, rank 64: 3 parts
+    // 290 us, 4 parts (544 items on 512 places) 305, 2 parts 298; 4096 rows: 5 parts 106, 13 parts 115.
+    int n = 1;
+    static const int places = tune_int("LORA_SHRINK_PLACES", 512, 1, 1 << 20);
+    static const int few = tune_int("LORA_SHRINK_FEW", 220, 1, 1 << 20);
+    if (groups < 64) {
+        n = (int)std::max<int64_t>(1, few / groups);
+    } else if (groups <= places) {
+        n = (int)(places / groups);
+    } else {
+        double best = 0;
+        for (int c = 1; c <= 4; ++c) {
+            const double rounds = std::ceil((double)groups * c / places);
+            const double filled = groups * c / (rounds * places) * (1 - 0.04 * c);
+            if (filled > best) {
+                best = filled;
+                n = c;
+            }
+        }
+    }
+    k.kb_per_part = whole(std::min(n, most));
+    k.n_parts = (kblocks + k.kb_per_part - 1) / k.kb_per_part;
+    return k;
+}
+
+KSplit ksplit_of(const lora_pool *p, int proj, int P, int tile_rows)
+{
+    return long_kernels(p, P, tile_rows) ? ksplit_long(p, proj, P) : ksplit_decode(p, proj, P);
 }
 
 // Segments are only meaningful together with the pool they were built for: the keys index that
@@ -334,11 +384,12 @@ size_t parts_bytes(const lora_pool *pool, int n_parts, int P)
 // bytes of one projection's intermediate
 size_t v_bytes(const lora_pool *pool, int proj, int P, int tile_rows)
 {
-    size_t n = parts_bytes(pool, ksplit_of(pool, proj, P, tile_rows).ws_parts, P);
-    // long-segment batches: the expand keeps its operand images behind the K parts
-    if (tile_rows == kTileRows)
-        n += align_up(expand_image_bytes(pool->d.rank, tiles_upper_bound(pool, P, kTileRows)), 256);
-    return n;
+    if (tile_rows == kDecodeTileRows) return parts_bytes(pool, ksplit_decode(pool, proj, P).ws_parts, P);
+    // long-segment batches: the expand keeps its operand images behind the K parts.  The size is that
+    // of the long-segment kernels also where the decode kernels run, which need less
+    const size_t n = parts_bytes(pool, ksplit_long(pool, proj, P).ws_parts, P) +
+                     align_up(expand_image_bytes(pool->d.rank, tiles_upper_bound(pool, P, kTileRows)), 256);
+    return long_kernels(pool, P, tile_rows) ? n : std::max(n, parts_bytes(pool, ksplit_decode(pool, proj, P).ws_parts, P));
 }
 
 // bytes of the workspace of a MoE application
@@ -393,9 +444,14 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
     sp.n_parts = ks.n_parts;
     sp.kb_per_part = ks.kb_per_part;
     sp.rank = pool->d.rank;
-    const int64_t items = tiles_upper_bound(pool, seg->P, seg->tile_rows) * ks.n_parts;
-    if (seg->tile_rows == kDecodeTileRows) {
-        static const int per_cu = tune_int("LORA_DEC_SHRINK_WGS_PER_CU", 8, 1, 64);
+    if (!long_kernels(pool, seg->P, seg->tile_rows)) {
+        sp.tile_halves = seg->tile_rows == kTileRows;
+        const int64_t items = ks.n_parts * (sp.tile_halves ? 2 * tiles_upper_bound(pool, seg->P, kTileRows)
+                                                           : tiles_upper_bound(pool, seg->P, kDecodeTileRows));
+        // halves of 32-row tiles: the second half is often empty, and a workgroup that strides over
+        // several items would meet only first or only second halves
+        static const int per_cu_env = tune_int("LORA_DEC_SHRINK_WGS_PER_CU", 8, 1, 64);
+        const int per_cu = sp.tile_halves ? 64 : per_cu_env;
         sp.proj0 = g.proj0;
         sp.n_fused = g.n;
         for (int j = 0; j < g.n; ++j) sp.v[j] = g.v[j];
@@ -407,8 +463,10 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
     }
     // 32-row tiles: work items are groups of tiles; at most two projections per launch
     static const int per_cu = tune_int("LORA_SHRINK_WGS_PER_CU", 2, 1, 64);
-    const int64_t groups = (tiles_upper_bound(pool, seg->P, seg->tile_rows) + shrink_long_tiles() - 1) /
-                           shrink_long_tiles();
+    const int64_t keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
+    const int64_t groups = std::min<int64_t>(seg->P, std::min<int64_t>(keys, seg->P) + seg->P / shrink_long_rows());
+    sp.seg_start = seg->seg_start;
+    sp.seg_key = seg->seg_key;
     sp.grid = (int)std::min<int64_t>(groups * ks.n_parts, (int64_t)cu_count() * per_cu);
     return sp;
 }
@@ -418,7 +476,7 @@ int do_shrink(const lora_pool *pool, int layer, const Group &g, const void *x, i
               const SegParams *build = nullptr)
 {
     ShrinkParams sp = shrink_params(pool, layer, g, x, ldx, src_row, seg);
-    if (seg->tile_rows == kDecodeTileRows) {
+    if (!long_kernels(pool, seg->P, seg->tile_rows)) {
         if (build) {
             // every workgroup sorts the batch before its first item: fewer, longer-lived workgroups
             static const int per_cu = tune_int("LORA_INLINE_BUILD_WGS_PER_CU", 4, 1, 64);
@@ -449,7 +507,7 @@ int do_expand(const lora_pool *pool, int layer, const Group &g, const lora_segme
 {
     ExpandParams ep;
     expand_params(pool, layer, g, seg, out_dtype, ep);
-    if (seg->tile_rows == kDecodeTileRows)
+    if (!long_kernels(pool, seg->P, seg->tile_rows))
         LORA_HIP(launch_expand_decode(ep, st));
     else
         LORA_HIP(launch_expand(ep, st));
@@ -471,8 +529,10 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     ep.counts = seg->counts;
     ep.out_f32 = out_dtype == LORA_DTYPE_F32;
     ep.rank = pool->d.rank;
-    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(pool, seg->P, seg->tile_rows));
-    if (seg->tile_rows == kDecodeTileRows) {
+    const bool decode = !long_kernels(pool, seg->P, seg->tile_rows);
+    const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(pool, seg->P, decode ? kDecodeTileRows : kTileRows));
+    if (decode) {
+        ep.tile_halves = seg->tile_rows == kTileRows;
         // every wave works alone on wave items = (tile, projection, slice of 128-column chunks).
         // Chunks per item: an item should move about item_bytes (its prologue - row indices, v -
         // costs a few load latencies), but a small batch must still yield a few thousand items;
@@ -804,20 +864,19 @@ int lora_pool_load_unit(lora_pool *pool, int adapter, int layer, int expert, int
     if (!aligned(A, 2) || !aligned(B, 2)) return LORA_ERR_MISALIGNED;
     const size_t base = pool->unit_base(layer, adapter, expert);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    PackParams pp;
-    pp.src = static_cast<const uint16_t *>(A);
-    pp.src_stride = 0;
-    pp.dst = reinterpret_cast<uint16_t *>(pool->slab + base + pool->A_off[proj]);
-    pp.dst_stride = 0;
-    pp.n_units = 1;
-    pp.h = pool->d.proj[proj].h_in;
-    pp.rank = pool->d.rank;
-    pp.src_rank = pool->arank[adapter];
-    LORA_HIP(launch_pack_A(pp, st));
-    pp.src = static_cast<const uint16_t *>(B);
-    pp.dst = reinterpret_cast<uint16_t *>(pool->slab + base + pool->B_off[proj]);
-    pp.h = pool->d.proj[proj].h_out;
-    LORA_HIP(launch_pack_B(pp, st));
+    PackLayerParams ps;
+    memset(&ps, 0, sizeof ps);
+    ps.n_jobs = 2;
+    for (int b = 0; b < 2; ++b) {
+        PackParams &pp = ps.job[b];
+        pp.src = static_cast<const uint16_t *>(b ? B : A);
+        pp.dst = reinterpret_cast<uint16_t *>(pool->slab + base + (b ? pool->B_off[proj] : pool->A_off[proj]));
+        pp.n_units = 1;
+        pp.h = b ? pool->d.proj[proj].h_out : pool->d.proj[proj].h_in;
+        pp.rank = pool->d.rank;
+        pp.src_rank = pool->arank[adapter];
+    }
+    LORA_HIP(launch_pack_layer(ps, st));      // A and B in one launch
     return LORA_OK;
 }
 
@@ -1261,7 +1320,7 @@ int lora_build_apply_launches(const lora_pool *pool, int proj0, int n_proj, int 
     g.proj0 = proj0;
     g.n = n_proj;
     if (P == 0) return 1;
-    const int apply = seg.tile_rows == kDecodeTileRows ? (fused_plan(pool, g, &seg, out_dtype, nullptr, nullptr) ? 1 : 2)
+    const int apply = !long_kernels(pool, P, seg.tile_rows) ? (fused_plan(pool, g, &seg, out_dtype, nullptr, nullptr) ? 1 : 2)
                                                        : (n_proj + 1) / 2 + 2;
     return apply + (inline_build_ok(pool, g, &seg, out_dtype) ? 0 : lora_segments_launches(pool, P));
 }
@@ -1280,7 +1339,7 @@ int lora_group_launches(const lora_pool *pool, int proj0, int n_proj, int out_dt
     memset(&g, 0, sizeof g);
     g.proj0 = proj0;
     g.n = n_proj;
-    if (seg->tile_rows == kDecodeTileRows) return fused_plan(pool, g, seg, out_dtype, nullptr, nullptr) ? 1 : 2;
+    if (!long_kernels(pool, seg->P, seg->tile_rows)) return fused_plan(pool, g, seg, out_dtype, nullptr, nullptr) ? 1 : 2;
     return (n_proj + 1) / 2 + 2;       // long segments: shrink launches of two projections, images, expand
 }
 
@@ -1491,7 +1550,7 @@ int lora_moe_down_combine(const lora_pool *pool, int layer, const void *hmid, in
     // 2. the per-pair updates into rows of their own.  Decode batches write them without reading
     // anything; the long-segment expand only knows how to add, so its rows are cleared first.
     Group g = moe_group(pool, LORA_MOE_DOWN, seg, ws, pair, nullptr, h_out);
-    if (seg->tile_rows == kDecodeTileRows)
+    if (!long_kernels(pool, seg->P, seg->tile_rows))
         g.overwrite = 1;
     else
         LORA_HIP(launch_fill_zero(pair, align_up((size_t)seg->P * h_out * sizeof(uint16_t), 16), st));

@@ -21,7 +21,7 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wpb = blockDim.x >> 6;
     const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + wave), nw = gridDim.x * wpb;
-    const int n_tiles = counts[2];
+    const int n_tiles = counts[2] << p.tile_halves;
     const int per_tile = p.slice0[p.n_fused];                     // wave items of one tile
     // Item order: tile_group consecutive items take the same (projection, slice) of
     // tile_group consecutive tiles, so the waves of a workgroup that work on tiles of one
@@ -41,7 +41,13 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
         const int cps = p.cps[pj];                                // chunks per slice
         const int c0 = slice * cps, c1 = min(c0 + cps, p.n_chunks[pj]);
         if (c0 >= c1) continue;
-        const lora_tile t = tiles[tile_ix];
+        lora_tile t = tiles[tile_ix >> p.tile_halves];
+        if (p.tile_halves) {                                      // rows 0..15 or 16..31 of a 32-row tile
+            const int off = (tile_ix & 1) * kDecodeTileRows;
+            t.row0 += off;
+            t.n_rows = min(t.n_rows - off, kDecodeTileRows);
+            if (t.n_rows <= 0) continue;
+        }
         const Unit unit = units[(int64_t)t.key * p.n_proj + p.proj0 + pj];
         expand_tile_chunks<R, F32, OVW, YNT>(p, t, unit, pj, c0, c1, lane);
     }

@@ -48,6 +48,8 @@ constexpr int64_t kFusedMaxWork = 21ll << 17;      // twice that at rank 8, whos
 // The output rows of one call are streamed from kStreamYMiB on: just-written ones would lose what
 // those in HBM gain (Mixtral shapes, 2048 tokens, 235 MiB: 246.8 / 259.1 against 258.9 / 247.4).
 constexpr int kLongMinRowsTimesRank = 1 << 17;   // long-segment kernels from this many rows x rank on
+constexpr int kLongMinRowsRank16 = 12288;        // rank 16: the long-segment kernels proper from here on, and
+constexpr int kLongRowsPerKeyRank16 = 128;       // from this many rows per key
 constexpr int kStreamXMiB = 8;
 constexpr int kStreamXHighRankMiB = 16;   // ranks 32 and 64
 constexpr int kStreamYMiB = 256;
@@ -78,7 +80,9 @@ struct PackParams {
 // all A and B repacks of one (adapter, layer) in one launch: job 2j = A, 2j+1 = B of projection j
 struct PackLayerParams {
     PackParams job[2 * LORA_MAX_PROJ];
+    int wg0[2 * LORA_MAX_PROJ + 1];      // first workgroup of a job; filled by launch_pack_layer
     int n_jobs;
+    int aligned;             // every source is 16-byte aligned; filled by launch_pack_layer
 };
 
 struct SegParams {
@@ -122,6 +126,8 @@ struct ShrinkParams {
     const int32_t *src_row;  // may be null
     const int32_t *perm;
     const lora_tile *tiles;
+    const int32_t *seg_start;    // long-segment kernel
+    const int32_t *seg_key;
     const int32_t *counts;
     float *v[kMaxFused];     // per fused projection: [n_parts][P][rank]
     int P;
@@ -130,6 +136,7 @@ struct ShrinkParams {
     int kb_per_part;
     int rank;
     int grid;
+    int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
     int wave_per_tile;       // decode kernel: every wave takes a whole tile (no K split across waves)
     int build;               // decode kernel: the segments are built inside the launch, from `seg`
     int x_stream;            // decode kernel, K-split form: x rows loaded with the streaming hint (ranks 8, 16: as whole lines)
@@ -157,6 +164,7 @@ struct ExpandParams {
     void *img[kMaxFused];    // long-segment kernel: operand images of the 16-row sub-tiles
     int image_grid;          // long-segment kernel: workgroups of the image launch
     int waves;               // waves per workgroup
+    int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
     int tile_group;          // decode kernel: consecutive wave items walk over this many tiles
     int out_f32;
     int overwrite;           // decode kernel, bf16 output: write the update, do not read the rows
@@ -186,9 +194,7 @@ struct FusedParams {
     ExpandParams e;          // slice0: workgroup items of a tile; v, cps unused
 };
 
-hipError_t launch_pack_A(const PackParams &p, hipStream_t s);
-hipError_t launch_pack_B(const PackParams &p, hipStream_t s);
-hipError_t launch_pack_layer(const PackLayerParams &p, hipStream_t s);
+hipError_t launch_pack_layer(PackLayerParams &p, hipStream_t s);
 hipError_t launch_unpack_A(const PackParams &p, hipStream_t s);   // src = packed, dst = row-major
 hipError_t launch_unpack_B(const PackParams &p, hipStream_t s);
 hipError_t launch_set_adapter(Unit *table, int n_layers, int n_adapters, int per_adapter, int adapter,
@@ -201,7 +207,7 @@ int inline_build_max_keys();
 bool segments_large_handles(const SegParams &p);    // does the multi-workgroup builder take this batch?
 int segments_large_launches(const SegParams &p);    // kernels it enqueues for it
 hipError_t launch_shrink(const ShrinkParams &p, hipStream_t s);
-int shrink_long_tiles();                                 // tiles per work item of launch_shrink
+int shrink_long_rows();                                  // rows of one segment per work item of launch_shrink
 hipError_t launch_expand(const ExpandParams &p, hipStream_t s);
 size_t expand_image_bytes(int rank, int64_t n_tiles);   // operand images of n_tiles 32-row tiles
 int expand_long_group();                                 // tiles per wave item of launch_expand

@@ -3,38 +3,82 @@
 //
 // With long segments the traffic is the read of x; A is small, but a wave that multiplies it
 // with only 32 rows re-reads it from the L2 four times as fast as x arrives from HBM.  So the
-// four waves of a workgroup take four consecutive tiles (up to 128 rows) and share A through
-// LDS: work item = (group of four tiles, K part).  Per stage of four K blocks the workgroup
-// copies the packed A blocks of the first tile's (adapter, expert) into one of two LDS
+// four waves of a workgroup take up to 128 consecutive rows of one segment and share A through
+// LDS: work item = (block of 128 rows of a segment, K part).  Per stage of four K blocks the
+// workgroup copies the packed A blocks of the segment's (adapter, expert) into one of two LDS
 // buffers while the previous stage is being multiplied; every wave gathers the x rows of its
-// own tile (the next stage's rows are in flight during the current stage's MFMAs) and reads
+// own 32 rows (the next stage's rows are in flight during the current stage's MFMAs) and reads
 // its MFMA operands from LDS with 16-byte reads that are contiguous per wave.  The x rows are
 // fetched as whole cache lines, four rows x 256 bytes per instruction, and turned into the MFMA
 // operand layout (16 rows x 64 bytes per operand) through 4 KiB of LDS per wave: fetching them
 // in the operand layout directly costs the address path twice the line look-ups, which a
-// load-only probe of the two streams puts at 32 against 27 us for the prefill workload.  A group whose
-// tiles do not all belong to one (adapter, expert) (a segment boundary inside the group) takes
-// a plain path in which every wave reads its own A from global memory.  Every wave owns its rows for the
-// whole K part, so there is no cross-wave reduction; lora_expand adds the K parts in a fixed
-// order, so results are bit-identical run to run.
+// load-only probe of the two streams puts at 32 against 27 us for the prefill workload.  A block
+// never spans two segments, so every one of them runs the shared-A loop: blocks of four consecutive
+// tiles that straddled a segment boundary took a path without LDS or prefetch, one K block at a time,
+// and the launch waited for them.  16384 rows in 8 uneven requests, rank 64, whole call: 308 -> 290 us
+// (with as many K parts as one round of the chip takes); 64 adapters, 4096 rows, rank 64: 157 -> 143.
+// Which segment a block belongs to is looked up by the workgroup: a prefix sum of the segments' block
+// counts, 256 segments at a time.  Every wave owns
+// its rows for the whole K part, so there is no cross-wave reduction; lora_expand adds the K parts in
+// a fixed order, so results are bit-identical run to run.
 //
 // The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and the rows on the N side, so
 // a lane ends up with four consecutive rank entries of one row.  With two fused projections
 // (gate and up, or two projections of a group that read the same input) x is loaded once.
 // Ranks 16, 32 and 64; rank-8 pools always use the 16-row-tile kernels.
 #include "lora_device.h"
-#include "lora_internal.h"
+#include "segments_common.h"
 
 namespace lora {
 
 namespace {
 
 constexpr int kLongTiles = 4;        // tiles (waves) per work item
+constexpr int kLongRows = kLongTiles * kTileRows;
 constexpr int kStageKB = 4;          // K blocks per LDS stage
+
+// Segment of the grp-th block of kLongRows rows and the block's number inside it; false when there
+// are fewer blocks.  The whole workgroup calls it; `scratch` (five ints of LDS) is free again after the
+// caller's next barrier.
+__device__ inline bool find_block(const int32_t *__restrict__ seg_start, int S, int grp, int *scratch, int *seg, int *block)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int before = 0;                                       // blocks of the segments looked at so far
+    for (int s0 = 0; s0 < S; s0 += 256) {
+        const int s = s0 + tid;
+        const int n = s < S ? (seg_start[s + 1] - seg_start[s] + kLongRows - 1) / kLongRows : 0;
+        const int incl = (int)wave_incl_sum((unsigned)n);
+        if (lane == 63) scratch[w] = incl;
+        if (tid == 0) scratch[4] = -1;
+        __syncthreads();
+        int first = before, total = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            first += k < w ? scratch[k] : 0;
+            total += scratch[k];
+        }
+        first += incl - n;
+        if (grp >= first && grp < first + n) scratch[4] = tid;          // one thread at most
+        __syncthreads();
+        const int hit = scratch[4];
+        if (hit >= 0) {
+            *seg = s0 + hit;
+            // the finder's first block, from the owner's lane
+            if (tid == hit) scratch[0] = first;
+            __syncthreads();
+            *block = grp - scratch[0];
+            return true;
+        }
+        before += total;
+        __syncthreads();
+    }
+    return false;
+}
 
 template <int R, int NPROJ>
 __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
-                                                             const lora_tile *__restrict__ tiles,
+                                                             const int32_t *__restrict__ seg_start,
+                                                             const int32_t *__restrict__ seg_key,
                                                              const Unit *__restrict__ units,
                                                              const int32_t *__restrict__ counts)
 {
@@ -53,49 +97,33 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, i16 = lane & 15;
-    const int n_tiles = counts[2];
-    const int n_groups = (n_tiles + kLongTiles - 1) / kLongTiles;
-    const int n_items = n_groups * p.n_parts;
+    const int S = counts[0];
     const int kblocks = (p.h_in + kKBlock - 1) / kKBlock;
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
 
-    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+    for (int item = blockIdx.x;; item += gridDim.x) {
         const int grp = item / p.n_parts;
         const int part = item - grp * p.n_parts;
-        const int key0 = tiles[grp * kLongTiles].key;
-        const int tix = __builtin_amdgcn_readfirstlane(grp * kLongTiles + wave);
-        const bool live = tix < n_tiles;                      // wave-uniform
-        const lora_tile t = tiles[min(tix, n_tiles - 1)];
-        // does every tile of the group belong to the first tile's (adapter, expert)?  Uniform
-        // over the workgroup: every wave looks at all four records.
-        bool same_key = true;
-#pragma unroll
-        for (int k = 1; k < kLongTiles; ++k)
-            same_key = same_key && tiles[min(grp * kLongTiles + k, n_tiles - 1)].key == key0;
+        int seg, block;
+        if (!find_block(seg_start, S, grp, reinterpret_cast<int *>(dyn_lds), &seg, &block)) break;   // uniform
+        seg = __builtin_amdgcn_readfirstlane(seg);
+        block = __builtin_amdgcn_readfirstlane(block);
+        const int key = seg_key[seg];
+        const int seg_row0 = seg_start[seg], seg_end = seg_start[seg + 1];
+        // this wave's rows; a wave beyond the segment's end re-reads its first row and stores nothing
+        const int w_row0 = seg_row0 + block * kLongRows + __builtin_amdgcn_readfirstlane(wave) * kTileRows;
+        const bool live = w_row0 < seg_end;                   // wave-uniform
+        const int row0 = live ? w_row0 : seg_row0;
+        const int n_rows = live ? min(kTileRows, seg_end - w_row0) : 1;
 
-        const uint16_t *Ag[NPROJ], *Aw[NPROJ];                // the group's A, this wave's A
+        const uint16_t *Ag[NPROJ];
 #pragma unroll
-        for (int pj = 0; pj < NPROJ; ++pj) {
-            Ag[pj] = units[(int64_t)key0 * p.n_proj + p.proj0 + pj].A;
-            Aw[pj] = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].A;
-        }
+        for (int pj = 0; pj < NPROJ; ++pj) Ag[pj] = units[(int64_t)key * p.n_proj + p.proj0 + pj].A;
 
-        // gathered input rows: lane (i16, g) reads x[row i16 of the sub-tile][8*g ...]; rows
-        // beyond the tile re-read its first row and are replaced by zeros
-        const uint16_t *xp[SUB];
-        bool rv[SUB];
-#pragma unroll
-        for (int sub = 0; sub < SUB; ++sub) {
-            const int r = sub * 16 + i16;
-            rv[sub] = live && r < t.n_rows;
-            int s = p.perm[t.row0 + min(r, t.n_rows - 1)];
-            if (p.src_row) s = p.src_row[s];
-            xp[sub] = p.x + (int64_t)s * p.ldx + g * 8;
-        }
-
-        // the same rows as they are fetched on the shared-A path: one instruction reads four
-        // rows (lane group g) x 256 contiguous bytes (16 lanes x 16 bytes), i.e. whole cache
-        // lines, which the address path serves faster than 16 rows x 64 bytes
+        // gathered input rows as they are fetched: one instruction reads four rows (lane group g) x
+        // 256 contiguous bytes (16 lanes x 16 bytes), i.e. whole cache lines, which the address path
+        // serves faster than 16 rows x 64 bytes; rows beyond the wave's re-read a valid one and are
+        // replaced by zeros
         const uint16_t *xq[SUB][4];
         bool qv[SUB][4];
 #pragma unroll
@@ -103,8 +131,8 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = sub * 16 + j * 4 + g;
-                qv[sub][j] = live && r < t.n_rows;
-                int s = p.perm[t.row0 + min(r, t.n_rows - 1)];
+                qv[sub][j] = live && r < n_rows;
+                int s = p.perm[row0 + min(r, n_rows - 1)];
                 if (p.src_row) s = p.src_row[s];
                 xq[sub][j] = p.x + (int64_t)s * p.ldx;            // start of the row
             }
@@ -187,47 +215,24 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
                     }
         };
 
-        if (same_key) {
-            u32x4 areg[LOADS];
-            u32x4 xr[SUB][4];                  // the next stage's x as fetched
-            u32x4 xc[SUB][kStageKB];           // the current stage's x as MFMA operands
-            load_a(kb_begin, areg);
-            load_rows(kb_begin, xr);
-            store_a(areg, lds[0]);
+        u32x4 areg[LOADS];
+        u32x4 xr[SUB][4];                  // the next stage's x as fetched
+        u32x4 xc[SUB][kStageKB];           // the current stage's x as MFMA operands
+        load_a(kb_begin, areg);
+        load_rows(kb_begin, xr);
+        __syncthreads();                   // the look-up's scratch lies in the first stage
+        store_a(areg, lds[0]);
+        to_operands(xr, xc);
+        __syncthreads();
+        for (int s = 0; s < n_stages; ++s) {
+            const int kb0 = kb_begin + s * kStageKB;
+            load_a(kb0 + kStageKB, areg);                 // beyond the part: zeros, never multiplied
+            load_rows(kb0 + kStageKB, xr);
+            __builtin_amdgcn_sched_barrier(0);            // all of the next stage's loads first
+            compute(lds[s & 1], xc);
+            store_a(areg, lds[(s + 1) & 1]);
             to_operands(xr, xc);
             __syncthreads();
-            for (int s = 0; s < n_stages; ++s) {
-                const int kb0 = kb_begin + s * kStageKB;
-                load_a(kb0 + kStageKB, areg);                 // beyond the part: zeros, never multiplied
-                load_rows(kb0 + kStageKB, xr);
-                __builtin_amdgcn_sched_barrier(0);            // all of the next stage's loads first
-                compute(lds[s & 1], xc);
-                store_a(areg, lds[(s + 1) & 1]);
-                to_operands(xr, xc);
-                __syncthreads();
-            }
-        } else {
-            // a segment boundary inside the group: every wave reads the A of its own tile from
-            // global memory, one K block at a time (rare, so kept simple)
-            for (int kb = kb_begin; kb < kb_end; ++kb) {
-                const bool c_ok = kb * kKBlock + g * 8 < p.h_in;
-                u32x4 xv[SUB];
-#pragma unroll
-                for (int sub = 0; sub < SUB; ++sub) {
-                    const u32x4 v = ld16<false>(xp[sub] + (c_ok ? kb * kKBlock : 0));
-                    xv[sub] = (c_ok && rv[sub]) ? v : zero4;
-                }
-#pragma unroll
-                for (int pj = 0; pj < NPROJ; ++pj)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        const u32x4 w = ld16<false>(Aw[pj] + (((int64_t)kb * NB + nb) * 64 + lane) * 8);
-#pragma unroll
-                        for (int sub = 0; sub < SUB; ++sub)
-                            acc[pj][sub][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                as_bf16x8(w), as_bf16x8(xv[sub]), acc[pj][sub][nb], 0, 0, 0);
-                    }
-            }
         }
 
         // this wave's rows of this part of v: lane (row i16, group g) holds rank entries
@@ -236,10 +241,10 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
         for (int pj = 0; pj < NPROJ; ++pj)
 #pragma unroll
             for (int sub = 0; sub < SUB; ++sub)
-                if (rv[sub]) {
+                if (live && sub * 16 + i16 < n_rows) {
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        st16f(p.v[pj] + ((int64_t)part * p.P + t.row0 + sub * 16 + i16) * R + nb * 16 + g * 4,
+                        st16f(p.v[pj] + ((int64_t)part * p.P + row0 + sub * 16 + i16) * R + nb * 16 + g * 4,
                               acc[pj][sub][nb]);
                 }
     }
@@ -253,8 +258,8 @@ hipError_t launch_rn(const ShrinkParams &p, hipStream_t s)
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_long_kernel<R, NPROJ>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((shrink_long_kernel<R, NPROJ>), dim3(p.grid), dim3(256), kLds, s, p, p.tiles, p.units,
-                       p.counts);
+    hipLaunchKernelGGL((shrink_long_kernel<R, NPROJ>), dim3(p.grid), dim3(256), kLds, s, p, p.seg_start,
+                       p.seg_key, p.units, p.counts);
     return hipGetLastError();
 }
 
@@ -266,7 +271,7 @@ hipError_t launch_r(const ShrinkParams &p, hipStream_t s)
 
 }  // namespace
 
-int shrink_long_tiles() { return kLongTiles; }
+int shrink_long_rows() { return kLongRows; }
 
 hipError_t launch_shrink(const ShrinkParams &p, hipStream_t s)
 {

@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
         build_segments_inline<4>(p.seg, scratch.counts, built, blockIdx.x == 0);   // `built` is complete behind its last barrier
         n_tiles = built.n_tiles;
     } else {
-        n_tiles = counts[2];
+        n_tiles = counts[2] << p.tile_halves;
     }
     const int n_items = n_tiles * p.n_parts;
     const int kblocks = (p.h_in + KU - 1) / KU;
@@ -89,7 +89,13 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
             t.row0 = __builtin_amdgcn_readfirstlane(t.row0);
             t.n_rows = __builtin_amdgcn_readfirstlane(t.n_rows);
         } else {
-            t = tiles[tile_ix];
+            t = tiles[tile_ix >> p.tile_halves];
+            if (p.tile_halves) {                      // rows 0..15 or 16..31 of a 32-row tile
+                const int off = (tile_ix & 1) * kDecodeTileRows;
+                t.row0 += off;
+                t.n_rows = min(t.n_rows - off, kDecodeTileRows);
+                if (t.n_rows <= 0) continue;          // uniform over everyone who shares the item
+            }
         }
 #pragma unroll
         for (int pj = 0; pj < NPROJ; ++pj)

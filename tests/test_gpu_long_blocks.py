@@ -1,0 +1,64 @@
+"""Work items of the long-segment shrink (blocks of 128 rows of one segment, looked up in the segment
+list) and the decode kernels on the halves of 32-row tiles: segment lengths around the block, tile and
+half sizes, more segments than one look-up pass covers, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_07173_amd as L
+import workloads as W
+from gpu_common import check_accumulate, check_delta, oracle_projection
+from harness import DeviceBatch, DevicePool, LayerRunner, bits_from_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def run_lengths(lengths, rank, widths, h_in, seed, y_mode, shuffle, n=None):
+    n = n or len(lengths)
+    aid = np.repeat(np.arange(len(lengths), dtype=np.int32), lengths)
+    aid = np.concatenate([aid, np.full(5, -1, np.int32)])
+    if shuffle:
+        aid = np.random.default_rng(seed).permutation(aid)
+    projs = tuple(W.Proj(f"p{i}", h_in, o, "x") for i, o in enumerate(widths))
+    w = W.Workload("t", "dense", n, 1, 1, rank, projs, aid.size, "uniform")
+    b = W.make_batch(w, seed, y_mode=y_mode, hetero_scale=True)
+    b.adapter_id[:] = aid
+    ws = W.make_weights(w, seed, bank_elems=1 << 22)
+    dp, db = DevicePool(ws, b.scale), DeviceBatch(b)
+    run = LayerRunner(dp, db)
+    run.v.fill_(float("nan"))                  # nothing may depend on what the workspace holds
+    run.step(0)
+    torch.cuda.synchronize()
+    assert db.seg.c.tile_rows == 32
+    rows = np.sort(np.random.default_rng(seed).choice(aid.size, min(aid.size, 700), replace=False))
+    none = b.adapter_id < 0
+    for j, p in enumerate(projs):
+        res = oracle_projection(b, ws, 0, j, rows=rows)
+        full = bits_from_dev(db.y[p.name])
+        got = np.ascontiguousarray(full[rows])
+        if y_mode == "zero":
+            check_delta(W.bf16_bits_to_f32(got).astype(np.float64), res.delta, f"blocks r{rank} {p.name}")
+        else:
+            check_accumulate(got, res, f"blocks r{rank} {p.name}")
+        assert np.array_equal(full[none], b.y_in[p.name][none])
+    return dp, db
+
+
+EDGES = [1, 127, 128, 129, 0, 31, 32, 33, 255, 256, 257, 16, 17, 384]
+
+
+@pytest.mark.parametrize("rank", [16, 32, 64])
+@pytest.mark.parametrize("lengths,shuffle", [(EDGES, True), ([1], False), ([2 + i % 3 for i in range(600)], True),
+                                             ([0] * 255 + [130, 3, 200], False)])
+def test_blocks_of_segments(rank, lengths, shuffle, monkeypatch):
+    monkeypatch.setenv("LORA_TILE_ROWS", "32")
+    run_lengths(lengths, rank, (392, 136, 264), 1032, 3, "normal", shuffle)
+
+
+@pytest.mark.parametrize("y_mode", ["zero", "normal"])
+@pytest.mark.parametrize("lengths", [EDGES * 5, [8187], [104 + 3 * i for i in range(48)]])
+def test_halves_of_tiles_at_rank_16(lengths, y_mode):
+    """8192 to 12287 rows at rank 16: 32-row tiles on the decode kernels, which take them in halves."""
+    dp, db = run_lengths(lengths, 16, (392, 264), 520, 4, y_mode, True)
+    assert 8192 <= db.P < 12288
+    assert L.lora_group_launches(dp.pool, 0, 2, db.P, db.seg) == 2
