@@ -593,6 +593,15 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         // is streamed at every length (cached: 255 -> 264 us for 2048 tokens).
         ep.share_b = long_segments;
         const int64_t wave_items = (tub + ep.tile_group - 1) / ep.tile_group * ep.tile_group * ep.slice0[g.n];
+        // Chunks in flight per wave: two, but one where the launch is a few rounds of the chip's waves
+        // long and its tiles are tall (more waves fit then, which shortens the rounds), or where an item is
+        // one chunk anyway.  Layer call in us, two / one: llama shapes, 1024 rows 116.3 / 111.5, at rank 64
+        // 284 / 261, 333 ragged fp32 rows at rank 32 70.6 / 66.3, llama shapes with 8 rows (one chunk) 31.6 /
+        // 31.0; but 256 rows (short tiles) 62.6 / 63.7, and Mixtral shapes with 2048 tokens (57 k items)
+        // 244.9 / 247.1, with 512 at rank 32 (36 k) 178.2 / 180.5.
+        static const int shallow = tune_int("LORA_DEC_SHALLOW_ITEMS", 24576, 0, 1 << 30);
+        static const int shallow_all = tune_int("LORA_DEC_SHALLOW_ALL", 0, 0, 1);
+        ep.deep = cpi > 1 && !((long_segments || shallow_all) && wave_items <= shallow);
         // The hardware hands workgroups out as others finish, which evens out tiles of different heights
         // better than a workgroup's walk over several items, and costs a launch of its own each: worth it
         // where an item is long.  16 / 32 / 64 workgroups per CU: rank 64, 1024 tokens over 512 adapters

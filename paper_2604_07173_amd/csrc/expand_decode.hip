@@ -12,7 +12,7 @@ namespace {
 // tiles, units and counts are passed again as restrict-qualified kernel arguments: with a
 // wave-uniform index the compiler then reads them through the scalar cache, which shortens
 // the dependent chain tile -> unit -> first data load.
-template <int R, bool F32, bool OVW, bool YNT>
+template <int R, bool F32, bool OVW, bool YNT, int D>
 __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
                                                           const lora_tile *__restrict__ tiles,
                                                           const Unit *__restrict__ units,
@@ -49,20 +49,30 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
             if (t.n_rows <= 0) continue;
         }
         const Unit unit = units[(int64_t)t.key * p.n_proj + p.proj0 + pj];
-        expand_tile_chunks<R, F32, OVW, YNT>(p, t, unit, pj, c0, c1, lane);
+        expand_tile_chunks<R, F32, OVW, YNT, D>(p, t, unit, pj, c0, c1, lane);
     }
+}
+
+template <int R, bool F32, bool OVW, bool YNT, int D>
+void launch_d(const ExpandParams &p, hipStream_t s)
+{
+    hipLaunchKernelGGL((expand16_kernel<R, F32, OVW, YNT, D>), dim3(p.grid), dim3(p.waves * 64), 0, s, p, p.tiles,
+                       p.units, p.counts);
+}
+
+template <int R, bool F32, bool OVW, bool YNT>
+void launch_o(const ExpandParams &p, hipStream_t s)
+{
+    if (p.deep) launch_d<R, F32, OVW, YNT, 2>(p, s);
+    else launch_d<R, F32, OVW, YNT, 1>(p, s);
 }
 
 template <int R, bool YNT>
 hipError_t launch_ry(const ExpandParams &p, hipStream_t s)
 {
-    const dim3 block(p.waves * 64);
-    if (p.out_f32)
-        hipLaunchKernelGGL((expand16_kernel<R, true, false, YNT>), dim3(p.grid), block, 0, s, p, p.tiles, p.units, p.counts);
-    else if (p.overwrite)
-        hipLaunchKernelGGL((expand16_kernel<R, false, true, YNT>), dim3(p.grid), block, 0, s, p, p.tiles, p.units, p.counts);
-    else
-        hipLaunchKernelGGL((expand16_kernel<R, false, false, YNT>), dim3(p.grid), block, 0, s, p, p.tiles, p.units, p.counts);
+    if (p.out_f32) launch_o<R, true, false, YNT>(p, s);
+    else if (p.overwrite) launch_o<R, false, true, YNT>(p, s);
+    else launch_o<R, false, false, YNT>(p, s);
     return hipGetLastError();
 }
 

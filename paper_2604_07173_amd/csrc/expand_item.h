@@ -5,9 +5,9 @@
 // Prologue: the wave adds the K parts of the tile's v in a fixed order, applies the adapter's
 // scale and splits the result into bf16 hi + lo planes held in MFMA operand registers (hi = v
 // truncated to bf16, lo = the rounded remainder, so the product sees about 16 mantissa bits of
-// v).  Main loop over the chunks, software-pipelined two deep (the first two chunks' loads are
-// issued before v is fetched): while chunk c is multiplied and written back, the packed B tile
-// and the base-output rows of chunk c+1 are already in flight (B with nontemporal loads: it is
+// v).  Main loop over the chunks, one or two of them in flight (the first ones' loads are issued before
+// v is fetched): the packed B tile and the base-output rows of a chunk are fetched while others, of
+// this wave or of the CU's other waves, are multiplied and written back (B with nontemporal loads: it is
 // read once; y with ordinary accesses: read-modify-write runs faster through the L2).  All loads
 // in the loop are unconditional and the loop is specialised on the number of row quads, so the
 // code is straight-line and the hardware counters let the next chunk's loads stay outstanding
@@ -32,7 +32,9 @@ namespace lora {
 // are not in a cache when the call starts, or are too large to be).
 // BNT: B is loaded with the streaming hint (it is read once), else left in the L2 for the other tiles
 // of the segment.
-template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true>
+// D: chunks in flight per wave, one or two.  Two take the registers of a fifth wave per SIMD at rank 16
+// (the third at rank 64); the host picks (three or four for the small rank-8 chunks measured no faster).
+template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1>
 struct ExpandWave {
     using Tile = ExpandTile<R>;
     static constexpr int KS = Tile::KS;
@@ -97,9 +99,6 @@ struct ExpandWave {
         }
     }
 
-    // chunks in flight (three or four for the small rank-8 chunks measured no faster)
-    static constexpr int D = 2;
-
     struct Stage {
         typename Tile::B b;
         YBuf y;
@@ -131,13 +130,13 @@ struct ExpandWave {
     }
 };
 
-template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true>
+template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1>
 __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, const Unit &unit, int pj,
                                    int c0, int c1, int lane)
 {
     using Tile = ExpandTile<R>;
     constexpr int KS = Tile::KS, KV = Tile::KV, ESZ = F32 ? 4 : 2;
-    using Wave = ExpandWave<R, F32, NI, OVW, YNT, BNT>;
+    using Wave = ExpandWave<R, F32, NI, OVW, YNT, BNT, D>;
     Wave w;
     w.lane = lane;
     w.g = lane >> 4;
@@ -191,7 +190,7 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
                     for (int q = 0; q < 4; ++q) s[ks][4 * h + q] += in ? buf[u][ks][h][q] : 0.f;
         }
     };
-    typename Wave::Stage st[Wave::D];
+    typename Wave::Stage st[D];
     if (p.n_parts == 1) {                                 // a single part: one load, no batch
         f32x4 one[KS][KV / 4];
 #pragma unroll
@@ -227,20 +226,20 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
 
 // one wave, one tile, chunks [c0, c1) of projection pj; the specialisation on the number of row
 // quads is picked here (wave-uniform)
-template <int R, bool F32, bool OVW, bool YNT = false>
+template <int R, bool F32, bool OVW, bool YNT, int D>
 __device__ inline void expand_tile_chunks(const ExpandParams &p, const lora_tile &t, const Unit &unit,
                                           int pj, int c0, int c1, int lane)
 {
     switch ((t.n_rows + 3) >> 2) {
-    case 1: expand_item<R, F32, 1, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
-    case 2: expand_item<R, F32, 2, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
-    case 3: expand_item<R, F32, 3, OVW, YNT>(p, t, unit, pj, c0, c1, lane); break;
+    case 1: expand_item<R, F32, 1, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane); break;
+    case 2: expand_item<R, F32, 2, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane); break;
+    case 3: expand_item<R, F32, 3, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane); break;
     default:
         // a full tile is most likely one of several of its segment: its B is worth keeping in the L2
         if (p.share_b && t.n_rows == kDecodeTileRows)
-            expand_item<R, F32, 4, OVW, YNT, false>(p, t, unit, pj, c0, c1, lane);
+            expand_item<R, F32, 4, OVW, YNT, false, D>(p, t, unit, pj, c0, c1, lane);
         else
-            expand_item<R, F32, 4, OVW, YNT>(p, t, unit, pj, c0, c1, lane);
+            expand_item<R, F32, 4, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane);
         break;
     }
 }

@@ -168,6 +168,7 @@ struct ExpandParams {
     int tile_group;          // decode kernel: consecutive wave items walk over this many tiles
     int out_f32;
     int overwrite;           // decode kernel, bf16 output: write the update, do not read the rows
+    int deep;                // decode kernel: two chunks in flight per wave, else one
     int share_b;             // decode kernel: B of full tiles loaded without the streaming hint
     int y_stream;            // decode kernel: output rows read and written with the streaming hint
     int rank;
