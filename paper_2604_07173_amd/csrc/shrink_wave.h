@@ -131,7 +131,7 @@ struct ShrinkWave {
     }
 
     // K units kb_begin, kb_begin + stride, ... below kb_end in steps of KB units (stride = KB:
-    // the contiguous range [kb_begin, kb_end)), two steps in flight
+    // the contiguous range [kb_begin, kb_end)), two steps in flight (one at rank 64)
     __device__ inline void run(int kb_begin, int kb_end, int stride = KB)
     {
         run(kb_begin, kb_end, stride, [] {});
@@ -148,6 +148,20 @@ struct ShrinkWave {
             for (int a = 0; a < NACC; ++a) acc[pj][a] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (kb_begin >= kb_end) {
             between();
+            return;
+        }
+        if constexpr (R == 64 && NT) {
+            // one step in flight: at rank 64 the second one's registers cost up to three of eight waves per
+            // SIMD (llama shapes, 256 rows 151 -> 148 us, 1024 rows 261 -> 259; slower at the lower ranks)
+            Step s;
+            load(kb_begin, kb_end, s);
+            between();
+            int kb0 = kb_begin;
+            for (; kb0 + stride < kb_end; kb0 += stride) {
+                mma(s);
+                load(kb0 + stride, kb_end, s);
+            }
+            mma(s);
             return;
         }
         Step s0, s1;
