@@ -247,7 +247,7 @@ struct KSplit {
 };
 
 // How the K range of a shrink is cut into parts: enough work items to fill the chip when the
-// batch has few tiles, and no part longer than kPartKBlocks K-blocks.  Depends only on the pool,
+// batch has few tiles, and no part much longer than it has to be.  Depends only on the pool,
 // P and the tile height, so lora_shrink, lora_expand and lora_v_bytes agree.
 KSplit ksplit_decode(const lora_pool *p, int proj, int P)
 {
@@ -404,8 +404,8 @@ size_t moe_ws_bytes(const lora_pool *pool, int P, int tile_rows)
 // x rows that every pair reads for itself (no gather through src_row) are read exactly once, so
 // keeping them cacheable pays only while they are small: from 8 MiB on (16 MiB at ranks 32 and 64,
 // whose kernels fetch half lines) they are streamed, so that they do not push out the output rows,
-// which are read, written and read again by whatever runs next.  Output rows, and read-once input rows of any
-// size, are streamed when the caller says its activations are not in a cache when a call starts
+// which are read, written and read again by whatever runs next.  Output rows, and read-once input
+// rows of any size, are streamed when the caller says its activations are not in a cache when a call starts
 // (LORA_ACT_STREAMING); output rows also when one call's outputs exceed the memory-side cache
 // anyway.  LORA_ACT_RESIDENT switches both off.
 bool stream_x(const lora_pool *pool, const int32_t *src_row, int64_t x_bytes)

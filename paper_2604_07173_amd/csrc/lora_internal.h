@@ -24,7 +24,7 @@ constexpr int kTileRows = 32;        // rows per tile of the long-segment kernel
 constexpr int kDecodeTileRows = 16;  // rows per tile of the decode kernels
 constexpr int kKBlock = 32;          // K elements per MFMA step (v_mfma_f32_16x16x32_bf16)
 constexpr int kColChunk = 128;       // output columns one wave owns in expand
-constexpr int kPartKBlocks = 32;     // K-blocks one shrink workgroup reduces (1024 inputs)
+constexpr int kPartKBlocks = 32;     // long segments: K-blocks of a part that the workspace is sized by
 constexpr int kMaxParts = 64;
 // Shrink and expand in one launch (fused_decode.hip): limits and work split, measured on MI355X.
 constexpr int kFusedWaves = 8;         // waves of a workgroup = 128-column chunks of a work item
