@@ -33,13 +33,15 @@ namespace {
 // first (segments_inline.h) and takes tile records and row indices from there, and workgroup 0
 // writes them out for the launches that follow.
 //
+// HALVES (rank 16): the tiles have up to 32 rows and are taken in halves.
 // XNT: the x rows are loaded with the streaming hint (K-split form only).
 // LINES: the x rows are fetched as whole cache lines and transposed through LDS (shrink_wave.h;
 // K-split form, ranks 8 and 16).  Used together with XNT: a streamed line that is fetched in two
 // halves by two instructions is fetched twice.  Measured on MI355X (rank 16, 14336 inputs): 4096
 // rows of the Mixtral down projection 48.5 -> 41.7 us, of the Llama one 60.9 -> 51.0 us for the
 // whole application; with inputs that stay cached (4096 wide, or few rows) it costs 5-10 %.
-template <int R, int NPROJ, bool NT, bool WPT, bool BUILD = false, bool XNT = false, bool LINES = false>
+template <int R, int NPROJ, bool NT, bool WPT, bool BUILD = false, bool XNT = false, bool LINES = false,
+          bool HALVES = false>
 __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
                                                           const lora_tile *__restrict__ tiles,
                                                           const Unit *__restrict__ units,
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
         build_segments_inline<4>(p.seg, scratch.counts, built, blockIdx.x == 0);   // `built` is complete behind its last barrier
         n_tiles = built.n_tiles;
     } else {
-        n_tiles = counts[2] << p.tile_halves;
+        n_tiles = HALVES ? 2 * counts[2] : counts[2];
     }
     const int n_items = n_tiles * p.n_parts;
     const int kblocks = (p.h_in + KU - 1) / KU;
@@ -89,8 +91,8 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
             t.row0 = __builtin_amdgcn_readfirstlane(t.row0);
             t.n_rows = __builtin_amdgcn_readfirstlane(t.n_rows);
         } else {
-            t = tiles[tile_ix >> p.tile_halves];
-            if (p.tile_halves) {                      // rows 0..15 or 16..31 of a 32-row tile
+            t = tiles[HALVES ? tile_ix >> 1 : tile_ix];
+            if constexpr (HALVES) {                   // rows 0..15 or 16..31 of a 32-row tile
                 const int off = (tile_ix & 1) * kDecodeTileRows;
                 t.row0 += off;
                 t.n_rows = min(t.n_rows - off, kDecodeTileRows);
@@ -186,6 +188,20 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     }
 }
 
+template <int R, int NPROJ, bool HALVES>
+void launch_form(const ShrinkParams &p, hipStream_t s)
+{
+    if (p.wave_per_tile)
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, true, false, false, false, HALVES>), dim3(p.grid), dim3(256), 0,
+                           s, p, p.tiles, p.units, p.counts);
+    else if (p.x_stream)       // large inputs that are read once: streamed, as whole lines where a step is 256 bytes of a row
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, true, (R <= 16), HALVES>), dim3(p.grid),
+                           dim3(256), 0, s, p, p.tiles, p.units, p.counts);
+    else
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, false, false, HALVES>), dim3(p.grid), dim3(256),
+                           0, s, p, p.tiles, p.units, p.counts);
+}
+
 template <int R, int NPROJ>
 hipError_t launch_rn(const ShrinkParams &p, hipStream_t s)
 {
@@ -194,15 +210,12 @@ hipError_t launch_rn(const ShrinkParams &p, hipStream_t s)
             return hipErrorInvalidValue;
         hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, true>), dim3(p.grid), dim3(256), 0, s, p,
                            p.tiles, p.units, p.counts);
-    } else if (p.wave_per_tile)
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, true>), dim3(p.grid), dim3(256), 0, s, p,
-                           p.tiles, p.units, p.counts);
-    else if (p.x_stream)       // large inputs that are read once: streamed, as whole lines where a step is 256 bytes of a row
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, true, (R <= 16)>), dim3(p.grid), dim3(256), 0,
-                           s, p, p.tiles, p.units, p.counts);
-    else
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false>), dim3(p.grid), dim3(256), 0, s, p,
-                           p.tiles, p.units, p.counts);
+    } else if (p.tile_halves) {
+        if constexpr (R == 16) launch_form<R, NPROJ, true>(p, s);
+        else return hipErrorInvalidValue;             // the other ranks' 32-row tiles have kernels of their own
+    } else {
+        launch_form<R, NPROJ, false>(p, s);
+    }
     return hipGetLastError();
 }
 
