@@ -248,7 +248,8 @@ struct KSplit {
 
 // How the K range of a shrink is cut into parts: enough work items to fill the chip when the
 // batch has few tiles, and no part much longer than it has to be.  Depends only on the pool,
-// P and the tile height, so lora_shrink, lora_expand and lora_v_bytes agree.
+// P and the tile height (long segments: on the segments as well, on the device), so lora_shrink,
+// lora_expand and lora_v_bytes agree.
 KSplit ksplit_decode(const lora_pool *p, int proj, int P)
 {
     const int kblocks = kblocks_of(p->d.proj[proj].h_in, p->d.rank);
@@ -302,46 +303,21 @@ KSplit ksplit_decode(const lora_pool *p, int proj, int P)
     return k;
 }
 
+// Long segments: the kernels look at the number of tiles and take the split from there (long_split);
+// here it is only bounded, by what the workspace has room for.  n_parts: that bound.
 KSplit ksplit_long(const lora_pool *p, int proj, int P)
 {
     const int kblocks = kblocks_of(p->d.proj[proj].h_in, p->d.rank);
-    // work items are blocks of rows of one segment; the workspace has room for the finest split used
-    const int tiles_per_item = shrink_long_rows() / kTileRows;
     const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(p, P, kTileRows));
-    const int64_t groups = (tub + tiles_per_item - 1) / tiles_per_item;
+    const int64_t groups = (tub + kLongRows / kTileRows - 1) / (kLongRows / kTileRows);
     static const int target = tune_int("LORA_SHRINK_ITEMS", 512, 1, 1 << 20);
     const int want = (int)std::min<int64_t>((target + groups - 1) / groups, kMaxParts);
     const int by_size = (kblocks + kPartKBlocks - 1) / kPartKBlocks;
-    auto whole = [&](int n) { return ((kblocks + n - 1) / n + 3) / 4 * 4; };
-    const int most = std::min(std::min(std::max(want, by_size), std::max(1, kblocks / 4)), kMaxParts);
     KSplit k;
     k.wave_per_tile = false;
-    k.ws_parts = (kblocks + whole(most) - 1) / whole(most);
-    // Two items fit a CU at a time, and all of them run for about as long, so a second round that is
-    // nearly empty costs a whole one: as many parts as one round of the chip takes.  Few blocks need
-    // less than a full round (more parts are more fp32 sums to write and read); many take several
-    // rounds, by how well those fill.  prefill of 16384 rows in 8 uneven requests, rank 64: 3 parts
-    // 290 us, 4 parts (544 items on 512 places) 305, 2 parts 298; 4096 rows: 5 parts 106, 13 parts 115.
-    int n = 1;
-    static const int places = tune_int("LORA_SHRINK_PLACES", 512, 1, 1 << 20);
-    static const int few = tune_int("LORA_SHRINK_FEW", 220, 1, 1 << 20);
-    if (groups < 64) {
-        n = (int)std::max<int64_t>(1, few / groups);
-    } else if (groups <= places) {
-        n = (int)(places / groups);
-    } else {
-        double best = 0;
-        for (int c = 1; c <= 4; ++c) {
-            const double rounds = std::ceil((double)groups * c / places);
-            const double filled = groups * c / (rounds * places) * (1 - 0.04 * c);
-            if (filled > best) {
-                best = filled;
-                n = c;
-            }
-        }
-    }
-    k.kb_per_part = whole(std::min(n, most));
-    k.n_parts = (kblocks + k.kb_per_part - 1) / k.kb_per_part;
+    k.n_parts = std::min(std::min(std::max(want, by_size), std::max(1, kblocks / 4)), kMaxParts);
+    k.kb_per_part = ((kblocks + k.n_parts - 1) / k.n_parts + 3) / 4 * 4;
+    k.ws_parts = (kblocks + k.kb_per_part - 1) / k.kb_per_part;
     return k;
 }
 
@@ -461,10 +437,10 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
         sp.grid = (int)std::min<int64_t>(wgs, (int64_t)cu_count() * per_cu);
         return sp;
     }
-    // 32-row tiles: work items are groups of tiles; at most two projections per launch
+    // long segments: work items are blocks of rows of one segment; at most two projections per launch
     static const int per_cu = tune_int("LORA_SHRINK_WGS_PER_CU", 2, 1, 64);
     const int64_t keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
-    const int64_t groups = std::min<int64_t>(seg->P, std::min<int64_t>(keys, seg->P) + seg->P / shrink_long_rows());
+    const int64_t groups = std::min<int64_t>(seg->P, std::min<int64_t>(keys, seg->P) + seg->P / kLongRows);
     sp.seg_start = seg->seg_start;
     sp.seg_key = seg->seg_key;
     sp.grid = (int)std::min<int64_t>(groups * ks.n_parts, (int64_t)cu_count() * per_cu);
@@ -617,6 +593,7 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     // long segments: operand images of the sub-tiles behind the K parts in each projection's
     // slice of the workspace, then wave items = (group of tiles, projection, 128-column chunk)
     static const int per_cu = tune_int("LORA_EXPAND_WGS_PER_CU", 32, 1, 64);
+    ep.kblocks = kblocks_of(pool->d.proj[g.proj0].h_in, pool->d.rank);
     ep.proj0 = g.proj0;
     ep.n_fused = g.n;
     ep.slice0[0] = 0;
@@ -628,7 +605,7 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         ep.n_chunks[j] = chunks_of(ep.h_out[j]);
         ep.n_slices[j] = ep.n_chunks[j];
         ep.slice0[j + 1] = ep.slice0[j] + ep.n_chunks[j];
-        ep.img[j] = reinterpret_cast<char *>(g.v[j]) + parts_bytes(pool, ks.n_parts, seg->P);
+        ep.img[j] = reinterpret_cast<char *>(g.v[j]) + parts_bytes(pool, ks.ws_parts, seg->P);
     }
     for (int j = g.n; j < kMaxFused; ++j) ep.slice0[j + 1] = ep.slice0[g.n];
     ep.waves = 4;

@@ -62,6 +62,7 @@ __global__ __launch_bounds__(256) void operand_image_kernel(ExpandParams p,
     const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave), nw = gridDim.x * 4;
     const int n_slots = counts[2] * 2;                 // 16-row sub-tiles, two per tile
     const int64_t part_stride = (int64_t)p.P * R;
+    const int n_parts = long_split(counts[2], p.kblocks, p.n_parts).n_parts;        // as the shrink has it
 
     for (int s = gw; s < n_slots * p.n_fused; s += nw) {
         const int pj = s / n_slots;
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(256) void operand_image_kernel(ExpandParams p,
             float sum[KV];
 #pragma unroll
             for (int q = 0; q < KV; ++q) sum[q] = 0.f;
-            for (int part = 0; part < p.n_parts; ++part) {
+            for (int part = 0; part < n_parts; ++part) {
 #pragma unroll
                 for (int h = 0; h < KV / 4; ++h) {
                     const f32x4 x = ld16f(vrow + part * part_stride + jb + 4 * h);

@@ -21,6 +21,7 @@ struct Unit {
 static_assert(sizeof(Unit) == 32, "table entry is 32 bytes");
 
 constexpr int kTileRows = 32;        // rows per tile of the long-segment kernels
+constexpr int kLongRows = 128;       // rows of one segment per work item of the long-segment shrink
 constexpr int kDecodeTileRows = 16;  // rows per tile of the decode kernels
 constexpr int kKBlock = 32;          // K elements per MFMA step (v_mfma_f32_16x16x32_bf16)
 constexpr int kColChunk = 128;       // output columns one wave owns in expand
@@ -60,6 +61,48 @@ inline int kunit_of(int rank) { return rank == 8 ? 64 : kKBlock; }   // K values
 inline int kblocks_of(int h_in, int rank) { return (h_in + kunit_of(rank) - 1) / kunit_of(rank); }
 // K-blocks a wave of the decode shrink takes per step: 128 K values at ranks 8 and 16, 64 and 32 above
 constexpr int shrink_wave_units(int rank) { return rank == 8 ? 2 : rank == 16 ? 4 : rank == 32 ? 2 : 1; }
+// K parts of the long-segment shrink.  Two work items fit a CU at a time, and all of them run for about
+// as long, so a second round that is nearly empty costs a whole one: as many K parts as one round of the
+// chip takes.  Few items need less than a full round (more parts are more fp32 sums to write and read);
+// many take several rounds, by how well those fill.  The tiles are counted, four to a full block: 16384 rows in 8 uneven requests (130
+// fours and more), rank 64, 3 parts 290 us, 4 parts (two rounds) 305, 2 parts 298; in 8 equal ones (128)
+// 4 parts 284, 3 parts 288; 4096 rows, 5 parts 106, 13 parts 115.  The tiles, and not a bound from the
+// number of rows, because that cannot tell the equal requests from the uneven ones.  `most`: what the
+// workspace has room for.  Whole numbers only: the shrink and the kernel that adds its parts both call it and
+// have to come to the same result.
+struct LongSplit {
+    int n_parts, kb_per_part;
+};
+
+__host__ __device__ inline LongSplit long_split(int n_tiles, int kblocks, int most)
+{
+    constexpr int kPlaces = 512, kFew = 220;
+    const int fours = n_tiles > 0 ? (n_tiles + 3) / 4 : 1;
+    int n = 1;
+    if (fours < 64) {
+        n = kFew / fours;
+    } else if (fours <= kPlaces) {
+        n = kPlaces / fours;
+    } else {
+        // c parts take `rounds` rounds; the share of them that is filled, less 4 % for a part's sums
+        long long best_filled = 0, best_rounds = 1;
+        for (int c = 1; c <= 4; ++c) {
+            const long long rounds = (fours * c + kPlaces - 1) / kPlaces;
+            const long long filled = (long long)fours * c * (100 - 4 * c);
+            if (filled * best_rounds > best_filled * rounds) {
+                best_filled = filled;
+                best_rounds = rounds;
+                n = c;
+            }
+        }
+    }
+    n = n < most ? n : most;
+    LongSplit s;
+    s.kb_per_part = ((kblocks + n - 1) / n + 3) / 4 * 4;
+    s.n_parts = (kblocks + s.kb_per_part - 1) / s.kb_per_part;
+    return s;
+}
+
 inline int chunks_of(int h_out) { return (h_out + kColChunk - 1) / kColChunk; }
 inline size_t packed_A_bytes(int h_in, int rank) { return (size_t)kblocks_of(h_in, rank) * kunit_of(rank) * rank * 2; }
 inline size_t packed_B_bytes(int h_out, int rank) { return (size_t)chunks_of(h_out) * kColChunk * rank * 2; }
@@ -132,8 +175,8 @@ struct ShrinkParams {
     float *v[kMaxFused];     // per fused projection: [n_parts][P][rank]
     int P;
     int h_in;
-    int n_parts;
-    int kb_per_part;
+    int n_parts;             // long-segment kernel: the most parts there may be (long_split)
+    int kb_per_part;         // decode kernel
     int rank;
     int grid;
     int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
@@ -149,7 +192,8 @@ struct ExpandParams {
     int proj0;
     int n_fused;             // 1 .. kMaxFused consecutive projections; their widths may differ
     const float *v[kMaxFused];
-    int n_parts;
+    int n_parts;             // long-segment kernels: the most parts there may be (long_split)
+    int kblocks;             // long-segment kernels: K-blocks of the input
     int P;
     const int32_t *perm;
     const lora_tile *tiles;
@@ -208,7 +252,6 @@ int inline_build_max_keys();
 bool segments_large_handles(const SegParams &p);    // does the multi-workgroup builder take this batch?
 int segments_large_launches(const SegParams &p);    // kernels it enqueues for it
 hipError_t launch_shrink(const ShrinkParams &p, hipStream_t s);
-int shrink_long_rows();                                  // rows of one segment per work item of launch_shrink
 hipError_t launch_expand(const ExpandParams &p, hipStream_t s);
 size_t expand_image_bytes(int rank, int64_t n_tiles);   // operand images of n_tiles 32-row tiles
 int expand_long_group();                                 // tiles per wave item of launch_expand

@@ -16,7 +16,7 @@
 // never spans two segments, so every one of them runs the shared-A loop: blocks of four consecutive
 // tiles that straddled a segment boundary took a path without LDS or prefetch, one K block at a time,
 // and the launch waited for them.  16384 rows in 8 uneven requests, rank 64, whole call: 308 -> 290 us
-// (with as many K parts as one round of the chip takes); 64 adapters, 4096 rows, rank 64: 157 -> 143.
+// (with as many K parts as one round of the chip takes, long_split); 64 adapters, 4096 rows, rank 64: 157 -> 143.
 // Which segment a block belongs to is looked up by the workgroup: a prefix sum of the segments' block
 // counts, 256 segments at a time.  Every wave owns
 // its rows for the whole K part, so there is no cross-wave reduction; lora_expand adds the K parts in
@@ -34,7 +34,7 @@ namespace lora {
 namespace {
 
 constexpr int kLongTiles = 4;        // tiles (waves) per work item
-constexpr int kLongRows = kLongTiles * kTileRows;
+static_assert(kLongRows == kLongTiles * kTileRows, "a wave takes a tile's rows");
 constexpr int kStageKB = 4;          // K blocks per LDS stage
 
 // Segment of the grp-th block of kLongRows rows and the block's number inside it; false when there
@@ -99,11 +99,12 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
     const int g = lane >> 4, i16 = lane & 15;
     const int S = counts[0];
     const int kblocks = (p.h_in + kKBlock - 1) / kKBlock;
+    const LongSplit split = long_split(counts[2], kblocks, p.n_parts);
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
 
     for (int item = blockIdx.x;; item += gridDim.x) {
-        const int grp = item / p.n_parts;
-        const int part = item - grp * p.n_parts;
+        const int grp = item / split.n_parts;
+        const int part = item - grp * split.n_parts;
         int seg, block;
         if (!find_block(seg_start, S, grp, reinterpret_cast<int *>(dyn_lds), &seg, &block)) break;   // uniform
         seg = __builtin_amdgcn_readfirstlane(seg);
@@ -137,8 +138,8 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
                 xq[sub][j] = p.x + (int64_t)s * p.ldx;            // start of the row
             }
 
-        const int kb_begin = part * p.kb_per_part;
-        const int kb_end = min(kb_begin + p.kb_per_part, kblocks);
+        const int kb_begin = part * split.kb_per_part;
+        const int kb_end = min(kb_begin + split.kb_per_part, kblocks);
         const int n_stages = (kb_end - kb_begin + kStageKB - 1) / kStageKB;
 
         f32x4 acc[NPROJ][SUB][NB];
@@ -270,8 +271,6 @@ hipError_t launch_r(const ShrinkParams &p, hipStream_t s)
 }
 
 }  // namespace
-
-int shrink_long_rows() { return kLongRows; }
 
 hipError_t launch_shrink(const ShrinkParams &p, hipStream_t s)
 {

@@ -55,6 +55,29 @@ def test_blocks_of_segments(rank, lengths, shuffle, monkeypatch):
     run_lengths(lengths, rank, (392, 136, 264), 1032, 3, "normal", shuffle)
 
 
+@pytest.mark.parametrize("rank", [32, 64])
+@pytest.mark.parametrize("lengths,h_in,parts", [([2048] * 8, 2048, 4), ([2047] * 7 + [2055], 2048, 3),
+                                                ([1024] * 8, 2048, 8), ([400] * 12, 2048, 4), ([8192] * 16, 512, 1)])
+def test_k_parts_follow_the_tiles_of_the_batch(lengths, h_in, parts, rank):
+    """Fours of 32-row tiles on 512 places (220 below 64 fours): equal requests of 2048 rows have 128
+    fours and take four K parts, and one tile more takes three, though the number of rows is the same.
+    Every row of every part is written, and no other."""
+    n, P = len(lengths), sum(lengths)
+    w = W.Workload("t", "dense", n, 1, 1, rank, (W.Proj("p", h_in, 8, "x"),), P, "uniform")
+    b = W.make_batch(w, 6, y_mode="zero")
+    b.adapter_id[:] = np.repeat(np.arange(n, dtype=np.int32), lengths)
+    dp, db = DevicePool(W.make_weights(w, 6, bank_elems=1 << 22), b.scale), DeviceBatch(b)
+    run = LayerRunner(dp, db)
+    run.build_segments()
+    run.v.fill_(float("nan"))
+    x = db.inputs["x"]
+    L.lora_shrink(dp.pool, 0, 0, x, x.shape[1], None, db.seg, run.v)
+    torch.cuda.synchronize()
+    assert db.seg.c.tile_rows == 32
+    written = ~torch.isnan(run.v)
+    assert int(written.sum()) == parts * P * rank and bool(written[:parts * P * rank].all())
+
+
 @pytest.mark.parametrize("y_mode", ["zero", "normal"])
 @pytest.mark.parametrize("lengths", [EDGES * 5, [8187], [104 + 3 * i for i in range(48)]])
 def test_halves_of_tiles_at_rank_16(lengths, y_mode):
