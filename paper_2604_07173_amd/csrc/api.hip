@@ -437,7 +437,7 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
         sp.grid = (int)std::min<int64_t>(wgs, (int64_t)cu_count() * per_cu);
         return sp;
     }
-    // long segments: work items are blocks of rows of one segment; at most two projections per launch
+    // long segments: work items are blocks or groups of tiles (do_shrink); at most two projections per launch
     static const int per_cu = tune_int("LORA_SHRINK_WGS_PER_CU", 2, 1, 64);
     const int64_t keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
     const int64_t groups = std::min<int64_t>(seg->P, std::min<int64_t>(keys, seg->P) + seg->P / kLongRows);
@@ -468,6 +468,14 @@ int do_shrink(const lora_pool *pool, int layer, const Group &g, const void *x, i
     for (int j = 0; j < g.n; j += 2) {
         sp.proj0 = g.proj0 + j;
         sp.n_fused = std::min(2, g.n - j);
+        // Short segments (less than three tiles on average) leave most waves of a block of one segment
+        // without rows: groups of four tiles then, but for one projection only, because with two a wave has
+        // no registers to fetch enough of its own A ahead.  Layer call in us, blocks / groups: one projection
+        // at rank 32 and 1024 inputs, 4096 adapters with 32 rows each 371 / 336, 256 of them 44.2 / 41.5; two,
+        // rank 64 and 4096 inputs, 128 adapters 91 / 123; 128 rows per adapter 219 / 233.
+        static const int by_tiles = tune_int("LORA_SHRINK_BY_TILES", -1, -1, 1);
+        const int64_t keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
+        sp.by_tiles = by_tiles >= 0 ? by_tiles : sp.n_fused == 1 && seg->P < 96 * keys;
         sp.v[0] = g.v[j];
         sp.v[1] = sp.n_fused == 2 ? g.v[j + 1] : nullptr;
         LORA_HIP(launch_shrink(sp, st));

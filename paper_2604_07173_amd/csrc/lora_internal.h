@@ -179,6 +179,7 @@ struct ShrinkParams {
     int kb_per_part;         // decode kernel
     int rank;
     int grid;
+    int by_tiles;            // long-segment kernel: work items are groups of four tiles, else blocks of one segment
     int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
     int wave_per_tile;       // decode kernel: every wave takes a whole tile (no K split across waves)
     int build;               // decode kernel: the segments are built inside the launch, from `seg`

@@ -12,15 +12,20 @@
 // fetched as whole cache lines, four rows x 256 bytes per instruction, and turned into the MFMA
 // operand layout (16 rows x 64 bytes per operand) through 4 KiB of LDS per wave: fetching them
 // in the operand layout directly costs the address path twice the line look-ups, which a
-// load-only probe of the two streams puts at 32 against 27 us for the prefill workload.  A block
-// never spans two segments, so every one of them runs the shared-A loop: blocks of four consecutive
-// tiles that straddled a segment boundary took a path without LDS or prefetch, one K block at a time,
-// and the launch waited for them.  16384 rows in 8 uneven requests, rank 64, whole call: 308 -> 290 us
-// (with as many K parts as one round of the chip takes, long_split); 64 adapters, 4096 rows, rank 64: 157 -> 143.
-// Which segment a block belongs to is looked up by the workgroup: a prefix sum of the segments' block
-// counts, 256 segments at a time.  Every wave owns
-// its rows for the whole K part, so there is no cross-wave reduction; lora_expand adds the K parts in
-// a fixed order, so results are bit-identical run to run.
+// load-only probe of the two streams puts at 32 against 27 us for the prefill workload.  Every wave
+// owns its rows for the whole K part, so there is no cross-wave reduction; lora_expand adds the K parts
+// in a fixed order, so results are bit-identical run to run.
+//
+// Two ways to number the work items (the host picks, do_shrink in api.hip):
+//  * blocks of one segment, so that every item runs the shared-A loop, found in a list that every wave
+//    holds in registers (BlockList).  For long segments, and for two projections.
+//  * groups of four consecutive tiles, whatever their segments.  A group with a segment boundary inside
+//    has no A to share: every wave fetches the A of its own tile.  For one projection of short segments,
+//    which leave most of a block empty, and for more segments than the list takes.
+// Whole call in us, groups whose waves fetch A without a step in flight / blocks found by walking over the
+// segment list for every item / now: 16384 rows in 8 uneven requests, rank 64, 308 / 291 / 291; 64 adapters,
+// 4096 rows, rank 64, 158 / 145 / 142; 4096 adapters with 32 rows each, 1024 inputs, rank 64 465 / 514 / 450,
+// rank 32 347 / 411 / 336; 2048 adapters with 64 rows each, two projections, rank 64, 667 / 594 / 586.
 //
 // The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and the rows on the N side, so
 // a lane ends up with four consecutive rank entries of one row.  With two fused projections
@@ -37,46 +42,54 @@ constexpr int kLongTiles = 4;        // tiles (waves) per work item
 static_assert(kLongRows == kLongTiles * kTileRows, "a wave takes a tile's rows");
 constexpr int kStageKB = 4;          // K blocks per LDS stage
 
-// Segment of the grp-th block of kLongRows rows and the block's number inside it; false when there
-// are fewer blocks.  The whole workgroup calls it; `scratch` (five ints of LDS) is free again after the
-// caller's next barrier.
-__device__ inline bool find_block(const int32_t *__restrict__ seg_start, int S, int grp, int *scratch, int *seg, int *block)
-{
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    int before = 0;                                       // blocks of the segments looked at so far
-    for (int s0 = 0; s0 < S; s0 += 256) {
-        const int s = s0 + tid;
-        const int n = s < S ? (seg_start[s + 1] - seg_start[s] + kLongRows - 1) / kLongRows : 0;
+constexpr int kListedSegs = 64 * 64;
+
+// The blocks of kLongRows rows of up to kListedSegs segments, in two levels: lane l of every wave keeps how
+// many blocks segments q l .. q l + q - 1 have (q <= 64) and the number of the first one; which of the q
+// segments a block belongs to is read again for each look-up, all of them at a time.  No LDS, no barrier.
+struct BlockList {
+    const int32_t *seg_start;
+    int S, q;
+    int first, n, total;               // the lane's first block and blocks, blocks of the batch
+
+    __device__ inline void make(const int32_t *__restrict__ seg_start_, int S_)
+    {
+        const int lane = threadIdx.x & 63;
+        seg_start = seg_start_;
+        S = S_;
+        q = (S + 63) / 64;
+        n = 0;
+        int at = seg_start[min(lane * q, S)];
+        for (int k = 1; k <= q; ++k) {
+            const int end = seg_start[min(lane * q + k, S)];
+            n += (end - at + kLongRows - 1) / kLongRows;
+            at = end;
+        }
         const int incl = (int)wave_incl_sum((unsigned)n);
-        if (lane == 63) scratch[w] = incl;
-        if (tid == 0) scratch[4] = -1;
-        __syncthreads();
-        int first = before, total = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            first += k < w ? scratch[k] : 0;
-            total += scratch[k];
-        }
-        first += incl - n;
-        if (grp >= first && grp < first + n) scratch[4] = tid;          // one thread at most
-        __syncthreads();
-        const int hit = scratch[4];
-        if (hit >= 0) {
-            *seg = s0 + hit;
-            // the finder's first block, from the owner's lane
-            if (tid == hit) scratch[0] = first;
-            __syncthreads();
-            *block = grp - scratch[0];
-            return true;
-        }
-        before += total;
-        __syncthreads();
+        first = incl - n;
+        total = __builtin_amdgcn_readlane(incl, 63);
     }
-    return false;
-}
+
+    // segment, first row and end row of a block below `total`; the same for all lanes
+    __device__ inline void find(int block, int &seg, int &row0, int &row_end) const
+    {
+        const int lane = threadIdx.x & 63;
+        const int owner = __builtin_ctzll(__ballot(block >= first && block < first + n));
+        const int left = block - __builtin_amdgcn_readlane(first, owner);
+        const int s = min(owner * q + min(lane, q), S);              // lane q and up: no rows
+        const int start = seg_start[s], end = seg_start[min(owner * q + min(lane + 1, q), S)];
+        const int blocks = (end - start + kLongRows - 1) / kLongRows;
+        const int before = (int)wave_incl_sum((unsigned)blocks) - blocks;
+        const int which = __builtin_ctzll(__ballot(left >= before && left < before + blocks));
+        seg = owner * q + which;
+        row0 = __builtin_amdgcn_readlane(start, which) + (left - __builtin_amdgcn_readlane(before, which)) * kLongRows;
+        row_end = __builtin_amdgcn_readlane(end, which);
+    }
+};
 
 template <int R, int NPROJ>
 __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
+                                                             const lora_tile *__restrict__ tiles,
                                                              const int32_t *__restrict__ seg_start,
                                                              const int32_t *__restrict__ seg_key,
                                                              const Unit *__restrict__ units,
@@ -97,29 +110,45 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, i16 = lane & 15;
-    const int S = counts[0];
     const int kblocks = (p.h_in + kKBlock - 1) / kKBlock;
-    const LongSplit split = long_split(counts[2], kblocks, p.n_parts);
+    const int n_tiles = counts[2];
+    const int S = counts[0];
+    const bool listed = !p.by_tiles && S <= kListedSegs;   // blocks of one segment, else groups of four tiles
+    const LongSplit split = long_split(n_tiles, kblocks, p.n_parts);
+    BlockList list;
+    if (listed) list.make(seg_start, S);
+    const int n_items = split.n_parts * (listed ? list.total : (n_tiles + kLongTiles - 1) / kLongTiles);
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
 
-    for (int item = blockIdx.x;; item += gridDim.x) {
+    for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
         const int grp = item / split.n_parts;
         const int part = item - grp * split.n_parts;
-        int seg, block;
-        if (!find_block(seg_start, S, grp, reinterpret_cast<int *>(dyn_lds), &seg, &block)) break;   // uniform
-        seg = __builtin_amdgcn_readfirstlane(seg);
-        block = __builtin_amdgcn_readfirstlane(block);
-        const int key = seg_key[seg];
-        const int seg_row0 = seg_start[seg], seg_end = seg_start[seg + 1];
-        // this wave's rows; a wave beyond the segment's end re-reads its first row and stores nothing
-        const int w_row0 = seg_row0 + block * kLongRows + __builtin_amdgcn_readfirstlane(wave) * kTileRows;
-        const bool live = w_row0 < seg_end;                   // wave-uniform
-        const int row0 = live ? w_row0 : seg_row0;
-        const int n_rows = live ? min(kTileRows, seg_end - w_row0) : 1;
-
-        const uint16_t *Ag[NPROJ];
+        // this wave's rows (a wave without any re-reads valid ones and stores nothing), and whether the
+        // workgroup's belong to one (adapter, expert); all but the rows is the same for all of it
+        lora_tile t;
+        bool live, same_key = true;
+        const int w4 = __builtin_amdgcn_readfirstlane(wave);
+        if (listed) {
+            int block_row0, seg_end;
+            list.find(grp, t.seg, block_row0, seg_end);
+            t.key = seg_key[t.seg];
+            t.row0 = block_row0 + w4 * kTileRows;
+            live = t.row0 < seg_end;
+            if (!live) t.row0 = block_row0;
+            t.n_rows = live ? min(kTileRows, seg_end - t.row0) : 1;
+        } else {
+            const int tix = grp * kLongTiles + w4;
+            live = tix < n_tiles;
+            t = tiles[min(tix, n_tiles - 1)];
+            const int key0 = tiles[grp * kLongTiles].key;
 #pragma unroll
-        for (int pj = 0; pj < NPROJ; ++pj) Ag[pj] = units[(int64_t)key * p.n_proj + p.proj0 + pj].A;
+            for (int k = 1; k < kLongTiles; ++k)
+                same_key = same_key && tiles[min(grp * kLongTiles + k, n_tiles - 1)].key == key0;
+        }
+
+        const uint16_t *Ag[NPROJ];                            // this wave's A; where it is shared, the group's
+#pragma unroll
+        for (int pj = 0; pj < NPROJ; ++pj) Ag[pj] = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].A;
 
         // gathered input rows as they are fetched: one instruction reads four rows (lane group g) x
         // 256 contiguous bytes (16 lanes x 16 bytes), i.e. whole cache lines, which the address path
@@ -132,8 +161,8 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = sub * 16 + j * 4 + g;
-                qv[sub][j] = live && r < n_rows;
-                int s = p.perm[row0 + min(r, n_rows - 1)];
+                qv[sub][j] = live && r < t.n_rows;
+                int s = p.perm[t.row0 + min(r, t.n_rows - 1)];
                 if (p.src_row) s = p.src_row[s];
                 xq[sub][j] = p.x + (int64_t)s * p.ldx;            // start of the row
             }
@@ -216,24 +245,81 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
                     }
         };
 
-        u32x4 areg[LOADS];
         u32x4 xr[SUB][4];                  // the next stage's x as fetched
         u32x4 xc[SUB][kStageKB];           // the current stage's x as MFMA operands
-        load_a(kb_begin, areg);
-        load_rows(kb_begin, xr);
-        __syncthreads();                   // the look-up's scratch lies in the first stage
-        store_a(areg, lds[0]);
-        to_operands(xr, xc);
-        __syncthreads();
-        for (int s = 0; s < n_stages; ++s) {
-            const int kb0 = kb_begin + s * kStageKB;
-            load_a(kb0 + kStageKB, areg);                 // beyond the part: zeros, never multiplied
-            load_rows(kb0 + kStageKB, xr);
-            __builtin_amdgcn_sched_barrier(0);            // all of the next stage's loads first
-            compute(lds[s & 1], xc);
-            store_a(areg, lds[(s + 1) & 1]);
+        if (same_key) {
+            u32x4 areg[LOADS];
+            load_a(kb_begin, areg);
+            load_rows(kb_begin, xr);
+            store_a(areg, lds[0]);
             to_operands(xr, xc);
             __syncthreads();
+            if (live) {
+#pragma unroll 1
+                for (int s = 0; s < n_stages; ++s) {
+                    const int kb0 = kb_begin + s * kStageKB;
+                    const bool more = s + 1 < n_stages;
+                    if (more) {
+                        load_a(kb0 + kStageKB, areg);
+                        load_rows(kb0 + kStageKB, xr);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);        // all of the next stage's loads first
+                    compute(lds[s & 1], xc);
+                    if (more) {
+                        store_a(areg, lds[(s + 1) & 1]);
+                        to_operands(xr, xc);
+                    }
+                    __syncthreads();
+                }
+            } else {                                          // no rows: only this wave's share of A
+                for (int s = 0; s < n_stages; ++s) {
+                    if (s + 1 < n_stages) {
+                        load_a(kb_begin + (s + 1) * kStageKB, areg);
+                        store_a(areg, lds[(s + 1) & 1]);
+                    }
+                    __syncthreads();
+                }
+            }
+        } else if (live) {
+            // tiles of several segments: every wave reads the A of its own tile, a step of kOwn operand
+            // blocks ahead, without LDS and without barriers
+            constexpr int kOwn = NPROJ == 2 ? 4 : kStageKB * BLK < 8 ? kStageKB * BLK : 8;    // two projections: no registers for eight
+            auto load_own = [&](int kb0, int b0, u32x4 (&a)[kOwn]) {
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i) {
+                    const int b = b0 + i, pj = b % BLK / NB, nb = b % NB;
+                    const bool k_ok = kb0 + b / BLK < kb_end;
+                    const int kb = k_ok ? kb0 + b / BLK : kb_end - 1;
+                    const u32x4 v = ld16<false>(Ag[pj] + (((int64_t)kb * NB + nb) * 64 + lane) * 8);
+                    a[i] = k_ok ? v : zero4;
+                }
+            };
+            u32x4 a[kOwn], an[kOwn];
+            load_rows(kb_begin, xr);
+            load_own(kb_begin, 0, a);
+            to_operands(xr, xc);
+#pragma unroll 1
+            for (int s = 0; s < n_stages; ++s) {
+                const int kb0 = kb_begin + s * kStageKB;
+                const bool more = s + 1 < n_stages;
+#pragma unroll
+                for (int b0 = 0; b0 < kStageKB * BLK; b0 += kOwn) {
+                    load_own(kb0, b0 + kOwn, an);             // beyond the part: zeros, never multiplied
+                    if (more && b0 == 0) load_rows(kb0 + kStageKB, xr);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < kOwn; ++i)
+#pragma unroll
+                        for (int sub = 0; sub < SUB; ++sub) {
+                            f32x4 &c = acc[(b0 + i) % BLK / NB][sub][(b0 + i) % NB];
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a[i]), as_bf16x8(xc[sub][(b0 + i) / BLK]),
+                                                                        c, 0, 0, 0);
+                        }
+#pragma unroll
+                    for (int i = 0; i < kOwn; ++i) a[i] = an[i];
+                }
+                if (more) to_operands(xr, xc);
+            }
         }
 
         // this wave's rows of this part of v: lane (row i16, group g) holds rank entries
@@ -242,10 +328,10 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
         for (int pj = 0; pj < NPROJ; ++pj)
 #pragma unroll
             for (int sub = 0; sub < SUB; ++sub)
-                if (live && sub * 16 + i16 < n_rows) {
+                if (live && sub * 16 + i16 < t.n_rows) {
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        st16f(p.v[pj] + ((int64_t)part * p.P + row0 + sub * 16 + i16) * R + nb * 16 + g * 4,
+                        st16f(p.v[pj] + ((int64_t)part * p.P + t.row0 + sub * 16 + i16) * R + nb * 16 + g * 4,
                               acc[pj][sub][nb]);
                 }
     }
@@ -259,7 +345,7 @@ hipError_t launch_rn(const ShrinkParams &p, hipStream_t s)
     static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(shrink_long_kernel<R, NPROJ>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((shrink_long_kernel<R, NPROJ>), dim3(p.grid), dim3(256), kLds, s, p, p.seg_start,
+    hipLaunchKernelGGL((shrink_long_kernel<R, NPROJ>), dim3(p.grid), dim3(256), kLds, s, p, p.tiles, p.seg_start,
                        p.seg_key, p.units, p.counts);
     return hipGetLastError();
 }

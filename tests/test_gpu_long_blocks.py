@@ -78,6 +78,44 @@ def test_k_parts_follow_the_tiles_of_the_batch(lengths, h_in, parts, rank):
     assert int(written.sum()) == parts * P * rank and bool(written[:parts * P * rank].all())
 
 
+@pytest.mark.parametrize("rank,n_proj", [(16, 1), (16, 2), (32, 1), (32, 2), (64, 1), (64, 3)])
+@pytest.mark.parametrize("n", [64, 65, 129, 4096, 4097])
+def test_both_ways_to_number_the_work_items(n, rank, n_proj, monkeypatch):
+    """Blocks of one segment (launches of two projections, up to 4096 segments) and groups of four tiles:
+    short and long segments mixed, every group of tiles with a segment boundary and, in the run of 513
+    rows, some without."""
+    monkeypatch.setenv("LORA_TILE_ROWS", "32")
+    lengths = [1 + (i * 7) % 3 for i in range(n)]
+    lengths[n // 3], lengths[n // 2], lengths[-1] = 513, 130, 33
+    run_lengths(lengths, rank, (136, 40, 8)[:n_proj], 392, 5, "normal", True)
+
+
+def test_finding_a_work_items_segment_is_cheap():
+    """The gate/up shrink of the same 524288 rows in 64 and in 16384 segments.  The many short ones read 256
+    times the weights; walking over the list of segments for every work item cost far more than that (1.5
+    times the time of the few long ones; 7.9 times with the walk)."""
+    P, h_in, us = 524288, 64, {}
+    for n in (64, 16384):
+        projs = (W.Proj("gate", h_in, 8, "x"), W.Proj("up", h_in, 8, "x"), W.Proj("down", 8, h_in, "mid"))
+        w = W.Workload("t", "moe", n, 1, 1, 32, projs, P, "uniform")
+        b = W.make_batch(w, 7, y_mode="zero")
+        dp, db = DevicePool(W.make_weights(w, 7, bank_elems=1 << 20), b.scale), DeviceBatch(b)
+        run = LayerRunner(dp, db)
+        run.build_segments()
+        assert db.seg.c.tile_rows == 32
+        x, times = db.inputs["x"], []
+        for _ in range(15):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            L.lora_moe_shrink(dp.pool, 0, L.LORA_MOE_UPGATE, x, h_in, db.token_of_pair, db.seg, run.ws)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 1e3)
+        us[n] = sorted(times)[len(times) // 2]
+    print("us by segments:", us)
+    assert us[16384] <= 4 * us[64], us
+
+
 @pytest.mark.parametrize("y_mode", ["zero", "normal"])
 @pytest.mark.parametrize("lengths", [EDGES * 5, [8187], [104 + 3 * i for i in range(48)]])
 def test_halves_of_tiles_at_rank_16(lengths, y_mode):
