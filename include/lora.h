@@ -169,7 +169,7 @@ int lora_pool_set_adapter(lora_pool *pool, int adapter, int rank, float scale, v
  *   LORA_ACT_AUTO (default)  input and output rows go through the caches, as suits rows that
  *       the kernel before the call has just written and the kernel after it will read; input
  *       rows that every pair reads for itself (no src_row / token_of_pair gather) are streamed
- *       once they reach 8 MiB per call (16 MiB at ranks 32 and 64), output rows once a call's
+ *       once they reach 16 MiB per call (64 MiB at rank 64), output rows once a call's
  *       outputs reach 256 MiB (the memory-side cache holds 256 MiB).
  *   LORA_ACT_RESIDENT        no streaming hint on any activation, whatever its size.
  *   LORA_ACT_STREAMING       for callers whose activations are in HBM only when a call starts

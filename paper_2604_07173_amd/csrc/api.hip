@@ -378,8 +378,8 @@ size_t moe_ws_bytes(const lora_pool *pool, int P, int tile_rows)
 // the per-launch projection fields)
 // Cache hints of the activation streams (the weights are always streamed: they are read once).
 // x rows that every pair reads for itself (no gather through src_row) are read exactly once, so
-// keeping them cacheable pays only while they are small: from 8 MiB on (16 MiB at ranks 32 and 64,
-// whose kernels fetch half lines) they are streamed, so that they do not push out the output rows,
+// keeping them cacheable pays only while they are small: from 16 MiB on (64 MiB at rank 64, whose
+// kernels fetch half lines) they are streamed, so that they do not push out the output rows,
 // which are read, written and read again by whatever runs next.  Output rows, and read-once input
 // rows of any size, are streamed when the caller says its activations are not in a cache when a call starts
 // (LORA_ACT_STREAMING); output rows also when one call's outputs exceed the memory-side cache
@@ -389,7 +389,7 @@ bool stream_x(const lora_pool *pool, const int32_t *src_row, int64_t x_bytes)
     static const int mb_env = tune_int("LORA_X_STREAM_MB", 0, 0, 1 << 20);
     if (pool->act_policy == LORA_ACT_RESIDENT || src_row) return false;
     if (pool->act_policy == LORA_ACT_STREAMING) return true;
-    const int mb = mb_env ? mb_env : pool->d.rank <= 16 ? kStreamXMiB : kStreamXHighRankMiB;
+    const int mb = mb_env ? mb_env : pool->d.rank <= 32 ? kStreamXMiB : kStreamXRank64MiB;
     return x_bytes >= (int64_t)mb << 20;
 }
 

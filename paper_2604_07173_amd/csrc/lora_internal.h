@@ -39,20 +39,29 @@ constexpr int kFusedMaxTiles = 64;     // largest batch, as the host's upper bou
 // 10.7; query/key/value of the Llama shapes, 8 rows, 3.1 M: two launches win by 2 us).
 constexpr int64_t kFusedMaxWork = 21ll << 17;      // twice that at rank 8, whose A is half the bytes of rank 16
 // Cache hints of the activation streams of the decode kernels, measured on MI355X.  Input rows that
-// are read once are streamed from kStreamXMiB on, and at ranks 8 and 16 fetched as whole lines.
-// Layer call in us, cacheable / streamed, by where the activations are when it starts (in HBM only;
-// just written by the kernels before; left in the memory-side cache by the previous call):
-//   Mixtral shapes, 512 tokens (28 MiB)   117.7 / 107.3    113.9 / 113.8    105.8 / 106.5
-//   llama shapes, 1024 rows (8 and 28 MiB), rank 8   103.6 / 97.6    98.7 / 99.0    92.6 / 96.1
-//     rank 64   305.8 / 292.8    292.5 / 299.6    269.9 / 275.9 (half lines: hence the higher limit)
-//   llama shapes, 512 rows (4 and 14 MiB; 2 MiB as the limit)   81.1 / 84.1    82.7 / 84.7    80.9 / 84.0
+// are read once are streamed from kStreamXMiB on, fetched as whole lines (ranks 8 to 32).  A wave of rank 64
+// takes 64 bytes of a row per step, and half a line that is fetched with the streaming hint costs where the
+// line was in a cache, so rank 64 streams only from kStreamXRank64MiB on (two steps as one, which would
+// fetch whole lines, cost the smaller batches 1-3 %: their order of sums has to be the same).
+// Layer call in us, cacheable / streamed in one process, by where the activations are when it starts
+// (in HBM only; just written by the kernels before; left in the memory-side cache by the previous call):
+//   Mixtral shapes, 512 tokens (28 MiB), rank 8    85.4 / 80.3    81.9 / 82.7    77.2 / 78.2
+//     rank 16  117.5 / 108.7  115.2 / 114.2  105.3 / 106.3;   rank 32  193.1 / 179.0  192.2 / 191.0  174.7 / 175.2
+//   Mixtral shapes, 1024 tokens (56 MiB), rank 8   141.0 / 135.0  123.0 / 125.2  114.9 / 116.4
+//     rank 16  176.8 / 168.2  158.0 / 160.3  141.1 / 142.1;   rank 32  270.9 / 259.0  258.5 / 257.8  227.5 / 224.9
+//   llama shapes, 2048 rows (16 and 56 MiB), rank 8   157.1 / 152.0  147.2 / 144.9  140.0 / 133.2
+//     rank 16  176.2 / 170.6  168.5 / 163.1  163.4 / 150.8;   rank 32  258.8 / 243.6  256.2 / 246.0  253.4 / 224.9
+//   rank 64: Mixtral shapes, 512 tokens   337 / 321  340.4 / 343.9  313.7 / 314.7;   1024 tokens   440 / 430
+//     441.6 / 448.6  408.9 / 401.2;   llama shapes, 1024 rows (28 MiB)   263.3 / 257.4  255.1 / 259.7  235.6 / 238.0
+// 8 MiB as the limit of ranks 8 and 16 costs where rows were just written: llama shapes, 1024 rows (8 and
+// 28 MiB), rank 8 95.1 against 94.2 us with 16 MiB, rank 16 108.8 against 108.2.
 // The output rows of one call are streamed from kStreamYMiB on: just-written ones would lose what
 // those in HBM gain (Mixtral shapes, 2048 tokens, 235 MiB: 246.8 / 259.1 against 258.9 / 247.4).
 constexpr int kLongMinRowsTimesRank = 1 << 17;   // long-segment kernels from this many rows x rank on
 constexpr int kLongMinRowsRank16 = 12288;        // rank 16: the long-segment kernels proper from here on, and
 constexpr int kLongRowsPerKeyRank16 = 128;       // from this many rows per key
-constexpr int kStreamXMiB = 8;
-constexpr int kStreamXHighRankMiB = 16;   // ranks 32 and 64
+constexpr int kStreamXMiB = 16;
+constexpr int kStreamXRank64MiB = 64;
 constexpr int kStreamYMiB = 256;
 constexpr int kMaxFused = 3;         // projections that share an input in one launch (q/k/v, gate/up)
 

@@ -36,10 +36,11 @@ namespace {
 // HALVES (rank 16): the tiles have up to 32 rows and are taken in halves.
 // XNT: the x rows are loaded with the streaming hint (K-split form only).
 // LINES: the x rows are fetched as whole cache lines and transposed through LDS (shrink_wave.h;
-// K-split form, ranks 8 and 16).  Used together with XNT: a streamed line that is fetched in two
+// K-split form, ranks 8 to 32).  Used together with XNT: a streamed line that is fetched in two
 // halves by two instructions is fetched twice.  Measured on MI355X (rank 16, 14336 inputs): 4096
 // rows of the Mixtral down projection 48.5 -> 41.7 us, of the Llama one 60.9 -> 51.0 us for the
-// whole application; with inputs that stay cached (4096 wide, or few rows) it costs 5-10 %.
+// whole application; with inputs that stay cached (4096 wide, or few rows) it costs 5-10 %.  Rank 32,
+// Mixtral shapes, 1024 tokens, streamed inputs that were just written: 266.0 -> 257.8 us (258.5 unstreamed).
 template <int R, int NPROJ, bool NT, bool WPT, bool BUILD = false, bool XNT = false, bool LINES = false,
           bool HALVES = false>
 __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
@@ -58,7 +59,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     };
     __shared__ Scratch scratch;
     __shared__ std::conditional_t<BUILD, InlineSegments, char> built;
-    __shared__ u32x4 xt_all[LINES ? 4 * 256 : 1];      // LINES: 4 KiB per wave
+    __shared__ u32x4 xt_all[LINES ? 4 * 64 * Wave::NQ : 1];      // LINES: NQ KiB per wave
     auto &red = scratch.red;
 
     const int tid = threadIdx.x, wave = tid >> 6;
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     w.g = w.lane >> 4;
     w.i16 = w.lane & 15;
     w.h_in = p.h_in;
-    w.xt = xt_all + (LINES ? wave * 256 : 0);
+    w.xt = xt_all + (LINES ? wave * 64 * Wave::NQ : 0);
     int n_tiles;
     if constexpr (BUILD) {
         build_segments_inline<4>(p.seg, scratch.counts, built, blockIdx.x == 0);   // `built` is complete behind its last barrier
@@ -104,19 +105,19 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
             w.Ap[pj] = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].A;
         w.row_ok = w.i16 < t.n_rows;
         if constexpr (LINES) {
-            int s[4];
+            int s[Wave::NQ];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int at = t.row0 + min(4 * q + w.g, t.n_rows - 1);
+            for (int q = 0; q < Wave::NQ; ++q) {
+                const int at = t.row0 + min(Wave::RPI * q + w.lane / Wave::PPR, t.n_rows - 1);
                 if constexpr (BUILD) s[q] = built.perm[at];
                 else s[q] = p.perm[at];
             }
             if (p.src_row) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) s[q] = p.src_row[s[q]];
+                for (int q = 0; q < Wave::NQ; ++q) s[q] = p.src_row[s[q]];
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) w.xq[q] = p.x + (int64_t)s[q] * p.ldx;
+            for (int q = 0; q < Wave::NQ; ++q) w.xq[q] = p.x + (int64_t)s[q] * p.ldx;
             w.xp = w.xq[0];
         } else {
             int s;
@@ -195,7 +196,7 @@ void launch_form(const ShrinkParams &p, hipStream_t s)
         hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, true, false, false, false, HALVES>), dim3(p.grid), dim3(256), 0,
                            s, p, p.tiles, p.units, p.counts);
     else if (p.x_stream)       // large inputs that are read once: streamed, as whole lines where a step is 256 bytes of a row
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, true, (R <= 16), HALVES>), dim3(p.grid),
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, true, (R <= 32), HALVES>), dim3(p.grid),
                            dim3(256), 0, s, p, p.tiles, p.units, p.counts);
     else
         hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, false, false, HALVES>), dim3(p.grid), dim3(256),

@@ -21,13 +21,13 @@ namespace lora {
 // NT: the packed A is loaded with the streaming hint (it is read once).  XNT: so are the x rows
 // (for inputs too large to stay in a cache until anyone reads them again).
 //
-// LINES (ranks 8 and 16, where a step covers 128 K values = 256 bytes of a row): the x rows are
-// fetched as whole cache lines - instruction q reads rows 4q .. 4q+3 of the tile, 256 contiguous
-// bytes each - and turned into the MFMA operand layout (16 rows on the lane index, 64 bytes of a
-// row per operand) through 4 KiB of LDS owned by the wave, the 16-byte column of a row stored
-// at column (col xor row) so that the row-wise writes and the operand-wise reads both touch every
-// bank once.  Fetched in the operand layout directly, an instruction reads 16 rows x 64 bytes:
-// half a line per row, and the other half by the next instruction.
+// LINES (ranks 8 to 32, where a step covers 128 or 64 K values = 256 or 128 bytes of a row): the x rows
+// are fetched as whole cache lines - an instruction reads 4 rows x 256 or 8 rows x 128 contiguous bytes -
+// and turned into the MFMA operand layout (16 rows on the lane index, 64 bytes of a row per operand)
+// through 4 or 2 KiB of LDS owned by the wave, the 16-byte column of a row stored at another column so that
+// the row-wise writes and the operand-wise reads both touch every bank once.  Fetched in the operand
+// layout directly, an instruction reads 16 rows x 64 bytes: half a line per row, and the other half by
+// the next instruction.
 template <int R, int NPROJ, bool NT, bool XNT = false, bool LINES = false>
 struct ShrinkWave {
     static constexpr int NB = R >= 16 ? R / 16 : 1;            // weight tiles per K unit
@@ -35,13 +35,16 @@ struct ShrinkWave {
     static constexpr int NACC = R == 8 ? 2 : NB;               // accumulators per projection
     static constexpr int KU = R == 8 ? 64 : 32;                // K values per unit
     static constexpr int KB = shrink_wave_units(R);            // units per step
-    static_assert(!LINES || KB * KU == 128, "whole-line rows: a step is 256 bytes of a row");
+    static constexpr int PPR = KB * KU / 8;                    // 16-byte pieces of a row in a step
+    static constexpr int RPI = 64 / PPR;                       // LINES: rows per instruction
+    static constexpr int NQ = 16 / RPI;                        // LINES: instructions per step
+    static_assert(!LINES || PPR == 16 || PPR == 8, "whole-line rows: a step is 256 or 128 bytes of a row");
 
     int lane, g, i16, h_in;
     const uint16_t *Ap[NPROJ];
     const uint16_t *xp;      // this lane's x row (a valid row even if the lane's row is not)
-    const uint16_t *xq[LINES ? 4 : 1];   // LINES: rows 4q + lane / 16 of the tile (valid rows likewise)
-    u32x4 *xt;               // LINES: the wave's 4 KiB of LDS
+    const uint16_t *xq[LINES ? NQ : 1];  // LINES: rows RPI * q + lane / PPR of the tile (valid rows likewise)
+    u32x4 *xt;               // LINES: the wave's LDS, NQ KiB
     bool row_ok;
     f32x4 acc[NPROJ][NACC];
 
@@ -78,12 +81,12 @@ struct ShrinkWave {
             }
         }
         if constexpr (LINES) {
-            // lane (g, i16) of instruction q: row 4q + g, K values kb0 * KU + 8 * i16 .. + 7; what
-            // lies beyond the range or the row is replaced by zeros after the transposition
-            const int c = kb0 * KU + i16 * 8;
-            const bool ok = kb0 + i16 / (KU / 8) < kb_end && c < h_in;
+            // lane of instruction q: row RPI * q + lane / PPR, K values kb0 * KU + 8 * (lane % PPR) .. + 7;
+            // what lies beyond the range or the row is replaced by zeros after the transposition
+            const int piece = lane % PPR, c = kb0 * KU + piece * 8;
+            const bool ok = kb0 + piece / (KU / 8) < kb_end && c < h_in;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) (&s.x[0][0])[q] = ld16<XNT>(xq[q] + (ok ? c : 0));
+            for (int q = 0; q < NQ; ++q) (&s.x[0][0])[q] = ld16<XNT>(xq[q] + (ok ? c : 0));
         }
     }
 
@@ -92,18 +95,15 @@ struct ShrinkWave {
     __device__ inline void to_operands(int kb0, int kb_end, Step &s) const
     {
         const u32x4 zero4 = {0u, 0u, 0u, 0u};
+        auto at = [](int row, int piece) { return row * PPR + (piece ^ (row / (16 / PPR))); };
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int row = 4 * q + g;
-            xt[row * 16 + (i16 ^ row)] = (&s.x[0][0])[q];
-        }
+        for (int q = 0; q < NQ; ++q) xt[at(RPI * q + lane / PPR, lane % PPR)] = (&s.x[0][0])[q];
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int u = 0; u < KB; ++u)
 #pragma unroll
             for (int h = 0; h < XN; ++h) {
-                const int piece = (u * KU + h * 32) / 8 + g;
-                const u32x4 t = xt[i16 * 16 + (piece ^ i16)];
+                const u32x4 t = xt[at(i16, (u * KU + h * 32) / 8 + g)];
                 const bool ok = kb0 + u < kb_end && row_ok && (kb0 + u) * KU + h * 32 + g * 8 < h_in;
                 s.x[u][h] = ok ? t : zero4;
             }

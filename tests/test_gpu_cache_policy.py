@@ -188,3 +188,36 @@ def test_streamed_inputs_at_a_ragged_width(rank, n_proj):
                     f"streamed ragged inputs r{rank}/{p.name}")
     del dp, db
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64])
+@pytest.mark.parametrize("h_in,n_proj,tokens", [(8, 1, 40), (64, 2, 33), (72, 3, 70), (200, 1, 5), (1032, 2, 120), (2184, 3, 60)])
+def test_streamed_inputs_at_the_edges_of_a_step(rank, h_in, n_proj, tokens):
+    """Inputs shorter than one step of a wave (64 or 128 values), of a whole number of steps and ragged,
+    with and without a gather, tiles of 1 to 16 rows: streamed inputs (at ranks 8 to 32 as whole cache
+    lines through LDS) give the bits of the plain loads."""
+    projs = tuple(W.Proj(f"p{j}", h_in, 136 + 64 * j, "x") for j in range(n_proj))
+    w = W.Workload("t", "dense", 5, 1, 1, rank, projs, tokens, "zipf", 1.0)
+    b = W.make_batch(w, 31, y_mode="normal", no_adapter_frac=0.05)
+    dp, db = DevicePool(W.make_weights(w, 31, bank_elems=1 << 20), b.scale), DeviceBatch(b)
+    x, ws = db.inputs["x"], LayerRunner(dp, db).v
+    L.lora_build_segments(dp.pool, db.adapter_id, None, db.P, db.seg)
+    src = to_dev(np.random.default_rng(3).integers(0, tokens, tokens).astype(np.int32))
+    for gather in (None, src):
+        out = {}
+        for policy in (L.LORA_ACT_RESIDENT, L.LORA_ACT_STREAMING):
+            L.lora_pool_set_activation_policy(dp.pool, policy)
+            for j in range(n_proj):
+                v = torch.full((ws.numel(),), float("nan"), device="cuda")
+                L.lora_shrink(dp.pool, 0, j, x, h_in, gather, db.seg, v)
+                out.setdefault(policy, []).append(v)
+            db.reset_y()
+            ys = [db.y[p.name] for p in projs]
+            L.lora_apply_group(dp.pool, 0, 0, x, h_in, gather, db.seg, ys, [y.shape[1] for y in ys], ws)
+            out[policy] += [y.clone() for y in ys]
+        for a, c in zip(out[L.LORA_ACT_RESIDENT], out[L.LORA_ACT_STREAMING]):
+            assert torch.equal(torch.nan_to_num(a.float(), nan=1e30), torch.nan_to_num(c.float(), nan=1e30))
+        if gather is None:
+            for j, p in enumerate(projs):
+                check_accumulate(bits_from_dev(out[L.LORA_ACT_STREAMING][n_proj + j]), oracle_projection(b, dp.ws, 0, j),
+                                 f"streamed steps r{rank} {h_in}")

@@ -15,14 +15,17 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # rank, h_in, widths, adapters, tokens
-    (16, 4096, (392,), 64, 1024),            # eight rows per tile of the bound: four K parts of 32 blocks; 8 MiB streamed
-    (16, 4096, (392,), 64, 1023),            # just below the streaming limit
+    (16, 4096, (392,), 64, 1024),            # eight rows per tile of the bound: four K parts of 32 blocks
+    (16, 4096, (392,), 64, 1023),            # one row fewer
     (16, 4096, (392, 136), 64, 300),         # short tiles: eight parts
     (16, 1536, (1032,), 500, 2100),          # too few rows per tile for the coarser split
     (16, 14336, (264,), 24, 700),            # parts of more than two rounds
     (16, 2600, (264,), 100, 1500),           # ragged K, one and a half rounds
-    (8, 4160, (520,), 40, 1100),             # rank 8: 64 K values per block, 8.7 MiB
-    (32, 4096, (392,), 64, 2048),            # 16 MiB: the high ranks' streaming limit
+    (8, 4160, (520,), 40, 1100),             # rank 8: 64 K values per block
+    (32, 4096, (392,), 64, 2048),            # 16 MiB: the streaming limit of ranks 8 to 32, where the batch is sorted first
+    (16, 4096, (392,), 300, 2048),           # the same with too many keys to be sorted inside the shrink
+    (16, 4096, (392,), 300, 2047),           # just below the limit
+    (64, 16384, (264,), 300, 2048),          # 64 MiB: the streaming limit of rank 64
     (64, 4096, (1032,), 40, 1900),           # rank 64: one step in flight, more workgroups
     (64, 1032, (392, 264, 136), 3, 900),     # tall tiles
 ]
