@@ -209,8 +209,12 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
         current = int(torch.cuda.current_stream().cuda_stream) or None
-        if _pycall is not None:      # the device is initialised now: from here on without Stream objects
-            _pycall.use_current_stream(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        # the device is initialised now: from here on without Stream objects, if this torch has the two
+        # calls behind torch.cuda.current_stream() under the names they have had so far
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if _pycall is not None and device is not None and raw is not None:
+            _pycall.use_current_stream(device, raw)
         return current
     if isinstance(stream, int):
         return stream or None

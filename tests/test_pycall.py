@@ -84,3 +84,22 @@ def test_nine_outputs_are_refused_by_the_library_not_written_past():
     with pytest.raises(L.LoraError) as e:
         L.lora_build_apply_group(None, 0, 0, x, 8, None, x, None, 4, seg, [x] * 4000, [8] * 4000, ws, stream=0)
     assert e.value.status == -5
+
+
+def test_current_stream_without_torchs_private_calls(monkeypatch):
+    """A torch that has renamed the calls behind torch.cuda.current_stream(): the handle comes from the
+    Stream object, as before there was a short way."""
+    import torch
+    from paper_2604_07173_amd import binding
+
+    class Current:
+        cuda_stream = 0x77
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Current())
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name)
+    L.load_library()
+    assert binding._stream(None) == 0x77
+    with pytest.raises(L.LoraError) as e:
+        L.lora_pool_load_adapter_layer(None, 0, 0, Buffer(64))
+    assert e.value.status == -5
