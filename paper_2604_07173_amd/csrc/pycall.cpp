@@ -95,26 +95,24 @@ bool pool_of(PyObject *v, lora_pool *&out)         // a Pool, a raw handle (int 
     return true;
 }
 
-// the lora_segments inside a Segments object (a ctypes structure, reached through the buffer protocol);
-// the object outlives the call, which holds a reference to it
-bool segments_of(PyObject *v, lora_segments *&out)
+struct Held {                                       // a reference for as long as a call runs
+    PyObject *obj = nullptr;
+    ~Held() { Py_XDECREF(obj); }
+};
+
+// the lora_segments inside a Segments object (a ctypes structure, reached through the buffer protocol).
+// `keep` holds the structure until the call is over: the object may hand out another one meanwhile
+bool segments_of(PyObject *v, lora_segments *&out, Held &keep)
 {
-    PyObject *c = PyObject_GetAttr(v, s_c);
-    if (!c) return false;
+    keep.obj = PyObject_GetAttr(v, s_c);
+    if (!keep.obj) return false;
     Py_buffer view;
-    const bool got = PyObject_GetBuffer(c, &view, PyBUF_WRITABLE) == 0;
-    if (got) {
-        out = static_cast<lora_segments *>(view.buf);
-        const bool fits = view.len >= (Py_ssize_t)sizeof(lora_segments);
-        PyBuffer_Release(&view);
-        if (!fits) {
-            PyErr_SetString(PyExc_TypeError, "not a lora_segments structure");
-            Py_DECREF(c);
-            return false;
-        }
-    }
-    Py_DECREF(c);
-    return got;
+    if (PyObject_GetBuffer(keep.obj, &view, PyBUF_WRITABLE) != 0) return false;
+    out = static_cast<lora_segments *>(view.buf);
+    const bool fits = view.len >= (Py_ssize_t)sizeof(lora_segments);
+    PyBuffer_Release(&view);
+    if (!fits) PyErr_SetString(PyExc_TypeError, "not a lora_segments structure");
+    return fits;
 }
 
 bool bytes_of(PyObject *tensor, size_t &out)
@@ -231,8 +229,9 @@ LORA_PY(build_segments)
     int P;
     size_t sbytes;
     lora_segments *seg;
+    Held seg_ref;
     if (!n_args(n, 6) || !pool_of(a[0], pool) || !addr(a[1], aid) || !addr(a[2], eid) || !to_int(a[3], P) ||
-        !segments_of(a[4], seg) || !seg_ws_of(a[4], sws, sbytes) || !stream_of(a[5], st))
+        !segments_of(a[4], seg, seg_ref) || !seg_ws_of(a[4], sws, sbytes) || !stream_of(a[5], st))
         return nullptr;
     LORA_CALL(lib.build_segments(pool, (const int32_t *)aid, (const int32_t *)eid, P, seg, sws, sbytes, st));
 }
@@ -245,8 +244,9 @@ LORA_PY(apply)
     void *x, *src, *y, *v, *st;
     int64_t ldx, ldy;
     lora_segments *seg;
+    Held seg_ref;
     if (!n_args(n, 12) || !pool_of(a[0], pool) || !to_int(a[1], layer) || !to_int(a[2], proj) || !addr(a[3], x) ||
-        !to_i64(a[4], ldx) || !addr(a[5], src) || !segments_of(a[6], seg) || !addr(a[7], y) || !to_i64(a[8], ldy) ||
+        !to_i64(a[4], ldx) || !addr(a[5], src) || !segments_of(a[6], seg, seg_ref) || !addr(a[7], y) || !to_i64(a[8], ldy) ||
         !addr(a[9], v) || !to_int(a[10], dt) || !stream_of(a[11], st))
         return nullptr;
     LORA_CALL(lib.apply(pool, layer, proj, x, ldx, (const int32_t *)src, seg, y, ldy, dt, (float *)v, st));
@@ -261,9 +261,10 @@ LORA_PY(apply_group)
     int64_t ldx;
     size_t bytes;
     lora_segments *seg;
+    Held seg_ref;
     Outputs o;
     if (!n_args(n, 12) || !pool_of(a[0], pool) || !to_int(a[1], layer) || !to_int(a[2], proj0) || !addr(a[3], x) ||
-        !to_i64(a[4], ldx) || !addr(a[5], src) || !segments_of(a[6], seg) || !outputs_of(a[7], a[8], o) ||
+        !to_i64(a[4], ldx) || !addr(a[5], src) || !segments_of(a[6], seg, seg_ref) || !outputs_of(a[7], a[8], o) ||
         !ws_of(a[9], Py_None, ws, bytes) || !to_int(a[10], dt) || !stream_of(a[11], st))
         return nullptr;
     LORA_CALL(lib.apply_group(pool, layer, proj0, o.n, x, ldx, (const int32_t *)src, seg, o.y, o.ld, dt, ws, bytes, st));
@@ -278,10 +279,11 @@ LORA_PY(build_apply_group)
     int64_t ldx;
     size_t sbytes, bytes;
     lora_segments *seg;
+    Held seg_ref;
     Outputs o;
     if (!n_args(n, 15) || !pool_of(a[0], pool) || !to_int(a[1], layer) || !to_int(a[2], proj0) || !addr(a[3], x) ||
         !to_i64(a[4], ldx) || !addr(a[5], src) || !addr(a[6], aid) || !addr(a[7], eid) || !to_int(a[8], P) ||
-        !segments_of(a[9], seg) || !seg_ws_of(a[9], sws, sbytes) || !outputs_of(a[10], a[11], o) ||
+        !segments_of(a[9], seg, seg_ref) || !seg_ws_of(a[9], sws, sbytes) || !outputs_of(a[10], a[11], o) ||
         !ws_of(a[12], Py_None, ws, bytes) || !to_int(a[13], dt) || !stream_of(a[14], st))
         return nullptr;
     LORA_CALL(lib.build_apply_group(pool, layer, proj0, o.n, x, ldx, (const int32_t *)src, (const int32_t *)aid,
@@ -297,8 +299,9 @@ LORA_PY(moe_apply)
     int64_t ld, ldy;
     size_t bytes;
     lora_segments *seg;
+    Held seg_ref;
     if (!n_args(n, 13) || !pool_of(a[0], pool) || !to_int(a[1], layer) || !to_int(a[2], which) || !addr(a[3], in) ||
-        !to_i64(a[4], ld) || !addr(a[5], tok) || !segments_of(a[6], seg) || !addr(a[7], y0) || !addr(a[8], y1) ||
+        !to_i64(a[4], ld) || !addr(a[5], tok) || !segments_of(a[6], seg, seg_ref) || !addr(a[7], y0) || !addr(a[8], y1) ||
         !to_i64(a[9], ldy) || !ws_of(a[10], a[11], ws, bytes) || !stream_of(a[12], st))
         return nullptr;
     LORA_CALL(lib.moe_apply(pool, layer, which, in, ld, (const int32_t *)tok, seg, y0, y1, ldy, ws, bytes, st));
@@ -313,9 +316,10 @@ LORA_PY(moe_build_apply)
     int64_t ld, ldy;
     size_t sbytes, bytes;
     lora_segments *seg;
+    Held seg_ref;
     if (!n_args(n, 16) || !pool_of(a[0], pool) || !to_int(a[1], layer) || !to_int(a[2], which) || !addr(a[3], in) ||
         !to_i64(a[4], ld) || !addr(a[5], tok) || !addr(a[6], aid) || !addr(a[7], eid) || !to_int(a[8], P) ||
-        !segments_of(a[9], seg) || !seg_ws_of(a[9], sws, sbytes) || !addr(a[10], y0) || !addr(a[11], y1) ||
+        !segments_of(a[9], seg, seg_ref) || !seg_ws_of(a[9], sws, sbytes) || !addr(a[10], y0) || !addr(a[11], y1) ||
         !to_i64(a[12], ldy) || !ws_of(a[13], a[14], ws, bytes) || !stream_of(a[15], st))
         return nullptr;
     LORA_CALL(lib.moe_build_apply(pool, layer, which, in, ld, (const int32_t *)tok, (const int32_t *)aid,
@@ -331,8 +335,9 @@ LORA_PY(moe_down_combine)
     int64_t ld, ldy;
     size_t bytes;
     lora_segments *seg;
+    Held seg_ref;
     if (!n_args(n, 14) || !pool_of(a[0], pool) || !to_int(a[1], layer) || !addr(a[2], in) || !to_i64(a[3], ld) ||
-        !addr(a[4], aid) || !addr(a[5], eid) || !segments_of(a[6], seg) || !addr(a[7], w) || !to_int(a[8], top_k) ||
+        !addr(a[4], aid) || !addr(a[5], eid) || !segments_of(a[6], seg, seg_ref) || !addr(a[7], w) || !to_int(a[8], top_k) ||
         !addr(a[9], y) || !to_i64(a[10], ldy) || !ws_of(a[11], a[12], ws, bytes) || !stream_of(a[13], st))
         return nullptr;
     LORA_CALL(lib.moe_down_combine(pool, layer, in, ld, (const int32_t *)aid, (const int32_t *)eid, seg,

@@ -1,6 +1,10 @@
-"""The layer calls' argument conversion (csrc/pycall.cpp) against the same calls through ctypes: the
-library refuses both with the same status before any device work, whatever the argument forms."""
+"""The layer calls' argument conversion (csrc/pycall.cpp): what the library is handed, argument by
+argument, against the same calls through ctypes (both reach host functions that record it), and what is
+refused before any device work, whatever the argument forms."""
+import contextlib
 import ctypes as C
+import gc
+import weakref
 
 import numpy as np
 import pytest
@@ -77,6 +81,117 @@ def test_argument_forms_and_mistakes():
 
     with pytest.raises(L.LoraError):
         group([x], [8], stream=Stream())
+
+
+ENTRIES = ("lora_build_segments", "lora_apply", "lora_apply_group", "lora_build_apply_group", "lora_moe_apply",
+           "lora_moe_build_apply", "lora_moe_down_combine", "lora_pool_load_adapter_layer")
+
+
+@contextlib.contextmanager
+def recorded():
+    """The extension module bound to host functions that note their arguments; yields (calls, ctypes
+    functions with the library's prototypes at the same addresses)."""
+    from paper_2604_07173_amd import binding
+    lib = L.load_library()
+    calls, keep, addresses, through_ctypes = [], [], {}, {}
+    for name in ENTRIES:
+        types = getattr(lib, name).argtypes
+        group = "apply_group" in name
+
+        def note(*args, name=name, types=types, group=group):
+            got = []
+            for t, v in zip(types, args):
+                if t is C.POINTER(binding._Segments):
+                    v = (C.addressof(v.contents), v.contents.P, v.contents.n_keys)
+                elif t in (C.POINTER(C.c_void_p), C.POINTER(C.c_int64)):
+                    v = [v[i] for i in range(min(args[3], 8))]
+                got.append(v)
+            calls.append((name, got))
+            return 0
+
+        proto = C.CFUNCTYPE(C.c_int, *types)
+        keep.append(proto(note))
+        addresses[name] = C.cast(keep[-1], C.c_void_p).value
+        through_ctypes[name] = proto(addresses[name])
+    binding._calls().bind(addresses, binding._stream)
+    try:
+        yield calls, through_ctypes
+    finally:
+        binding._calls().bind({n: C.cast(getattr(lib, n), C.c_void_p).value for n in binding.EXPORTED_SYMBOLS},
+                              binding._stream)
+
+
+def test_every_argument_arrives_where_ctypes_puts_it():
+    b = [Buffer(1000 + i, 0x7F0000000000 + 4096 * i) for i in range(12)]         # addresses beyond 32 bits
+    a = [v.address for v in b]
+    big, seg, pool = 1 << 40, Seg(), 0x5500_0000_1000
+    ref, sws = C.byref(seg.c), (4096, 512)
+    two = (C.c_void_p * 2)(a[3], a[4]), (C.c_int64 * 2)(big, 24)
+    f32 = L.LORA_DTYPE_F32
+    with recorded() as (calls, ct):
+        pairs = [
+            (lambda: L.lora_build_segments(pool, b[0], b[1], 7, seg, stream=9),
+             lambda: ct["lora_build_segments"](pool, a[0], a[1], 7, ref, *sws, 9)),
+            (lambda: L.lora_apply(pool, 2, 3, b[0], big, b[1], seg, b[2], 16, b[3], f32, stream=9),
+             lambda: ct["lora_apply"](pool, 2, 3, a[0], big, a[1], ref, a[2], 16, f32, a[3], 9)),
+            (lambda: L.lora_apply_group(pool, 2, 3, b[0], 16, b[1], seg, [b[3], a[4]], (np.int64(big), 24), b[5], f32, 9),
+             lambda: ct["lora_apply_group"](pool, 2, 3, 2, a[0], 16, a[1], ref, *two, f32, a[5], 1005, 9)),
+            (lambda: L.lora_build_apply_group(pool, 2, 3, b[0], 16, b[1], b[6], b[7], 7, seg, (b[3], b[4]), [big, 24], b[5],
+                                              stream=9),
+             lambda: ct["lora_build_apply_group"](pool, 2, 3, 2, a[0], 16, a[1], a[6], a[7], 7, ref, *sws, *two, 0, a[5],
+                                                  1005, 9)),
+            (lambda: L.lora_moe_apply(pool, 2, 1, b[0], 16, b[1], seg, b[2], b[3], big, b[4], 77, stream=9),
+             lambda: ct["lora_moe_apply"](pool, 2, 1, a[0], 16, a[1], ref, a[2], a[3], big, a[4], 77, 9)),
+            (lambda: L.lora_moe_build_apply(pool, 2, 1, b[0], 16, b[1], b[5], b[6], 7, seg, b[2], None, big, b[4], stream=9),
+             lambda: ct["lora_moe_build_apply"](pool, 2, 1, a[0], 16, a[1], a[5], a[6], 7, ref, *sws, a[2], None, big, a[4],
+                                                1004, 9)),
+            (lambda: L.lora_moe_down_combine(pool, 2, b[0], 16, b[1], b[5], seg, b[6], 4, b[2], big, b[4], 78, stream=9),
+             lambda: ct["lora_moe_down_combine"](pool, 2, a[0], 16, a[1], a[5], ref, a[6], 4, a[2], big, a[4], 78, 9)),
+            (lambda: L.lora_pool_load_adapter_layer(pool, 5, 2, b[0], stream=9),
+             lambda: ct["lora_pool_load_adapter_layer"](pool, 5, 2, a[0], 9)),
+        ]
+        for short, long_way in pairs:
+            short()
+            assert long_way() == 0
+            (name, got), (name2, want) = calls[-2:]
+            assert name == name2 and got == want, name
+        assert {name for name, _ in calls} == set(ENTRIES)
+
+
+def test_segments_live_as_long_as_the_call():
+    """A Segments object that hands out its structure anew each time: the call's own one is still there,
+    with its contents, while the library runs."""
+    from paper_2604_07173_amd import binding
+    made = []
+
+    class Fresh(Seg):
+        @property
+        def c(self):
+            s = binding._Segments()
+            s.P, s.n_keys = 1234, 56
+            made.append(weakref.ref(s))
+            return s
+
+        @c.setter
+        def c(self, value):
+            pass
+
+    lib, alive = L.load_library(), []
+    types = lib.lora_build_segments.argtypes
+
+    def look(*args):
+        gc.collect()
+        alive.append(made[-1]() is not None)
+        return 0
+
+    stub = C.CFUNCTYPE(C.c_int, *types)(look)
+    addresses = {n: C.cast(getattr(lib, n), C.c_void_p).value for n in binding.EXPORTED_SYMBOLS}
+    try:
+        binding._calls().bind(dict(addresses, lora_build_segments=C.cast(stub, C.c_void_p).value), binding._stream)
+        L.lora_build_segments(None, 4096, None, 4, Fresh(), stream=0)
+    finally:
+        binding._calls().bind(addresses, binding._stream)
+    assert alive == [True] and made[-1]() is None
 
 
 def test_nine_outputs_are_refused_by_the_library_not_written_past():
