@@ -256,9 +256,9 @@ def test_long_segment_kernels_at_ragged_widths(rank, h_in, h_out, y_mode, monkey
                                                      (64, 8, 2047, 16), (64, 8, 2048, 32), (16, 64, 4096, 16),
                                                      (32, 300, 8192, 16)])
 def test_kernel_family_switch_for_long_decode_batches(rank, n, tokens, tile_rows):
-    """The 32-row-tile kernels are taken from rows x rank = 2^17 on (8192 rows at rank 16, 2048 at
-    rank 64) if there are at least 32 rows per key: both sides of the limits, against the oracle
-    (all rows)."""
+    """Tiles have 32 rows from rows x rank = 2^17 on (8192 rows at rank 16, 2048 at rank 64) if there
+    are at least 32 rows per key: both sides of the limits, against the oracle (all rows).  Which kernels
+    such a batch runs on is another rule: see test_gpu_halves.py."""
     w = W.Workload("t", "dense", n, 1, 1, rank, (W.Proj("p", 264, 136, "x"),), tokens, "zipf", 0.6)
     b, ws, got, (dp, db, run) = run_dense(w, 52, "zero", drop=0.02)
     assert db.seg.c.tile_rows == tile_rows

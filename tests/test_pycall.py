@@ -201,6 +201,29 @@ def test_nine_outputs_are_refused_by_the_library_not_written_past():
     assert e.value.status == -5
 
 
+@pytest.mark.gpu
+def test_too_many_outputs_are_refused_for_a_registered_pool():
+    """More outputs than a group may have, up to and beyond the module's own table of them: refused for
+    their number, by both group calls, before anything is enqueued."""
+    import torch
+    desc = L.PoolDesc(2, 1, 1, [(8, 8)] * 8, 16)
+    slab = torch.zeros(L.lora_pool_bytes(desc), dtype=torch.uint8, device="cuda")
+    pool = L.lora_register_pool(desc, slab)
+    seg, P = L.Segments(4), 4
+    aid = torch.zeros(P, dtype=torch.int32, device="cuda")
+    x, y = torch.zeros(P, 8, dtype=torch.bfloat16, device="cuda"), torch.ones(P, 8, dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    L.lora_build_segments(pool, aid, None, P, seg)
+    for n in (0, 4, 8, 9, 4000):
+        for call in (lambda: L.lora_apply_group(pool, 0, 0, x, 8, None, seg, [y] * n, [8] * n, ws),
+                     lambda: L.lora_build_apply_group(pool, 0, 0, x, 8, None, aid, None, P, seg, [y] * n, [8] * n, ws)):
+            with pytest.raises(L.LoraError) as e:
+                call()
+            assert e.value.status == -1, n
+    torch.cuda.synchronize()
+    assert bool((y == 1).all())
+
+
 def test_current_stream_without_torchs_private_calls(monkeypatch):
     """A torch that has renamed the calls behind torch.cuda.current_stream(): the handle comes from the
     Stream object, as before there was a short way."""
