@@ -146,8 +146,9 @@ def launches_per_step(w, dp, db, run, combine=False):
         return None
     groups = [(0, 2), (2, 1)] if w.kind == "moe" else run.groups
     if combine:
+        # the long-segment kernels (more than two launches a group) also build images and clear the pair rows
         return (L.lora_segments_launches(dp.pool, db.P) + L.lora_group_launches(dp.pool, 0, 2, db.P, db.seg) + 3
-                + (2 if db.seg.c.tile_rows > 16 else 0))
+                + (2 if L.lora_group_launches(dp.pool, 2, 1, db.P, db.seg) > 2 else 0))
     j0, c0 = groups[0]       # the first application of the call builds the segments
     return L.lora_build_apply_launches(dp.pool, j0, c0, db.P) + sum(L.lora_group_launches(dp.pool, j, c, db.P, db.seg)
                                                                      for j, c in groups[1:])
