@@ -188,14 +188,18 @@ struct ShrinkParams {
     int kb_per_part;         // decode kernel
     int rank;
     int grid;
-    int by_tiles;            // long-segment kernel: work items are groups of four tiles, else blocks of one segment
-    int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
+    union {
+        int tile_halves;     // decode kernel: the tiles have up to 32 rows and are taken in halves
+        int by_tiles;        // long-segment kernel: work items are groups of four tiles, else blocks of one segment
+    };
     int wave_per_tile;       // decode kernel: every wave takes a whole tile (no K split across waves)
     int build;               // decode kernel: the segments are built inside the launch, from `seg`
     int x_stream;            // decode kernel, K-split form: x rows loaded with the streaming hint (ranks 8, 16: as whole lines)
     SegParams seg;
 };
 
+// (the arguments of a launch are read by the GPU from host memory: 16 bytes more in these two structures
+// cost a small call 0.1 us per launch, hence the unions)
 struct ExpandParams {
     const Unit *units;
     int n_proj;
@@ -203,7 +207,6 @@ struct ExpandParams {
     int n_fused;             // 1 .. kMaxFused consecutive projections; their widths may differ
     const float *v[kMaxFused];
     int n_parts;             // long-segment kernels: the most parts there may be (long_split)
-    int kblocks;             // long-segment kernels: K-blocks of the input
     int P;
     const int32_t *perm;
     const lora_tile *tiles;
@@ -219,7 +222,10 @@ struct ExpandParams {
     int image_grid;          // long-segment kernel: workgroups of the image launch
     int waves;               // waves per workgroup
     int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
-    int tile_group;          // decode kernel: consecutive wave items walk over this many tiles
+    union {
+        int tile_group;      // decode kernel: consecutive wave items walk over this many tiles
+        int kblocks;         // long-segment kernels: K-blocks of the input
+    };
     int out_f32;
     int overwrite;           // decode kernel, bf16 output: write the update, do not read the rows
     int deep;                // decode kernel: two chunks in flight per wave, else one
