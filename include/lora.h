@@ -175,8 +175,13 @@ int lora_pool_set_adapter(lora_pool *pool, int adapter, int rank, float scale, v
  *   LORA_ACT_STREAMING       for callers whose activations are in HBM only when a call starts
  *       (arrived over a link, or written long ago): output rows are read and written with
  *       streaming hints at every size, and so are input rows that every pair reads for itself.
- * Results are bit-identical under all three; only the decode kernels (tiles of at most 16 rows)
- * look at the policy, the long-segment kernels always stream their outputs.  Host state only:
+ * Results are bit-identical under all three.  Only the decode kernels look at the policy (batches with
+ * tiles of at most 16 rows, and batches of rank 16 with 32-row tiles that run on them: those below
+ * 12288 rows or below 128 rows per key); the long-segment kernels always stream their outputs.  Some
+ * forms of the decode kernels have no streamed inputs: shrink and expand as one launch (nor streamed
+ * outputs), the shrink that sorts the batch itself (lora_build_apply_group, lora_moe_build_apply: up to
+ * 2048 rows over up to 256 keys) and the one for thousands of tiles over inputs of at most 4096.
+ * Host state only:
  * takes effect from the next call on, must not race with calls on the same pool.  Errors:
  * LORA_ERR_NOT_REGISTERED, LORA_ERR_INVALID_ARG (unknown policy).
  */
@@ -273,7 +278,11 @@ int lora_build_segments(const lora_pool *pool, const int32_t *adapter_id,
  *   must be gathered.  x: device bf16, row stride ldx elements.
  *   v: device workspace of lora_v_bytes(pool, proj, P) bytes; it holds per-K-slice fp32
  *   partial sums in sorted-row order (and room that lora_expand uses for itself) and is
- *   meant only to be passed to lora_expand with the same pool, layer, proj and segments.
+ *   meant only to be passed to lora_expand with the same pool, layer, proj and segments.  The
+ *   size does not grow steadily with P (fewer rows may be cut into more K slices; the other workspace
+ *   queries follow it): a workspace that serves batches of several sizes has to be the largest over every
+ *   P it is used for, not that of the largest batch.  lora_shrink, lora_expand and lora_apply take no
+ *   size and cannot check it.
  * lora_expand:  y[perm[i]] += scale * v_i * B   (Sec. 2.2: the update is added to the base
  *   output; Fig. 7b: final addition of the two outputs).  y: device, row stride ldy
  *   elements, bf16 (read, add in fp32, round to nearest even, write) or fp32.  Rows that

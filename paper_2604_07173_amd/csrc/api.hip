@@ -288,7 +288,8 @@ KSplit ksplit_decode(const lora_pool *p, int proj, int P)
     // nor at ranks 32 and 64, where a part is two and four times the bytes (1024 rows: 171
     // against 178 us, 280 against 288), nor from two rounds on (448 K-blocks in eight parts of 56
     // against seven of 64: Mixtral shapes, 2048 tokens, 255 against 263 us).  The workspace keeps
-    // room for the finer split, so that a buffer sized for a batch also takes every smaller one.
+    // room for the finer split: its size is what it was before this rule.  (It does not grow steadily with
+    // P: fewer rows may be cut into more parts.)
     static const int full = tune_int("LORA_DEC_SHRINK_FULL", 768, 1, 1 << 20);
     const int round = 4 * shrink_wave_units(p->d.rank);
     if (p->d.rank <= 16 && P >= 4 * tub && tub * k.ws_parts >= full) {
@@ -457,7 +458,7 @@ int do_shrink(const lora_pool *pool, int layer, const Group &g, const void *x, i
             // every workgroup sorts the batch before its first item: fewer, longer-lived workgroups
             static const int per_cu = tune_int("LORA_INLINE_BUILD_WGS_PER_CU", 4, 1, 64);
             sp.build = 1;
-            sp.x_stream = 0;                      // at most 2048 rows: nothing to stream
+            sp.x_stream = 0;                      // the kernel that sorts has no streamed form: inputs stay cacheable
             sp.seg = *build;
             sp.grid = (int)std::min<int64_t>(sp.grid, (int64_t)cu_count() * per_cu);
         }

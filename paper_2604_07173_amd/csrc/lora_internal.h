@@ -35,7 +35,7 @@ constexpr int kFusedMaxTiles = 64;     // largest batch, as the host's upper bou
 // Work items x rank x inputs, that is half the bytes of A that all items together read.  A workgroup
 // fetches the whole A of its item at what one CU can pull, so one launch loses to two as that grows
 // (whole call in us, one launch / two; 4096 -> 4096, rank 16: 1 row 6.7 / 7.7, 8 rows, 2.1 M: 7.4 /
-// 8.4, 24 rows, 6.5 M: 8.8 / 8.6; rank 8, 24 rows, 3.3 M: 7.1 / 8.5; rank 64, 8 rows, 8.4 M: 16.2 /
+// 8.4, 24 rows, 6.3 M: 8.8 / 8.6; rank 8, 24 rows, 3.1 M: 7.1 / 8.5; rank 64, 8 rows, 8.4 M: 16.2 /
 // 10.7; query/key/value of the Llama shapes, 8 rows, 3.1 M: two launches win by 2 us).
 constexpr int64_t kFusedMaxWork = 21ll << 17;      // twice that at rank 8, whose A is half the bytes of rank 16
 // Cache hints of the activation streams of the decode kernels, measured on MI355X.  Input rows that

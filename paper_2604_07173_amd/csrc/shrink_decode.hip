@@ -7,8 +7,8 @@
 //  * wave per tile: every wave takes a whole tile over the whole K range, no LDS, no barrier.
 //    For batches with thousands of small tiles and short inputs (fine-grained MoE).
 // In both a wave streams its slice of the packed A (and of the second fused projection's A)
-// with 16-byte loads that are contiguous per wave, two steps in flight (the loads of step
-// s+1 are issued before the MFMAs of step s; all loads are unconditional so the loop is
+// with 16-byte loads that are contiguous per wave, two steps in flight, one at rank 64 (the loads of
+// step s+1 are issued before the MFMAs of step s; all loads are unconditional so the loop is
 // branch-free and the hardware counters keep them outstanding), and multiplies it with the
 // tile's gathered x rows.  The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and
 // the rows on the N side, so a lane ends up with four consecutive rank entries of one row.

@@ -4,7 +4,7 @@
 // gathered x rows of one tile.
 //
 // A wave streams its slice of the packed A with 16-byte loads that are contiguous per wave, two
-// steps in flight (the loads of step s+1 are issued before the MFMAs of step s; all loads are
+// steps in flight, one at rank 64 (the loads of step s+1 are issued before the MFMAs of step s; all loads are
 // unconditional so the loop is branch-free and the hardware counters keep them outstanding).
 // The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and the rows on the N side, so a
 // lane ends up with four consecutive rank entries of one row.

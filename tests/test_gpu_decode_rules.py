@@ -63,3 +63,23 @@ def test_rules_of_the_decode_kernels(rank, h_in, widths, n, tokens):
     got = y.cpu().numpy()[rows].astype(np.float64)
     # fp32 accumulation over K and the two-part bf16 operand: 1e-5 of the result's norm
     assert np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want)
+
+
+def test_a_smaller_batch_may_need_a_larger_workspace():
+    """1327 rows over 64 adapters at rank 64 are cut into more K parts than 1328: the size query says so,
+    and a call that is handed the larger batch's workspace is refused, not run past its end."""
+    desc = L.PoolDesc(64, 1, 1, [(4096, 8)], 64)
+    slab = torch.zeros(L.lora_pool_bytes(desc), dtype=torch.uint8, device="cuda")
+    pool = L.lora_register_pool(desc, slab)
+    P = 1327
+    small, large = L.lora_group_ws_bytes(pool, 0, 1, P), L.lora_group_ws_bytes(pool, 0, 1, P + 1)
+    assert small > large
+    seg, aid = L.Segments(P), torch.zeros(P, dtype=torch.int32, device="cuda")
+    x, y = torch.zeros(P, 4096, dtype=torch.bfloat16, device="cuda"), torch.ones(P, 8, dtype=torch.bfloat16, device="cuda")
+    L.lora_build_segments(pool, aid, None, P, seg)
+    with pytest.raises(L.LoraError) as e:
+        L.lora_apply_group(pool, 0, 0, x, 4096, None, seg, [y], [8], torch.empty(large, dtype=torch.uint8, device="cuda"))
+    assert e.value.status == -4
+    L.lora_apply_group(pool, 0, 0, x, 4096, None, seg, [y], [8], torch.empty(small, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert bool((y == 1).all())
