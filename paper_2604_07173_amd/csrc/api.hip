@@ -419,6 +419,7 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
     sp.P = seg->P;
     sp.h_in = pd.h_in;
     sp.n_parts = ks.n_parts;
+    sp.parts = fast_div(ks.n_parts);
     sp.kb_per_part = ks.kb_per_part;
     sp.rank = pool->d.rank;
     if (!long_kernels(pool, seg->P, seg->tile_rows)) {
@@ -546,38 +547,41 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         // that single-chunk items are needed to occupy the chip
         int cpi = std::max(2, (int)std::lround(item_bytes / chunk_bytes));
         cpi = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(cpi, cpi_max), units / want_items));
-        ep.slice0[0] = 0;
         for (int j = 0; j < g.n; ++j) {
-            ep.v[j] = g.v[j];
-            ep.y[j] = g.y[j];
-            ep.ldy[j] = g.ldy[j];
-            ep.h_out[j] = pool->d.proj[g.proj0 + j].h_out;
-            ep.n_chunks[j] = chunks_of(ep.h_out[j]);
+            ExpandProj &q = ep.proj[j];
+            q.v = g.v[j];
+            q.y = g.y[j];
+            q.ldy = g.ldy[j];
+            q.h_out = pool->d.proj[g.proj0 + j].h_out;
+            q.n_chunks = chunks_of(q.h_out);
             // no empty slice: a row is cut into n_slices pieces of cps = ceil(n_chunks / n_slices)
             // chunks; cps even, because the kernel keeps two chunks in flight with unconditional
             // loads and a piece of odd length costs it one chunk loaded twice
-            const int want = std::max(1, (ep.n_chunks[j] + cpi - 1) / cpi);
-            int cps = (ep.n_chunks[j] + want - 1) / want;
-            if (cpi > 1) cps = std::min(ep.n_chunks[j], (cps + 1) & ~1);     // cpi 1: a small batch, items first
-            ep.cps[j] = cps;
-            ep.n_slices[j] = (ep.n_chunks[j] + cps - 1) / cps;
-            ep.slice0[j + 1] = ep.slice0[j] + ep.n_slices[j];
+            const int want = std::max(1, (q.n_chunks + cpi - 1) / cpi);
+            int cps = (q.n_chunks + want - 1) / want;
+            if (cpi > 1) cps = std::min(q.n_chunks, (cps + 1) & ~1);     // cpi 1: a small batch, items first
+            q.cps = cps;
+            q.slice0 = ep.per_tile;
+            ep.per_tile += (q.n_chunks + cps - 1) / cps;
         }
-        for (int j = g.n; j < kMaxFused; ++j) ep.slice0[j + 1] = ep.slice0[g.n];
+        ep.slice1 = g.n > 1 ? ep.proj[1].slice0 : ep.per_tile;
+        ep.slice2 = g.n > 2 ? ep.proj[2].slice0 : ep.per_tile;
         ep.waves = 4;
         // with many rows per (adapter, expert) a segment spans several tiles: let neighbouring
         // waves take neighbouring tiles, so that they share the segment's B through the L2
-        static const int tile_group = tune_int("LORA_DEC_EXPAND_TILE_GROUP", 0, 0, 4);
+        static const int tile_group = tune_int("LORA_DEC_EXPAND_TILE_GROUP", 0, 0, 4);     // 1, 2 or 4
         const int64_t n_keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
         const bool long_segments = seg->P >= 8 * n_keys;
-        ep.tile_group = tile_group ? tile_group : (long_segments ? 2 : 1);
+        const int group = tile_group ? tile_group : (long_segments ? 2 : 1);
+        ep.group_shift = group / 2;
+        ep.group_items = fast_div(ep.per_tile << ep.group_shift);
         // ... and keep the B of full tiles in the L2 (the other tiles' is read once and streamed):
         // Mixtral shapes, 2048 tokens, 255.2 -> 247.2 us at rank 16, 375 -> 355 at rank 32; llama shapes,
         // 2048 rows of which 1792 share an adapter, 163.5 -> 158.1.  Not for shorter segments:
         // 512 tokens of the Mixtral shapes (four rows per key) 104.3 -> 106.2.  The A of the shrink
         // is streamed at every length (cached: 255 -> 264 us for 2048 tokens).
         ep.share_b = long_segments;
-        const int64_t wave_items = (tub + ep.tile_group - 1) / ep.tile_group * ep.tile_group * ep.slice0[g.n];
+        const int64_t wave_items = (tub + group - 1) / group * group * ep.per_tile;
         // Chunks in flight per wave: two, but one where the launch is a few rounds of the chip's waves
         // long and its tiles are tall (more waves fit then, which shortens the rounds), or where an item is
         // one chunk anyway.  Layer call in us, two / one: llama shapes, 1024 rows 116.3 / 111.5, at rank 64
@@ -605,21 +609,22 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     ep.kblocks = kblocks_of(pool->d.proj[g.proj0].h_in, pool->d.rank);
     ep.proj0 = g.proj0;
     ep.n_fused = g.n;
-    ep.slice0[0] = 0;
     for (int j = 0; j < g.n; ++j) {
-        ep.v[j] = g.v[j];
-        ep.y[j] = g.y[j];
-        ep.ldy[j] = g.ldy[j];
-        ep.h_out[j] = pool->d.proj[g.proj0 + j].h_out;
-        ep.n_chunks[j] = chunks_of(ep.h_out[j]);
-        ep.n_slices[j] = ep.n_chunks[j];
-        ep.slice0[j + 1] = ep.slice0[j] + ep.n_chunks[j];
-        ep.img[j] = reinterpret_cast<char *>(g.v[j]) + parts_bytes(pool, ks.ws_parts, seg->P);
+        ExpandProj &q = ep.proj[j];
+        q.v = g.v[j];
+        q.y = g.y[j];
+        q.ldy = g.ldy[j];
+        q.h_out = pool->d.proj[g.proj0 + j].h_out;
+        q.n_chunks = chunks_of(q.h_out);
+        q.slice0 = ep.per_tile;
+        ep.per_tile += q.n_chunks;
+        q.img = reinterpret_cast<char *>(g.v[j]) + parts_bytes(pool, ks.ws_parts, seg->P);
     }
-    for (int j = g.n; j < kMaxFused; ++j) ep.slice0[j + 1] = ep.slice0[g.n];
+    ep.slice1 = g.n > 1 ? ep.proj[1].slice0 : ep.per_tile;
+    ep.slice2 = g.n > 2 ? ep.proj[2].slice0 : ep.per_tile;
     ep.waves = 4;
     const int64_t groups = (tub + expand_long_group() - 1) / expand_long_group();
-    const int64_t wave_items = groups * ep.slice0[g.n];
+    const int64_t wave_items = groups * ep.per_tile;
     ep.grid = (int)std::min<int64_t>((wave_items + 3) / 4, (int64_t)cu_count() * per_cu);
     ep.image_grid = (int)std::min<int64_t>((tub * 2 * g.n + 3) / 4, (int64_t)cu_count() * 8);
     return LORA_OK;
@@ -654,7 +659,11 @@ bool fused_plan(const lora_pool *pool, const Group &g, const lora_segments *seg,
     if (tub * slice0[g.n] * pool->d.rank * pool->d.proj[g.proj0].h_in > (int64_t)max_work * (pool->d.rank == 8 ? 2 : 1))
         return false;
     if (!sp || !ep) return true;
-    for (int j = 0; j <= kMaxFused; ++j) ep->slice0[j] = slice0[std::min(j, g.n)];
+    for (int j = 0; j < g.n; ++j) ep->proj[j].slice0 = slice0[j];
+    ep->per_tile = slice0[g.n];
+    ep->slice1 = slice0[1];
+    ep->slice2 = slice0[std::min(2, g.n)];
+    ep->group_items = fast_div(ep->per_tile);
     sp->n_parts = 1;
     sp->kb_per_part = kblocks_of(pool->d.proj[g.proj0].h_in, pool->d.rank);
     ep->n_parts = 1;

@@ -71,8 +71,8 @@ __global__ __launch_bounds__(256) void operand_image_kernel(ExpandParams p,
         const float scale = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].scale;
         const int row = (slot & 1) * 16 + (i16 & 3) * 4 + (i16 >> 2);
         const bool valid = row < t.n_rows;
-        const float *vrow = p.v[pj] + (int64_t)(t.row0 + (valid ? row : 0)) * R;
-        LORA_GLOBAL vec *img = (LORA_GLOBAL vec *)p.img[pj] + (int64_t)slot * image_vecs<R>();
+        const float *vrow = p.proj[pj].v + (int64_t)(t.row0 + (valid ? row : 0)) * R;
+        LORA_GLOBAL vec *img = (LORA_GLOBAL vec *)p.proj[pj].img + (int64_t)slot * image_vecs<R>();
         typename Tile::A a;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -199,14 +199,14 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
     const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave), nw = gridDim.x * 4;
     const int n_tiles = counts[2];
     const int n_groups = (n_tiles + kLongGroup - 1) / kLongGroup;
-    const int per_group = p.slice0[p.n_fused];                    // chunks of all projections
+    const int per_group = p.per_tile;                               // chunks of all projections
     const int n_items = n_groups * per_group;
 
     for (int item = gw; item < n_items; item += nw) {
         const int tg = item / per_group;
         const int rem = item - tg * per_group;
-        const int pj = (rem >= p.slice0[1] ? 1 : 0) + (p.n_fused > 2 && rem >= p.slice0[2] ? 1 : 0);
-        const int chunk = rem - p.slice0[pj];
+        const int pj = (rem >= p.slice1 ? 1 : 0) + (rem >= p.slice2 ? 1 : 0);
+        const int chunk = rem - p.proj[pj].slice0;
 
         Wave w;
         w.lane = lane;
@@ -214,10 +214,10 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
         w.i16 = lane & 15;
         w.perm = p.perm;
         const int col = chunk * kColChunk + w.i16 * 8;
-        w.col_ok = col < p.h_out[pj];
-        w.ybase = static_cast<char *>(p.y[pj]) + (int64_t)(w.col_ok ? col : 0) * Wave::ESZ;
-        w.ld_bytes = p.ldy[pj] * Wave::ESZ;
-        w.img = (const LORA_GLOBAL typename Wave::vec *)p.img[pj];
+        w.col_ok = col < p.proj[pj].h_out;
+        w.ybase = static_cast<char *>(p.proj[pj].y) + (int64_t)(w.col_ok ? col : 0) * Wave::ESZ;
+        w.ld_bytes = p.proj[pj].ldy * Wave::ESZ;
+        w.img = (const LORA_GLOBAL typename Wave::vec *)p.proj[pj].img;
 #pragma unroll
         for (int k = 0; k < kLongGroup; ++k) {
             w.live[k] = tg * kLongGroup + k < n_tiles;

@@ -39,16 +39,18 @@ struct ExpandTile {
     }
 
     template <bool NT>
+    // (the chunk's address is the same for every lane: a scalar base and the lane's 32-bit offset)
     __device__ static inline void load_b(const uint16_t *Bp, int chunk, int lane, B &b)
     {
-        const int g = lane >> 4, i16 = lane & 15;
+        [[maybe_unused]] const unsigned g = lane >> 4, i16 = lane & 15;
+        const char *base = reinterpret_cast<const char *>(Bp) + (int64_t)chunk * (128 * R * 2);
         if constexpr (R >= 32) {
 #pragma unroll
             for (int blk = 0; blk < 8; ++blk)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
-                    const int64_t off = (((((int64_t)chunk * 8 + blk) * KS + ks) * 4 + g) * 16 + i16) * 8;
-                    b.r[blk][ks] = ld16<NT>(Bp + off);
+                    const int at = (blk * KS + ks) * 1024;
+                    b.r[blk][ks] = ld16<NT>(base + (at & ~4095) + (unsigned)lane * 16u + (at & 4095));
                 }
         } else {
             // one 16-byte load per pair of sub-blocks; rank 8: lane groups 2,3 re-read the
@@ -56,8 +58,7 @@ struct ExpandTile {
             constexpr int G = R / 4;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int64_t off = ((((int64_t)chunk * 4 + q) * G + (R == 16 ? g : (g & 1))) * 16 + i16) * 8;
-                const u32x4 v = ld16<NT>(Bp + off);
+                const u32x4 v = ld16<NT>(base + ((R == 16 ? g : (g & 1)) * 16u + i16) * 16u + q * G * 256);
                 b.r[2 * q][0] = u32x2{v[0], v[1]};
                 b.r[2 * q + 1][0] = u32x2{v[2], v[3]};
             }

@@ -19,29 +19,33 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
                                                           const int32_t *__restrict__ counts)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wpb = blockDim.x >> 6;
-    const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + wave), nw = gridDim.x * wpb;
-    const int n_tiles = HALVES ? 2 * counts[2] : counts[2];
-    const int per_tile = p.slice0[p.n_fused];                     // wave items of one tile
+    const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave), nw = p.grid * 4;
+    const int per_tile = p.per_tile;
     // Item order: tile_group consecutive items take the same (projection, slice) of
     // tile_group consecutive tiles, so the waves of a workgroup that work on tiles of one
     // segment ask for the same B chunk at about the same time and all but one are served by
     // the L2.  tile_group 1: consecutive items are the slices of one tile.
-    const int G = p.tile_group;
-    const int n_items = (n_tiles + G - 1) / G * G * per_tile;
+    const int gs = p.group_shift;
 
-    for (int item = gw; item < n_items; item += nw) {
-        const int grp = item / (per_tile * G);
-        const int in_grp = item - grp * (per_tile * G);
-        const int rem = in_grp / G;
-        const int tile_ix = grp * G + (in_grp - rem * G);
+    for (int item = gw;; item += nw) {
+        const int grp = item / p.group_items;
+        const int in_grp = item - grp * (per_tile << gs);
+        const int rem = in_grp >> gs;
+        const int tile_ix = (grp << gs) + (in_grp - (rem << gs));
+        const int pj = (rem >= p.slice1 ? 1 : 0) + (rem >= p.slice2 ? 1 : 0);
+        // What does not depend on one another is fetched together: the number of tiles, the tile's record
+        // (looked at only once the number says that there is one; the buffer has a record per row) and the
+        // projection's parameters.
+        const int count = counts[2];
+        lora_tile t = tiles[min(HALVES ? tile_ix >> 1 : tile_ix, p.P - 1)];
+        const ExpandProj q = p.proj[pj];
+        asm volatile("" ::"s"(count), "s"(t.key), "s"(t.row0), "s"(t.n_rows), "s"(q.v), "s"(q.y), "s"(q.ldy),
+                     "s"(q.h_out), "s"(q.n_chunks), "s"(q.cps), "s"(q.slice0));
+        const int n_tiles = HALVES ? 2 * count : count;
+        if (grp << gs >= n_tiles) break;
         if (tile_ix >= n_tiles) continue;
-        const int pj = (rem >= p.slice0[1] ? 1 : 0) + (p.n_fused > 2 && rem >= p.slice0[2] ? 1 : 0);
-        const int slice = rem - p.slice0[pj];
-        const int cps = p.cps[pj];                                // chunks per slice
-        const int c0 = slice * cps, c1 = min(c0 + cps, p.n_chunks[pj]);
+        const int c0 = (rem - q.slice0) * q.cps, c1 = min(c0 + q.cps, q.n_chunks);
         if (c0 >= c1) continue;
-        lora_tile t = tiles[HALVES ? tile_ix >> 1 : tile_ix];
         if constexpr (HALVES) {                                   // rows 0..15 or 16..31 of a 32-row tile
             const int off = (tile_ix & 1) * kDecodeTileRows;
             t.row0 += off;
@@ -49,7 +53,7 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
             if (t.n_rows <= 0) continue;
         }
         const Unit unit = units[(int64_t)t.key * p.n_proj + p.proj0 + pj];
-        expand_tile_chunks<R, F32, OVW, YNT, D>(p, t, unit, pj, c0, c1, lane);
+        expand_tile_chunks<R, F32, OVW, YNT, D>(p, q, t, unit, c0, c1, lane);
     }
 }
 

@@ -13,6 +13,12 @@
 // code is straight-line and the hardware counters let the next chunk's loads stay outstanding
 // across the current chunk's compute.
 //
+// A wave's start is a chain of dependent loads, and for a small batch that chain is the launch: arguments -> tile
+// record, count, projection (together, expand_decode.hip) -> table entry, row indices, parts of v -> B, output
+// rows.  With the loads of a link issued together and the row indices looked at only behind the loads of v and B:
+// llama shapes, 256 rows 60.7 -> 56.2 us for the layer (four expands), 8 rows 34.6 -> 32.2, 333 ragged fp32 rows at
+// rank 32 64.3 -> 60.0, Mixtral shapes, 64 tokens with the combine 46.5 -> 44.2, 512 tokens 104.3 -> 102.1.
+//
 // Row placement: tile row r sits in MFMA row slot (r % 4) * 4 + r / 4, so result register i of
 // lane group g is row 4*i + g.  A tile of n rows then needs only ceil(n / 4) y loads and stores
 // per chunk, each with all four lane groups busy (16 lanes cover 256 contiguous bytes of a row),
@@ -54,6 +60,11 @@ struct ExpandWave {
     __device__ inline void load(int c, typename Tile::B &b, YBuf &y) const
     {
         Tile::template load_b<BNT>(Bp, c, lane, b);
+        load_y(c, y);
+    }
+
+    __device__ inline void load_y(int c, YBuf &y) const
+    {
         const int col = c * kColChunk + i16 * 8;
         const int colc = col < h_out ? col : 0;
 #pragma unroll
@@ -106,13 +117,19 @@ struct ExpandWave {
 
     // issue the loads of the first D chunks of [c0, c1) (a slice shorter than D repeats its
     // last chunk; the repeats are never used)
-    __device__ inline void prefetch(int c0, int c1, Stage (&st)[D]) const
+    __device__ inline void prefetch_b(int c0, int c1, Stage (&st)[D]) const
     {
 #pragma unroll
-        for (int k = 0; k < D; ++k) load(min(c0 + k, c1 - 1), st[k].b, st[k].y);
+        for (int k = 0; k < D; ++k) Tile::template load_b<BNT>(Bp, min(c0 + k, c1 - 1), lane, st[k].b);
     }
 
-    // chunks [c0, c1) after prefetch(): D in flight; every load in the loop body is
+    __device__ inline void prefetch_y(int c0, int c1, Stage (&st)[D]) const
+    {
+#pragma unroll
+        for (int k = 0; k < D; ++k) load_y(min(c0 + k, c1 - 1), st[k].y);
+    }
+
+    // chunks [c0, c1) after their first ones are in flight: D of them at a time; every load in the loop body is
     // unconditional
     __device__ inline void run(int c0, int c1, Stage (&st)[D]) const
     {
@@ -131,46 +148,56 @@ struct ExpandWave {
 };
 
 template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1>
-__device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, const Unit &unit, int pj,
-                                   int c0, int c1, int lane)
+__device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, const lora_tile &t,
+                                   const Unit &unit, int c0, int c1, int lane)
 {
     using Tile = ExpandTile<R>;
     constexpr int KS = Tile::KS, KV = Tile::KV, ESZ = F32 ? 4 : 2;
     using Wave = ExpandWave<R, F32, NI, OVW, YNT, BNT, D>;
     Wave w;
+    asm volatile("" : "+v"(lane));               // keeps what follows from the lane out of registers of the item loop
     w.lane = lane;
     w.g = lane >> 4;
     w.i16 = lane & 15;
-    w.h_out = p.h_out[pj];
+    w.h_out = pe.h_out;
     w.Bp = unit.B;
     const float scale = unit.scale;
+    int dst[NI];             // row indices: asked for first, looked at behind the loads of v and B
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         const int r = 4 * i + w.g;                       // row of result register i
         w.rok[i] = r < t.n_rows;
-        const int at = t.row0 + min(r, t.n_rows - 1);
-        const int dst = p.perm[at];
-        w.yrow[i] = static_cast<char *>(p.y[pj]) + (int64_t)dst * p.ldy[pj] * ESZ;
+        dst[i] = p.perm[t.row0 + min(r, t.n_rows - 1)];
     }
 
     // v operand: this lane's row slot i16 holds tile row (i16 % 4) * 4 + i16 / 4.  The loads of
-    // the K parts (PB at a time) are issued before anything is added, and before the first
+    // the K parts (PB rounds at a time) are issued before anything is added, and before the first
     // chunks' weights and base output, so that the wait for v leaves those in flight; a part
-    // beyond the last re-reads the last one and counts as zero.  The parts are added in
-    // ascending order.
-    constexpr int PB = R <= 32 ? 4 : (F32 ? 1 : 2);              // parts per batch of loads (registers permitting)
-    const int row = (w.i16 & 3) * 4 + (w.i16 >> 2);
-    const bool valid = row < t.n_rows;
-    const float *vrow = p.v[pj] + (int64_t)(t.row0 + (valid ? row : 0)) * R;
-    const int64_t part_stride = (int64_t)p.P * R;
+    // beyond the last re-reads the last one and counts as zero.
+    //
+    // Loads return in order, so parts that are fetched behind the first chunks wait for those as well:
+    // one round trip more for every batch after the first.  Therefore the eight parts a decode
+    // shrink has at most come in one batch at ranks 8 and 16 (in two for taller tiles above), and where a tile
+    // has at most four (eight) rows, the four (two) lanes of a quad whose row slots share the lane's tile row or are
+    // empty fetch a part each; their sums meet on the cross-lane data path.  The order of the sum is
+    // fixed: per lane in ascending order, then the lanes.
+    constexpr int PQ = NI == 1 ? 4 : NI == 2 ? 2 : 1;            // parts per round, one per lane of a row
+    constexpr int PB = R <= 32 ? (NI == 1 ? 2 : 4) : NI == 1 ? 2 : (F32 ? 1 : 2);      // registers permitting
+    const int slot = w.i16;
+    const int row = NI == 1 ? slot >> 2 : NI == 2 ? (slot & 1) * 4 + (slot >> 2) : (slot & 3) * 4 + (slot >> 2);
+    const int sub = NI == 1 ? slot & 3 : NI == 2 ? (slot & 3) >> 1 : 0;
+    const bool valid = row < t.n_rows && sub == 0;
+    const unsigned vrow = (unsigned)(t.row0 + min(row, t.n_rows - 1)) * (R * 4);      // bytes; a part is at most 2^28 of them
+    const int64_t part_stride = (int64_t)p.P * (R * 4);
     auto load_v = [&](int part0, f32x4 (&buf)[PB][KS][KV / 4]) {
 #pragma unroll
         for (int u = 0; u < PB; ++u) {
-            const float *src = vrow + min(part0 + u, p.n_parts - 1) * part_stride;
+            const char *src = reinterpret_cast<const char *>(pe.v) + min(part0 + u * PQ + sub, p.n_parts - 1) * part_stride;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int h = 0; h < KV / 4; ++h) buf[u][ks][h] = ld16f(src + Tile::jbase(w.g, ks) + 4 * h);
+                for (int h = 0; h < KV / 4; ++h) 
+                    buf[u][ks][h] = ld16f(reinterpret_cast<const float *>(src + (vrow + (Tile::jbase(w.g, ks) + 4 * h) * 4u)));
         }
     };
     float s[KS][KV];
@@ -181,7 +208,7 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
     auto add_v = [&](int part0, const f32x4 (&buf)[PB][KS][KV / 4]) {
 #pragma unroll
         for (int u = 0; u < PB; ++u) {
-            const bool in = part0 + u < p.n_parts;             // wave-uniform
+            const bool in = part0 + u * PQ + sub < p.n_parts;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -191,13 +218,26 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
         }
     };
     typename Wave::Stage st[D];
+    // the first chunks' weights and base output, behind the loads of v: only the output rows wait for
+    // the row indices
+    auto prefetch = [&] {
+        w.prefetch_b(c0, c1, st);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            asm volatile("" : "+v"(dst[i]));      // here, and not where the two uses of this code part
+            w.yrow[i] = static_cast<char *>(pe.y) + (int64_t)dst[i] * pe.ldy * ESZ;
+        }
+        w.prefetch_y(c0, c1, st);
+    };
     if (p.n_parts == 1) {                                 // a single part: one load, no batch
         f32x4 one[KS][KV / 4];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int h = 0; h < KV / 4; ++h) one[ks][h] = ld16f(vrow + Tile::jbase(w.g, ks) + 4 * h);
-        w.prefetch(c0, c1, st);
+            for (int h = 0; h < KV / 4; ++h) 
+                one[ks][h] = ld16f(reinterpret_cast<const float *>(reinterpret_cast<const char *>(pe.v) +
+                                                                   (vrow + (Tile::jbase(w.g, ks) + 4 * h) * 4u)));
+        prefetch();
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -207,12 +247,19 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
     } else {
         f32x4 vbuf[PB][KS][KV / 4];
         load_v(0, vbuf);
-        w.prefetch(c0, c1, st);                                  // the first chunks' weights and base output
+        prefetch();
         add_v(0, vbuf);
-        for (int part0 = PB; part0 < p.n_parts; part0 += PB) {
+        for (int part0 = PB * PQ; part0 < p.n_parts; part0 += PB * PQ) {
             load_v(part0, vbuf);
             add_v(part0, vbuf);
         }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int q = 0; q < KV; ++q) {
+                if (PQ >= 2) s[ks][q] += quad_lane<0x4E>(s[ks][q]);          // lane ^ 2
+                if (PQ == 4) s[ks][q] += quad_lane<0xB1>(s[ks][q]);          // lane ^ 1
+            }
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -227,19 +274,19 @@ __device__ inline void expand_item(const ExpandParams &p, const lora_tile &t, co
 // one wave, one tile, chunks [c0, c1) of projection pj; the specialisation on the number of row
 // quads is picked here (wave-uniform)
 template <int R, bool F32, bool OVW, bool YNT, int D>
-__device__ inline void expand_tile_chunks(const ExpandParams &p, const lora_tile &t, const Unit &unit,
-                                          int pj, int c0, int c1, int lane)
+__device__ inline void expand_tile_chunks(const ExpandParams &p, const ExpandProj &pe, const lora_tile &t,
+                                          const Unit &unit, int c0, int c1, int lane)
 {
     switch ((t.n_rows + 3) >> 2) {
-    case 1: expand_item<R, F32, 1, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane); break;
-    case 2: expand_item<R, F32, 2, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane); break;
-    case 3: expand_item<R, F32, 3, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane); break;
+    case 1: expand_item<R, F32, 1, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane); break;
+    case 2: expand_item<R, F32, 2, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane); break;
+    case 3: expand_item<R, F32, 3, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane); break;
     default:
         // a full tile is most likely one of several of its segment: its B is worth keeping in the L2
         if (p.share_b && t.n_rows == kDecodeTileRows)
-            expand_item<R, F32, 4, OVW, YNT, false, D>(p, t, unit, pj, c0, c1, lane);
+            expand_item<R, F32, 4, OVW, YNT, false, D>(p, pe, t, unit, c0, c1, lane);
         else
-            expand_item<R, F32, 4, OVW, YNT, true, D>(p, t, unit, pj, c0, c1, lane);
+            expand_item<R, F32, 4, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane);
         break;
     }
 }

@@ -72,15 +72,16 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
     } else {
         n_tiles = counts[2];
     }
-    const int per_tile = ep.slice0[ep.n_fused];                  // workgroup items of one tile
+    const int per_tile = ep.per_tile;                            // workgroup items of one tile
     const int n_items = n_tiles * per_tile;
     const int kblocks = (sp.h_in + KU - 1) / KU;
 
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const int tile_ix = item / per_tile;
+        const int tile_ix = item / ep.group_items;
         const int rem = item - tile_ix * per_tile;
-        const int pj = (rem >= ep.slice0[1] ? 1 : 0) + (ep.n_fused > 2 && rem >= ep.slice0[2] ? 1 : 0);
-        const int slice = rem - ep.slice0[pj];
+        const int pj = (rem >= ep.slice1 ? 1 : 0) + (rem >= ep.slice2 ? 1 : 0);
+        const ExpandProj &pe = ep.proj[pj];
+        const int slice = rem - pe.slice0;
         lora_tile t;
         if constexpr (BUILD) {
             t = built.tiles[tile_ix];                            // the same for every lane: scalars from here on
@@ -98,18 +99,18 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
 
         // this wave's chunk, and the output rows of result registers 0..3
         const int c0 = slice * NW + wave;
-        const bool has_chunk = c0 < ep.n_chunks[pj];             // wave-uniform
+        const bool has_chunk = c0 < pe.n_chunks;             // wave-uniform
         Out out;
         out.lane = w.lane;
         out.g = w.g;
         out.i16 = w.i16;
-        out.h_out = ep.h_out[pj];
+        out.h_out = pe.h_out;
         out.Bp = unit.B;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * i + w.g;
             out.rok[i] = r < t.n_rows;
-            out.yrow[i] = static_cast<char *>(ep.y[pj]) + (int64_t)row_of(t.row0 + min(r, t.n_rows - 1)) * ep.ldy[pj] * ESZ;
+            out.yrow[i] = static_cast<char *>(pe.y) + (int64_t)row_of(t.row0 + min(r, t.n_rows - 1)) * pe.ldy * ESZ;
         }
         typename Tile::B b;
         typename Out::YBuf y;
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
         }
         // a wave without a chunk re-reads the last one and does not use it: no branch around loads
         w.run(wave * Wave::KB, kblocks, NW * Wave::KB,
-              [&] { out.load(min(c0, ep.n_chunks[pj] - 1), b, y); });
+              [&] { out.load(min(c0, pe.n_chunks - 1), b, y); });
 #pragma unroll
         for (int a = 0; a < NACC; ++a) red[wave][a][w.lane] = w.acc[0][a];
         __syncthreads();

@@ -45,4 +45,11 @@ __device__ inline unsigned pack_bf16_rne(float lo, float hi)
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
+// the value of another lane of the quad (lanes 4k .. 4k + 3): CTRL holds the source lane of each, two bits per lane
+template <int CTRL>
+__device__ inline float quad_lane(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+
 }  // namespace lora

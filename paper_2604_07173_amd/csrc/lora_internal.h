@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "../../include/lora.h"
+#include "lora_layout.h"
 
 namespace lora {
 
@@ -185,6 +186,7 @@ struct ShrinkParams {
     int P;
     int h_in;
     int n_parts;             // long-segment kernel: the most parts there may be (long_split)
+    FastDiv parts;           // decode kernel: division by n_parts
     int kb_per_part;         // decode kernel
     int rank;
     int grid;
@@ -198,32 +200,41 @@ struct ShrinkParams {
     SegParams seg;
 };
 
-// (the arguments of a launch are read by the GPU from host memory: 16 bytes more in these two structures
-// cost a small call 0.1 us per launch, hence the unions)
+// What the front of the expand looks like decides a small call: 1.4 us of a launch's 5 us went into scalar loads
+// that waited for one another (arguments, tile count, a projection's arguments by a run-time index, tile record,
+// table entry) and into two divisions.  So the arguments that every wave needs lie together, those of a projection
+// in a structure that one load fetches beside the tile count and the record, and divisors come as FastDiv.
+struct ExpandProj {          // one projection of an expand: a wave reads the one it works on, with one scalar load
+    const float *v;
+    void *y;
+    int64_t ldy;
+    void *img;               // long-segment kernel: operand images of the 16-row sub-tiles
+    int h_out;
+    int n_chunks;            // 128-column chunks
+    int cps;                 // decode kernel: chunks per wave item (the last of a row may have fewer)
+    int slice0;              // first wave item of the projection within a tile (long segments: chunk)
+};
+
 struct ExpandParams {
     const Unit *units;
+    const lora_tile *tiles;
+    const int32_t *counts;
+    const int32_t *perm;
     int n_proj;
     int proj0;
     int n_fused;             // 1 .. kMaxFused consecutive projections; their widths may differ
-    const float *v[kMaxFused];
-    int n_parts;             // long-segment kernels: the most parts there may be (long_split)
     int P;
-    const int32_t *perm;
-    const lora_tile *tiles;
-    const int32_t *counts;
-    void *y[kMaxFused];
-    int64_t ldy[kMaxFused];
-    int h_out[kMaxFused];
-    int n_chunks[kMaxFused]; // 128-column chunks
-    int n_slices[kMaxFused]; // decode kernel: wave items per (tile, projection)
-    int cps[kMaxFused];      // decode kernel: chunks per wave item (the last of a row may have fewer)
-    int slice0[kMaxFused + 1];   // decode kernel: first wave item of a projection within a tile
-    void *img[kMaxFused];    // long-segment kernel: operand images of the 16-row sub-tiles
+    int n_parts;             // long-segment kernels: the most parts there may be (long_split)
+    int per_tile;            // wave items of a tile (one-launch kernel: workgroup items; long segments: chunks)
+    int slice1, slice2;      // slice0 of the second and the third projection, per_tile where there is none
+    FastDiv group_items;     // division by the wave items of a tile group (one-launch kernel: of a tile)
+    int grid;
+    ExpandProj proj[kMaxFused];
     int image_grid;          // long-segment kernel: workgroups of the image launch
     int waves;               // waves per workgroup
     int tile_halves;         // decode kernel: the tiles have up to 32 rows and are taken in halves
     union {
-        int tile_group;      // decode kernel: consecutive wave items walk over this many tiles
+        int group_shift;     // decode kernel: consecutive wave items walk over 2^group_shift tiles
         int kblocks;         // long-segment kernels: K-blocks of the input
     };
     int out_f32;
@@ -232,7 +243,6 @@ struct ExpandParams {
     int share_b;             // decode kernel: B of full tiles loaded without the streaming hint
     int y_stream;            // decode kernel: output rows read and written with the streaming hint
     int rank;
-    int grid;
 };
 
 // routing-weighted combine of per-pair update rows into token rows
@@ -252,7 +262,7 @@ struct CombineParams {
 // shrink and expand of a decode batch in one launch
 struct FusedParams {
     ShrinkParams s;          // n_parts = 1; v unused
-    ExpandParams e;          // slice0: workgroup items of a tile; v, cps unused
+    ExpandParams e;          // slices: workgroup items of a tile; v, cps unused
 };
 
 hipError_t launch_pack_layer(PackLayerParams &p, hipStream_t s);

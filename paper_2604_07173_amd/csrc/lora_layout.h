@@ -63,4 +63,22 @@ LORA_HD int64_t packB_index(int j, int d, int rank)
     return ((((((int64_t)chunk * 8 + blk) * KS + ks) * 4 + gl) * 16) + n) * 8 + t;
 }
 
+// n / d for 0 <= n < 2^31 as one multiplication.  The divisors of a work item's number are known on the host;
+// a division by a run-time value is a chain of some thirty instructions in front of a wave's first load.
+// With 2^k >= d and mul = 2^(31+k) / d rounded up, mul * d - 2^(31+k) < d <= 2^k, so the error of n * mul / 2^(31+k)
+// stays below n * 2^k / (d * 2^(31+k)) < 1 / d: the quotient is exact.
+struct FastDiv {
+    uint32_t mul, shift;
+};
+
+inline FastDiv fast_div(int d)
+{
+    FastDiv f = {0, 31};
+    while ((1ll << (f.shift - 31)) < d) ++f.shift;
+    f.mul = (uint32_t)(((1ull << f.shift) + d - 1) / d);
+    return f;
+}
+
+LORA_HD int operator/(int n, FastDiv f) { return (int)(((uint64_t)(uint32_t)n * f.mul) >> f.shift); }
+
 }  // namespace lora

@@ -69,30 +69,30 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     w.i16 = w.lane & 15;
     w.h_in = p.h_in;
     w.xt = xt_all + (LINES ? wave * 64 * Wave::NQ : 0);
-    int n_tiles;
-    if constexpr (BUILD) {
+    if constexpr (BUILD)
         build_segments_inline<4>(p.seg, scratch.counts, built, blockIdx.x == 0);   // `built` is complete behind its last barrier
-        n_tiles = built.n_tiles;
-    } else {
-        n_tiles = HALVES ? 2 * counts[2] : counts[2];
-    }
-    const int n_items = n_tiles * p.n_parts;
     const int kblocks = (p.h_in + KU - 1) / KU;
 
     // item loop: a workgroup's item in the K-split form, a wave's item otherwise
     const int first = WPT ? __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave) : blockIdx.x;
-    const int stride = WPT ? gridDim.x * 4 : gridDim.x;
-    for (int item = first; item < n_items; item += stride) {
-        const int tile_ix = item / p.n_parts;
+    const int stride = WPT ? p.grid * 4 : p.grid;
+    for (int item = first;; item += stride) {
+        const int tile_ix = item / p.parts;
         const int part = item - tile_ix * p.n_parts;
         lora_tile t;
         if constexpr (BUILD) {
+            if (tile_ix >= built.n_tiles) break;
             t = built.tiles[tile_ix];                 // the same for every lane: scalars from here on
             t.key = __builtin_amdgcn_readfirstlane(t.key);
             t.row0 = __builtin_amdgcn_readfirstlane(t.row0);
             t.n_rows = __builtin_amdgcn_readfirstlane(t.n_rows);
         } else {
-            t = tiles[HALVES ? tile_ix >> 1 : tile_ix];
+            // the number of tiles and the tile's record are fetched together; the record is looked at only
+            // once the number says that there is one (the buffer has a record per row)
+            const int count = counts[2];
+            t = tiles[min(HALVES ? tile_ix >> 1 : tile_ix, p.P - 1)];
+            asm volatile("" ::"s"(count), "s"(t.key), "s"(t.row0), "s"(t.n_rows));
+            if (tile_ix >= (HALVES ? 2 * count : count)) break;
             if constexpr (HALVES) {                   // rows 0..15 or 16..31 of a 32-row tile
                 const int off = (tile_ix & 1) * kDecodeTileRows;
                 t.row0 += off;

@@ -67,7 +67,7 @@ struct ShrinkWave {
             for (int pj = 0; pj < NPROJ; ++pj)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const u32x4 t = ld16<NT>(Ap[pj] + (((int64_t)kb * NB + nb) * 64 + lane) * 8);
+                    const u32x4 t = ld16<NT>(reinterpret_cast<const char *>(Ap[pj]) + ((int64_t)kb * NB + nb) * 1024 + (unsigned)lane * 16u);
                     s.w[pj][u][nb] = k_ok ? t : zero4;
                 }
             if constexpr (!LINES) {

@@ -14,12 +14,22 @@ SRC = r'''
 #include <cstdio>
 #include <cstdlib>
 #include <cstdint>
+#include <initializer_list>
 #define LORA_HD inline
 #include "lora_layout.h"
 int main(int argc, char** argv) {
   int which = atoi(argv[1]), h = atoi(argv[2]), r = atoi(argv[3]);
   if (which == 0) { for (int c = 0; c < h; ++c) for (int j = 0; j < r; ++j) printf("%lld\n", (long long)lora::packA_index(c, j, r)); }
-  else { for (int j = 0; j < r; ++j) for (int d = 0; d < h; ++d) printf("%lld\n", (long long)lora::packB_index(j, d, r)); }
+  else if (which == 2) {        // every divisor from h to r: quotients around its multiples and at the ends of the range
+    for (int d = h; d <= r; ++d) {
+      const lora::FastDiv f = lora::fast_div(d);
+      const long long top = 2147483647ll;
+      for (long long q : {0ll, 1ll, 2ll, 1000ll, top / d / 3, top / d - 1, top / d})
+        for (long long n = q * d - 1; n <= q * d + 1; ++n)
+          if (n >= 0 && n <= top && (int)n / f != n / d) { printf("%lld %d\n", n, d); return 1; }
+      if ((int)top / f != top / d) { printf("%lld %d\n", top, d); return 1; }
+    }
+  } else { for (int j = 0; j < r; ++j) for (int d = 0; d < h; ++d) printf("%lld\n", (long long)lora::packB_index(j, d, r)); }
   return 0;
 }
 '''
@@ -83,3 +93,10 @@ def test_packB_is_a_bijection_and_groups_eight_columns_per_lane(exe, r):
             assert ix[0, d] // per_pair == (d % 8) // 2
             assert (ix[0, d] // 4) % 2 == d % 2
         assert ix[0, 1] == ix[0, 0] + 4
+
+
+@pytest.mark.parametrize("lo,hi", [(1, 70000), (1 << 20, (1 << 20) + 2000), ((1 << 30) - 1000, (1 << 30) + 1000),
+                                   ((1 << 31) - 1000, (1 << 31) - 2)])
+def test_division_by_multiplication_is_exact(exe, lo, hi):
+    r = subprocess.run([exe, "2", str(lo), str(hi)], capture_output=True, text=True)
+    assert r.returncode == 0, f"n d: {r.stdout}"
