@@ -117,14 +117,14 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
 
         // ---- shrink: this tile, this projection, the whole K range over the waves ----------------
         w.Ap[0] = unit.A;
-        w.row_ok = w.i16 < t.n_rows;
-        {
-            int s = row_of(t.row0 + min(w.i16, t.n_rows - 1));
-            if (sp.src_row) s = sp.src_row[s];
-            w.xp = sp.x + (int64_t)s * sp.ldx;
-        }
+        int at = row_of(t.row0 + min(w.i16, t.n_rows - 1));
+        if (sp.src_row) at = sp.src_row[at];
+        auto rows = [&] {
+            asm volatile("" : "+v"(at));
+            w.xp = sp.x + (int64_t)at * sp.ldx;
+        };
         // a wave without a chunk re-reads the last one and does not use it: no branch around loads
-        w.run(wave * Wave::KB, kblocks, NW * Wave::KB,
+        w.run(wave * Wave::KB, kblocks, NW * Wave::KB, rows,
               [&] { out.load(min(c0, pe.n_chunks - 1), b, y); });
 #pragma unroll
         for (int a = 0; a < NACC; ++a) red[wave][a][w.lane] = w.acc[0][a];

@@ -7,10 +7,8 @@
 //  * wave per tile: every wave takes a whole tile over the whole K range, no LDS, no barrier.
 //    For batches with thousands of small tiles and short inputs (fine-grained MoE).
 // In both a wave streams its slice of the packed A (and of the second fused projection's A)
-// with 16-byte loads that are contiguous per wave, two steps in flight, one at rank 64 (the loads of
-// step s+1 are issued before the MFMAs of step s; all loads are unconditional so the loop is
-// branch-free and the hardware counters keep them outstanding), and multiplies it with the
-// tile's gathered x rows.  The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and
+// with 16-byte loads that are contiguous per wave, two steps in flight (shrink_wave.h), and multiplies it
+// with the tile's gathered x rows.  The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and
 // the rows on the N side, so a lane ends up with four consecutive rank entries of one row.
 //
 // Rank 8: a packed block holds 64 K values (two 32-deep halves side by side in the 16 M
@@ -62,7 +60,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     __shared__ u32x4 xt_all[LINES ? 4 * 64 * Wave::NQ : 1];      // LINES: NQ KiB per wave
     auto &red = scratch.red;
 
-    const int tid = threadIdx.x, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Wave w;
     w.lane = tid & 63;
     w.g = w.lane >> 4;
@@ -74,7 +72,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     const int kblocks = (p.h_in + KU - 1) / KU;
 
     // item loop: a workgroup's item in the K-split form, a wave's item otherwise
-    const int first = WPT ? __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave) : blockIdx.x;
+    const int first = WPT ? (int)blockIdx.x * 4 + wave : blockIdx.x;
     const int stride = WPT ? p.grid * 4 : p.grid;
     for (int item = first;; item += stride) {
         const int tile_ix = item / p.parts;
@@ -103,34 +101,35 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
 #pragma unroll
         for (int pj = 0; pj < NPROJ; ++pj)
             w.Ap[pj] = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].A;
-        w.row_ok = w.i16 < t.n_rows;
-        if constexpr (LINES) {
-            int s[Wave::NQ];
+        const bool row_ok = w.i16 < t.n_rows;
+        // Row indices: asked for here, looked at behind the first loads of A.  (Loads return in order, so the second
+        // look-up has to be in front of those.)
+        int at[LINES ? Wave::NQ : 1];
 #pragma unroll
-            for (int q = 0; q < Wave::NQ; ++q) {
-                const int at = t.row0 + min(Wave::RPI * q + w.lane / Wave::PPR, t.n_rows - 1);
-                if constexpr (BUILD) s[q] = built.perm[at];
-                else s[q] = p.perm[at];
-            }
-            if (p.src_row) {
-#pragma unroll
-                for (int q = 0; q < Wave::NQ; ++q) s[q] = p.src_row[s[q]];
-            }
-#pragma unroll
-            for (int q = 0; q < Wave::NQ; ++q) w.xq[q] = p.x + (int64_t)s[q] * p.ldx;
-            w.xp = w.xq[0];
-        } else {
-            int s;
-            if constexpr (BUILD) s = built.perm[t.row0 + min(w.i16, t.n_rows - 1)];
-            else s = p.perm[t.row0 + min(w.i16, t.n_rows - 1)];
-            if (p.src_row) s = p.src_row[s];
-            w.xp = p.x + (int64_t)s * p.ldx;
+        for (int q = 0; q < (LINES ? Wave::NQ : 1); ++q) {
+            const int row = t.row0 + min(LINES ? Wave::RPI * q + w.lane / Wave::PPR : w.i16, t.n_rows - 1);
+            if constexpr (BUILD) at[q] = built.perm[row];
+            else at[q] = p.perm[row];
         }
+        if (p.src_row) {
+#pragma unroll
+            for (int q = 0; q < (LINES ? Wave::NQ : 1); ++q) at[q] = p.src_row[at[q]];
+        }
+        auto rows = [&] {
+#pragma unroll
+            for (int q = 0; q < (LINES ? Wave::NQ : 1); ++q) asm volatile("" : "+v"(at[q]));
+            if constexpr (LINES) {
+#pragma unroll
+                for (int q = 0; q < Wave::NQ; ++q) w.xq[q] = p.x + (int64_t)at[q] * p.ldx;
+            } else {
+                w.xp = p.x + (int64_t)at[0] * p.ldx;
+            }
+        };
         const int part_begin = part * p.kb_per_part;
         const int part_end = min(part_begin + p.kb_per_part, kblocks);
 
         if constexpr (WPT) {
-            w.run(part_begin, part_end);
+            w.run(part_begin, part_end, Wave::KB, rows, [] {});
             // lane (row i16, group g) holds rank entries 4g..4g+3 of its row; for rank 8 the
             // entries of groups 2,3 belong to the second half product and are added to the
             // first half's entries held 32 lanes below
@@ -140,12 +139,12 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
                     f32x4 s = w.acc[pj][0];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) s[q] += __shfl_down(w.acc[pj][1][q], 32, 64);
-                    if (w.row_ok && w.g < 2)
+                    if (row_ok && w.g < 2)
                         st16f(p.v[pj] + ((int64_t)part * p.P + t.row0 + w.i16) * R + w.g * 4, s);
                 } else {
 #pragma unroll
                     for (int nb = 0; nb < Wave::NB; ++nb)
-                        if (w.row_ok)
+                        if (row_ok)
                             st16f(p.v[pj] + ((int64_t)part * p.P + t.row0 + w.i16) * R + nb * 16 + w.g * 4,
                                   w.acc[pj][nb]);
                 }
@@ -153,7 +152,7 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
         } else {
             // the four waves take the part's steps in turn, so that together they read a
             // contiguous kilobyte or more of every x row (and of A) at about the same time
-            w.run(part_begin + wave * Wave::KB, part_end, 4 * Wave::KB);
+            w.run(part_begin + wave * Wave::KB, part_end, 4 * Wave::KB, rows, [] {});
 
             // add the four waves' sums in a fixed order and store this part of v
 #pragma unroll

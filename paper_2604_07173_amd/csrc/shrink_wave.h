@@ -3,9 +3,14 @@
 // K units of the packed A (of up to three projections that read the same input) with the
 // gathered x rows of one tile.
 //
-// A wave streams its slice of the packed A with 16-byte loads that are contiguous per wave, two
-// steps in flight, one at rank 64 (the loads of step s+1 are issued before the MFMAs of step s; all loads are
-// unconditional so the loop is branch-free and the hardware counters keep them outstanding).
+// A wave streams its slice of the packed A with 16-byte loads that are contiguous per wave, two steps in
+// flight: the loads of step s+1 are issued before the MFMAs of step s, all loads are unconditional so that the loop is
+// branch-free, and nothing looks at loaded data but the MFMAs, so the hardware counters keep a whole step
+// outstanding while the other is multiplied.  (With the rows and columns that do not count replaced by zeros where they
+// are loaded, and the order left to the scheduler, a wave waited for everything it had asked for once
+// per turn.)  Layer call, before / after: Mixtral shapes, 512 tokens, rank 64 331 -> 318 us; llama shapes, 256 rows,
+// rank 64 145 -> 137, rank 32 89.3 -> 83.2, rank 8 53.0 -> 48.8; fine-grained MoE, 256 tokens 66.3 -> 61.3; rank 64 with
+// one step in flight 322 and 137.
 // The rank index sits on the M side of v_mfma_f32_16x16x32_bf16 and the rows on the N side, so a
 // lane ends up with four consecutive rank entries of one row.
 //
@@ -45,7 +50,6 @@ struct ShrinkWave {
     const uint16_t *xp;      // this lane's x row (a valid row even if the lane's row is not)
     const uint16_t *xq[LINES ? NQ : 1];  // LINES: rows RPI * q + lane / PPR of the tile (valid rows likewise)
     u32x4 *xt;               // LINES: the wave's LDS, NQ KiB
-    bool row_ok;
     f32x4 acc[NPROJ][NACC];
 
     struct Step {
@@ -53,36 +57,44 @@ struct ShrinkWave {
         u32x4 x[KB][XN];
     };
 
-    // All loads are unconditional: a K unit beyond the wave's range re-reads the last valid
-    // unit and a row beyond the tile re-reads the tile's first row; both are then replaced
-    // by zeros with selects.  No branches, so the next step's loads stay in flight.
+    // All loads are unconditional: a K unit beyond the wave's range re-reads the last valid unit, columns
+    // beyond the row re-read its last ones, and a row beyond the tile the tile's last row.  Only a wave's last step can have
+    // such units and columns; its multiplications leave them out (mma<true>).  Rows beyond the tile are
+    // columns of the result that nobody reads, so they need no zeros.
     __device__ inline void load(int kb0, int kb_end, Step &s) const
     {
-        const u32x4 zero4 = {0u, 0u, 0u, 0u};
+        load_a(kb0, kb_end, s);
+        load_x(kb0, kb_end, s);
+    }
+
+    __device__ inline void load_a(int kb0, int kb_end, Step &s) const
+    {
+        unsigned off = (unsigned)lane * 16u;
+        asm volatile("" : "+v"(off));        // a 32-bit offset on a scalar base: not widened ahead of time
 #pragma unroll
         for (int u = 0; u < KB; ++u) {
-            const bool k_ok = kb0 + u < kb_end;
-            const int kb = k_ok ? kb0 + u : kb_end - 1;
+            const int kb = min(kb0 + u, kb_end - 1);
 #pragma unroll
-            for (int pj = 0; pj < NPROJ; ++pj)
+            for (int pj = 0; pj < NPROJ; ++pj) {
+                const char *base = reinterpret_cast<const char *>(Ap[pj]) + (int64_t)kb * (NB * 1024);
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const u32x4 t = ld16<NT>(reinterpret_cast<const char *>(Ap[pj]) + ((int64_t)kb * NB + nb) * 1024 + (unsigned)lane * 16u);
-                    s.w[pj][u][nb] = k_ok ? t : zero4;
-                }
-            if constexpr (!LINES) {
-#pragma unroll
-                for (int h = 0; h < XN; ++h) {
-                    const int c = kb * KU + h * 32 + g * 8;
-                    const bool c_ok = c < h_in;
-                    const u32x4 t = ld16<XNT>(xp + (c_ok ? c : 0));
-                    s.x[u][h] = (k_ok && row_ok && c_ok) ? t : zero4;
-                }
+                for (int nb = 0; nb < NB; ++nb) s.w[pj][u][nb] = ld16<NT>(base + off + nb * 1024);
             }
         }
-        if constexpr (LINES) {
-            // lane of instruction q: row RPI * q + lane / PPR, K values kb0 * KU + 8 * (lane % PPR) .. + 7;
-            // what lies beyond the range or the row is replaced by zeros after the transposition
+    }
+
+    __device__ inline void load_x(int kb0, int kb_end, Step &s) const
+    {
+        if constexpr (!LINES) {
+#pragma unroll
+            for (int u = 0; u < KB; ++u) {
+                const int kb = min(kb0 + u, kb_end - 1);
+#pragma unroll
+                for (int h = 0; h < XN; ++h)
+                    s.x[u][h] = ld16<XNT>(xp + (unsigned)min(kb * KU + h * 32 + g * 8, h_in - 8));
+            }
+        } else {
+            // lane of instruction q: row RPI * q + lane / PPR, K values kb0 * KU + 8 * (lane % PPR) .. + 7
             const int piece = lane % PPR, c = kb0 * KU + piece * 8;
             const bool ok = kb0 + piece / (KU / 8) < kb_end && c < h_in;
 #pragma unroll
@@ -90,11 +102,9 @@ struct ShrinkWave {
         }
     }
 
-    // LINES: the step's rows through LDS into operand order; everything the MFMAs must not see
-    // (rows beyond the tile, K beyond the range) becomes zero here
-    __device__ inline void to_operands(int kb0, int kb_end, Step &s) const
+    // LINES: the step's rows through LDS into operand order
+    __device__ inline void to_operands(Step &s) const
     {
-        const u32x4 zero4 = {0u, 0u, 0u, 0u};
         auto at = [](int row, int piece) { return row * PPR + (piece ^ (row / (16 / PPR))); };
 #pragma unroll
         for (int q = 0; q < NQ; ++q) xt[at(RPI * q + lane / PPR, lane % PPR)] = (&s.x[0][0])[q];
@@ -102,18 +112,25 @@ struct ShrinkWave {
 #pragma unroll
         for (int u = 0; u < KB; ++u)
 #pragma unroll
-            for (int h = 0; h < XN; ++h) {
-                const u32x4 t = xt[at(i16, (u * KU + h * 32) / 8 + g)];
-                const bool ok = kb0 + u < kb_end && row_ok && (kb0 + u) * KU + h * 32 + g * 8 < h_in;
-                s.x[u][h] = ok ? t : zero4;
-            }
+            for (int h = 0; h < XN; ++h) s.x[u][h] = xt[at(i16, (u * KU + h * 32) / 8 + g)];
         __builtin_amdgcn_wave_barrier();
     }
 
-    __device__ inline void mma(const Step &s)
+    // LAST: the step may reach beyond the range (those units are left out; a uniform branch) and beyond the
+    // row's end (zeros for x: the packed A holds zeros there, and zero times whatever was read may be a NaN)
+    template <bool LAST>
+    __device__ inline void mma(int kb0, int kb_end, Step &s)
     {
+        if constexpr (LINES) to_operands(s);
 #pragma unroll
-        for (int u = 0; u < KB; ++u)
+        for (int u = 0; u < KB; ++u) {
+            if (LAST && kb0 + u >= kb_end) break;
+            if (LAST && (kb0 + u + 1) * KU > h_in) {
+                const u32x4 zero4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int h = 0; h < XN; ++h)
+                    if ((kb0 + u) * KU + h * 32 + g * 8 >= h_in) s.x[u][h] = zero4;
+            }
 #pragma unroll
             for (int pj = 0; pj < NPROJ; ++pj) {
                 if (R == 8) {
@@ -128,63 +145,51 @@ struct ShrinkWave {
                             as_bf16x8(s.w[pj][u][nb]), as_bf16x8(s.x[u][0]), acc[pj][nb], 0, 0, 0);
                 }
             }
+        }
     }
 
     // K units kb_begin, kb_begin + stride, ... below kb_end in steps of KB units (stride = KB:
-    // the contiguous range [kb_begin, kb_end)), two steps in flight (one at rank 64)
-    __device__ inline void run(int kb_begin, int kb_end, int stride = KB)
-    {
-        run(kb_begin, kb_end, stride, [] {});
-    }
-
-    // `between` issues loads of the caller's behind those of the first step, so that they are in flight
-    // while the wave works through its range
-    template <typename F>
-    __device__ inline void run(int kb_begin, int kb_end, int stride, F between)
+    // the contiguous range [kb_begin, kb_end)), two steps in flight.  `rows` sets the pointers of the x rows; it is
+    // called behind the first loads of A, which do not wait for the row indices.  `between` issues loads of the
+    // caller's behind those of the first step, so that they are in flight while the wave works through its range.
+    template <typename G, typename F>
+    __device__ inline void run(int kb_begin, int kb_end, int stride, G rows, F between)
     {
 #pragma unroll
         for (int pj = 0; pj < NPROJ; ++pj)
 #pragma unroll
             for (int a = 0; a < NACC; ++a) acc[pj][a] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (kb_begin >= kb_end) {
+            rows();
             between();
             return;
         }
-        if constexpr (R == 64 && NT) {
-            // one step in flight: at rank 64 the second one's registers cost up to three of eight waves per
-            // SIMD (llama shapes, 256 rows 151 -> 148 us, 1024 rows 261 -> 259; slower at the lower ranks)
-            Step s;
-            load(kb_begin, kb_end, s);
-            between();
-            int kb0 = kb_begin;
-            for (; kb0 + stride < kb_end; kb0 += stride) {
-                mma(s);
-                load(kb0 + stride, kb_end, s);
-            }
-            mma(s);
-            return;
-        }
-        Step s0, s1;
-        load(kb_begin, kb_end, s0);
-        between();
+        // The barriers keep the loads of a step in front of the multiplications of the step before: without
+        // them the scheduler puts both steps' loads behind, and a wave waits for everything it asked for.
+        auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
         int kb0 = kb_begin;
+        Step s0, s1;
+        load_a(kb0, kb_end, s0);
+        rows();
+        load_x(kb0, kb_end, s0);
+        between();
         for (; kb0 + 2 * stride < kb_end; kb0 += 2 * stride) {
             load(kb0 + stride, kb_end, s1);
-            if constexpr (LINES) to_operands(kb0, kb_end, s0);
-            mma(s0);
+            fence();
+            mma<false>(kb0, kb_end, s0);
+            fence();
             load(kb0 + 2 * stride, kb_end, s0);
-            if constexpr (LINES) to_operands(kb0 + stride, kb_end, s1);
-            mma(s1);
+            fence();
+            mma<false>(kb0 + stride, kb_end, s1);
+            fence();
         }
         if (kb0 + stride < kb_end) {
             load(kb0 + stride, kb_end, s1);
-            if constexpr (LINES) to_operands(kb0, kb_end, s0);
-            mma(s0);
-            if constexpr (LINES) to_operands(kb0 + stride, kb_end, s1);
-            mma(s1);
+            fence();
+            mma<false>(kb0, kb_end, s0);
+            mma<true>(kb0 + stride, kb_end, s1);
         } else {
-            if constexpr (LINES) to_operands(kb0, kb_end, s0);
-            mma(s0);
+            mma<true>(kb0, kb_end, s0);
         }
     }
 };
