@@ -54,6 +54,10 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
         }
         const Unit unit = units[(int64_t)t.key * p.n_proj + p.proj0 + pj];
         expand_tile_chunks<R, F32, OVW, YNT, D>(p, q, t, unit, c0, c1, lane);
+        // A wave's last item ends here: no decoding of a next one.  Before another item the loads that the last chunks
+        // repeated come in (vmcnt(0)), so that the compiler does not wait for them in the middle of the next item's first loads.
+        if (item + nw >= ((n_tiles + (1 << gs) - 1) >> gs) * (per_tile << gs)) break;
+        __builtin_amdgcn_s_waitcnt(0x0f70);
     }
 }
 

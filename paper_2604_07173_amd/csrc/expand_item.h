@@ -237,6 +237,7 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
             for (int h = 0; h < KV / 4; ++h) 
                 one[ks][h] = ld16f(reinterpret_cast<const float *>(reinterpret_cast<const char *>(pe.v) +
                                                                    (vrow + (Tile::jbase(w.g, ks) + 4 * h) * 4u)));
+        __builtin_amdgcn_sched_barrier(0);                       // v first: everything waits for it
         prefetch();
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -247,6 +248,7 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
     } else {
         f32x4 vbuf[PB][KS][KV / 4];
         load_v(0, vbuf);
+        __builtin_amdgcn_sched_barrier(0);                       // v first: everything waits for it
         prefetch();
         add_v(0, vbuf);
         for (int part0 = PB * PQ; part0 < p.n_parts; part0 += PB * PQ) {
