@@ -7,7 +7,8 @@
 // the results.  One CU issues one wave instruction per four cycles and SIMD, so the time of
 // either path below is essentially its instruction count.
 //
-// Two paths with identical results (rows ordered by key, original order inside a key):
+// Three paths with identical results (rows ordered by key, original order inside a key), one of them for at most
+// kSmallMaxRows rows over 256 keys (segments_small_kernel) and:
 //
 // * Radix path (segments_kernel; long segments, or key spaces too large for LDS counters).
 //   LDS holds key[row] for the whole batch and two 16-bit row-index arrays that the radix
@@ -26,7 +27,7 @@
 // * Counting path (segments_bucket_kernel; many short segments): described at the kernel.
 #include <cstdlib>
 
-#include "segments_common.h"
+#include "segments_inline.h"
 
 namespace lora {
 
@@ -366,6 +367,30 @@ __global__ __launch_bounds__(kThreads) void segments_kernel(SegParams p)
     radix_body(p);
 }
 
+// ---- few keys, a few thousand rows -----------------------------------------------------------
+// The sort that small batches do inside the first shrink (segments_inline.h), by one workgroup of sixteen waves: the
+// groups of 64 rows of a wave are matched bit by bit together, where the radix path takes them one after the
+// other and waits for the running count between them.  What is left is mostly that match (one workgroup's instructions).
+// Back to back in a graph, before (radix or bucket path) / now: 64 rows 5.4 / 3.2 us, 1024 rows over 256 keys 6.4 /
+// 3.5, 2048 8.0 / 4.3, 4096 10.6 / 5.8, 4096 rows of 8 requests 9.1 / 5.1; four threads per key for the sums over
+// the groups: no change.
+constexpr int kSmallMaxRows = 4096;
+constexpr int kSmallGroups = kSmallMaxRows / 64;
+
+template <int GROUPS, int TR>
+__global__ __launch_bounds__(kThreads) void segments_small_kernel(SegParams p)
+{
+    __shared__ SortCounts<GROUPS> counts;
+    __shared__ SortedSegments<64 * GROUPS, false> sorted;
+    build_segments_inline_n<kWaves, GROUPS, TR>(p, counts, sorted, true);
+}
+
+template <int GROUPS, int TR>
+void launch_small(const SegParams &p, hipStream_t s)
+{
+    hipLaunchKernelGGL((segments_small_kernel<GROUPS, TR>), dim3(1), dim3(kThreads), 0, s, p);
+}
+
 // ---- bucket path ---------------------------------------------------------------------------
 // For batches of many short segments (decode): one LDS counter per key instead of radix
 // passes over the key bits.
@@ -650,6 +675,14 @@ hipError_t launch_segments(const SegParams &p_in, void *ws, hipStream_t s)
         const char *e = getenv("LORA_SEGMENT_PATH");
         return e && e[0] == 'r';
     }();
+    // at most 256 keys and 4096 rows: a kernel of its own, ahead of both paths at every size it takes
+    if (!force_radix && n_keys <= kInlineMaxKeys && p.P > 0 && p.P <= kSmallMaxRows) {
+        if (p.tile_rows == kTileRows) launch_small<kSmallGroups, kTileRows>(p, s);
+        else if (p.P <= 1024) launch_small<16, kDecodeTileRows>(p, s);
+        else if (p.P <= 2048) launch_small<32, kDecodeTileRows>(p, s);
+        else launch_small<kSmallGroups, kDecodeTileRows>(p, s);
+        return hipGetLastError();
+    }
     // one radix pass (at most 256 keys) is as fast as the counting path and has no bucket
     // limit: prefer it once there are enough rows per key for long buckets to be likely
     const bool radix_is_cheap = p.passes == 1 && (int64_t)p.P >= 8 * (int64_t)n_keys;

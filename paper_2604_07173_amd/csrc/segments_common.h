@@ -87,9 +87,8 @@ __device__ inline __noinline__ Match match_digit(unsigned digit, bool valid, int
     Match m = {(unsigned)v, (unsigned)(v >> 32)};
 #pragma unroll 1
     for (int b = 0; b < nbits; ++b) {
-        const unsigned bit = (digit >> b) & 1u;
-        const unsigned long long bal = __ballot(valid && bit);
-        const unsigned same = 0u - bit;                  // all ones if my bit is set
+        const unsigned same = (unsigned)__builtin_amdgcn_sbfe((int)digit, (unsigned)b, 1u);    // all ones if my bit is set
+        const unsigned long long bal = __ballot(same != 0);            // lanes that are not valid are in no mask
         m.lo &= ~((unsigned)bal ^ same);                 // bit ? bal : ~bal
         m.hi &= ~((unsigned)(bal >> 32) ^ same);
     }

@@ -13,6 +13,8 @@
 // Limits: kInlineMaxRows rows, kInlineMaxKeys keys, tiles of kDecodeTileRows rows, workgroups
 // of four waves and more (thread k < kInlineMaxKeys owns key k).
 //
+// The stand-alone builder of up to 4096 rows is the same sort with sixteen waves (segments.hip).
+//
 // Stability without order-defining atomics: the batch is cut into groups of 64 consecutive
 // rows, one wave handles a group at a time and ranks equal keys inside it by lane order (ballot
 // match); counts[group][key] is written by the group's first lane of that key.  Thread k then
@@ -28,25 +30,30 @@ namespace lora {
 constexpr int kInlineMaxRows = 2048;
 constexpr int kInlineMaxKeys = 256;
 constexpr int kInlineGroups = kInlineMaxRows / 64;
-constexpr int kInlineMaxTiles = kInlineMaxRows / kDecodeTileRows + kInlineMaxKeys;
 constexpr int kInlineKeyWaves = kInlineMaxKeys / 64;             // waves whose threads own a key
 
-typedef uint16_t InlineCounts[kInlineGroups][kInlineMaxKeys];     // 16 KiB, free again after the build
+template <int GROUPS>
+using SortCounts = uint16_t[GROUPS][kInlineMaxKeys];
+typedef SortCounts<kInlineGroups> InlineCounts;                   // 16 KiB, free again after the build
 
-struct InlineSegments {                 // lives in LDS for the whole kernel
-    uint16_t perm[kInlineMaxRows];
-    lora_tile tiles[kInlineMaxTiles];
+// TILES: room for the tile records, which otherwise go straight to the caller's segments
+template <int ROWS, bool TILES>
+struct SortedSegments {
+    static constexpr bool kKeepsTiles = TILES;
+    uint16_t perm[ROWS];
+    lora_tile tiles[TILES ? ROWS / kDecodeTileRows + kInlineMaxKeys : 1];
+    unsigned key_tile[TILES ? 1 : kInlineMaxKeys];               // first tile of a key, its segment << 16
     unsigned key_start[kInlineMaxKeys];
     unsigned wave_sums[kInlineKeyWaves][3];
     unsigned status;
     int n_tiles;
 };
+typedef SortedSegments<kInlineMaxRows, true> InlineSegments;     // lives in LDS for the whole kernel
 
 // G: groups of 64 rows that the code is unrolled for (batches of up to 64 * G rows); NW: waves of the
-// workgroup
-template <int NW, int G>
-__device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts &counts, InlineSegments &L,
-                                               bool write_global)
+// workgroup; TR: rows per tile
+template <int NW, int G, int TR = kDecodeTileRows, class Counts, class Segments>
+__device__ inline void build_segments_inline_n(const SegParams &sp, Counts &counts, Segments &L, bool write_global)
 {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int P = sp.P;
@@ -88,9 +95,9 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     for (int b = 0; b < sp.key_bits; ++b) {
 #pragma unroll
         for (int u = 0; u < GPW; ++u) {
-            const unsigned bit = (key[u] >> b) & 1u;         // kNoKey lanes are in no mask anyway
-            const unsigned long long bal = __ballot(key[u] != kNoKey && bit);
-            const unsigned same = 0u - bit;
+            // all ones if my bit is set; lanes without a key (all bits set) are in no mask
+            const unsigned same = (unsigned)__builtin_amdgcn_sbfe((int)key[u], (unsigned)b, 1u);
+            const unsigned long long bal = __ballot(same != 0);
             m[u].lo &= ~((unsigned)bal ^ same);
             m[u].hi &= ~((unsigned)(bal >> 32) ^ same);
         }
@@ -116,7 +123,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
             counts[g][tid] = (uint16_t)total;
             total += c[g];
         }
-        my_tiles = (total + kDecodeTileRows - 1) / kDecodeTileRows;
+        my_tiles = (total + TR - 1) / TR;
         occ = total ? 1u : 0u;
         ir = wave_incl_sum(total), is = wave_incl_sum(occ), it = wave_incl_sum(my_tiles);
         if (lane == 63) {
@@ -140,26 +147,32 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     if (owner) L.key_start[tid] = row0;
     if (tid == 0) L.n_tiles = (int)n_tiles;
     // tiles and segment record of my key (a thread without a key has no rows)
+    if constexpr (!Segments::kKeepsTiles) {
+        if (owner) L.key_tile[tid] = tile0 | seg << 16;
+    }
     auto put_tile = [&](int key, unsigned first, unsigned rows, unsigned s, unsigned tile_base, unsigned j) {
         lora_tile t;
         t.key = key;
-        t.row0 = (int32_t)(first + j * kDecodeTileRows);
-        t.n_rows = (int32_t)min((unsigned)kDecodeTileRows, rows - j * kDecodeTileRows);
+        t.row0 = (int32_t)(first + j * TR);
+        t.n_rows = (int32_t)min((unsigned)TR, rows - j * TR);
         t.seg = (int32_t)s;
-        L.tiles[tile_base + j] = t;
+        if constexpr (Segments::kKeepsTiles) L.tiles[tile_base + j] = t;
+        else sp.tiles[tile_base + j] = t;
     };
-    constexpr unsigned kOwnTiles = 3;
+    if constexpr (Segments::kKeepsTiles) {
+        constexpr unsigned kOwnTiles = 3;
 #pragma unroll
-    for (unsigned j = 0; j < kOwnTiles; ++j)
-        if (j < my_tiles) put_tile(tid, row0, total, seg, tile0, j);
-    // the rest of a long segment by the whole wave (one thread writing the 112 tiles of a prompt of 1792 rows:
-    // 150.2 us for the layer of llama shapes that it is part of, 148.4 so)
-    for (unsigned long long more = __ballot(my_tiles > kOwnTiles); more; more &= more - 1) {
-        const int l = __ffsll((long long)more) - 1;
-        const unsigned r0 = __builtin_amdgcn_readlane(row0, l), n = __builtin_amdgcn_readlane(total, l);
-        const unsigned s = __builtin_amdgcn_readlane(seg, l), t0 = __builtin_amdgcn_readlane(tile0, l);
-        const unsigned nt = __builtin_amdgcn_readlane(my_tiles, l);
-        for (unsigned j = kOwnTiles + lane; j < nt; j += 64) put_tile(w * 64 + l, r0, n, s, t0, j);
+        for (unsigned j = 0; j < kOwnTiles; ++j)
+            if (j < my_tiles) put_tile(tid, row0, total, seg, tile0, j);
+        // the rest of a long segment by the whole wave (one thread writing the 112 tiles of a prompt of 1792 rows:
+        // 150.2 us for the layer of llama shapes that it is part of, 148.4 so)
+        for (unsigned long long more = __ballot(my_tiles > kOwnTiles); more; more &= more - 1) {
+            const int l = __ffsll((long long)more) - 1;
+            const unsigned r0 = __builtin_amdgcn_readlane(row0, l), n = __builtin_amdgcn_readlane(total, l);
+            const unsigned s = __builtin_amdgcn_readlane(seg, l), t0 = __builtin_amdgcn_readlane(tile0, l);
+            const unsigned nt = __builtin_amdgcn_readlane(my_tiles, l);
+            for (unsigned j = kOwnTiles + lane; j < nt; j += 64) put_tile(w * 64 + l, r0, n, s, t0, j);
+        }
     }
     if (write_global && total) {
         sp.seg_start[seg] = (int32_t)row0;
@@ -167,6 +180,19 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
     }
     __syncthreads();
 
+    if constexpr (!Segments::kKeepsTiles) {
+        // a tile per thread and turn: its key is the last one whose first tile is not beyond it (an empty key shares
+        // its first tile with the next key, which wins)
+        for (unsigned ti = tid; ti < n_tiles; ti += 64 * NW) {
+            int key = 0;
+#pragma unroll
+            for (int step = kInlineMaxKeys / 2; step > 0; step >>= 1)
+                if ((L.key_tile[key + step] & 0xFFFFu) <= ti) key += step;
+            const unsigned first = L.key_start[key], end = key + 1 < kInlineMaxKeys ? L.key_start[key + 1] : P_act;
+            const unsigned t0 = L.key_tile[key] & 0xFFFFu;
+            put_tile(key, first, end - first, L.key_tile[key] >> 16, t0, ti - t0);
+        }
+    }
     // rows to their positions
 #pragma unroll
     for (int u = 0; u < GPW; ++u) {
@@ -178,7 +204,8 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, InlineCounts
 
     if (write_global) {
         for (unsigned i = tid; i < P_act; i += 64 * NW) sp.perm[i] = (int32_t)L.perm[i];
-        for (unsigned i = tid; i < n_tiles; i += 64 * NW) sp.tiles[i] = L.tiles[i];
+        if constexpr (Segments::kKeepsTiles)
+            for (unsigned i = tid; i < n_tiles; i += 64 * NW) sp.tiles[i] = L.tiles[i];
         if (tid == 0) {
             sp.seg_start[S] = (int32_t)P_act;
             sp.counts[0] = (int32_t)S;
