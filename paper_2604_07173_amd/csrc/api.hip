@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <mutex>
 #include <new>
@@ -123,6 +124,9 @@ struct lora_pool {
     size_t B_off[LORA_MAX_PROJ], B_bytes[LORA_MAX_PROJ];
     std::vector<Unit> table;              // host mirror of the device table
     std::vector<hipEvent_t> ready;        // [adapter][layer], created at the first async load
+    // An adapter's rank is below the pool's: the decode kernels look at the ranks.  Atomic, because a call on one thread
+    // may read it while another gives a slot a new rank; results are the same either way.
+    std::atomic<bool> lower_ranks;
     int act_policy;                       // LORA_ACT_*: cache hints of the activation streams
 
     size_t unit_base(int layer, int adapter, int expert) const
@@ -134,7 +138,19 @@ struct lora_pool {
     {
         return (((size_t)layer * d.n_adapters + adapter) * d.n_experts + expert) * d.n_proj + proj;
     }
+    void note_ranks()
+    {
+        bool any = false;
+        for (int32_t r : arank) any = any || r < d.rank;
+        lower_ranks.store(any, std::memory_order_relaxed);
+    }
     const Unit *device_table() const { return reinterpret_cast<const Unit *>(slab); }
+    // a_rank or b_rank of a unit's entry in the device table
+    int32_t *rank_field(int layer, int adapter, int expert, int proj, bool of_b) const
+    {
+        Unit *u = reinterpret_cast<Unit *>(slab) + table_index(layer, adapter, expert, proj);
+        return of_b ? &u->b_rank : &u->a_rank;
+    }
 };
 
 namespace {
@@ -422,6 +438,7 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
     sp.parts = fast_div(ks.n_parts);
     sp.kb_per_part = ks.kb_per_part;
     sp.rank = pool->d.rank;
+    sp.lower_ranks = pool->lower_ranks.load(std::memory_order_relaxed);
     if (!long_kernels(pool, seg->P, seg->tile_rows)) {
         sp.tile_halves = seg->tile_rows == kTileRows;
         const int64_t items = ks.n_parts * (sp.tile_halves ? 2 * tiles_upper_bound(pool, seg->P, kTileRows)
@@ -515,6 +532,7 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     ep.counts = seg->counts;
     ep.out_f32 = out_dtype == LORA_DTYPE_F32;
     ep.rank = pool->d.rank;
+    ep.lower_ranks = pool->lower_ranks.load(std::memory_order_relaxed);
     const bool decode = !long_kernels(pool, seg->P, seg->tile_rows);
     const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(pool, seg->P, decode ? kDecodeTileRows : kTileRows));
     if (decode) {
@@ -793,6 +811,7 @@ int lora_register_pool(const lora_pool_desc *d, void *slab, size_t slab_bytes,
     if (d->scale) p->scale.assign(d->scale, d->scale + d->n_adapters);
     p->arank.assign(d->n_adapters, d->rank);
     if (d->adapter_rank) p->arank.assign(d->adapter_rank, d->adapter_rank + d->n_adapters);
+    p->note_ranks();
     p->d.scale = nullptr;
     p->d.adapter_rank = nullptr;
     p->slab = static_cast<char *>(slab);
@@ -816,7 +835,7 @@ int lora_register_pool(const lora_pool_desc *d, void *slab, size_t slab_bytes,
                     u.B = reinterpret_cast<const uint16_t *>(p->slab + base + L.B_off[j]);
                     u.scale = p->scale[a];
                     u.rank = p->arank[a];
-                    u.pad[0] = u.pad[1] = 0;
+                    u.a_rank = u.b_rank = 0;
                 }
 
     {
@@ -879,6 +898,7 @@ int lora_pool_load_unit(lora_pool *pool, int adapter, int layer, int expert, int
         pp.h = b ? pool->d.proj[proj].h_out : pool->d.proj[proj].h_in;
         pp.rank = pool->d.rank;
         pp.src_rank = pool->arank[adapter];
+        pp.rank_out = pool->rank_field(layer, adapter, expert, proj, b);
     }
     LORA_HIP(launch_pack_layer(ps, st));      // A and B in one launch
     return LORA_OK;
@@ -913,11 +933,14 @@ int lora_pool_load_adapter_layer(lora_pool *pool, int adapter, int layer, const 
         pp.h = pool->d.proj[j].h_in;
         pp.rank = pool->d.rank;
         pp.src_rank = r;
+        pp.rank_out = pool->rank_field(layer, adapter, 0, j, false);
+        pp.rank_stride = pool->d.n_proj * (int)(sizeof(Unit) / 4);
         ps.job[2 * j] = pp;
         off += (int64_t)pool->d.proj[j].h_in * r;
         pp.src = static_cast<const uint16_t *>(src) + off;
         pp.dst = reinterpret_cast<uint16_t *>(pool->slab + base + pool->B_off[j]);
         pp.h = pool->d.proj[j].h_out;
+        pp.rank_out = pool->rank_field(layer, adapter, 0, j, true);
         ps.job[2 * j + 1] = pp;
         off += (int64_t)pool->d.proj[j].h_out * r;
     }
@@ -937,6 +960,7 @@ int lora_pool_set_adapter(lora_pool *pool, int adapter, int rank, float scale, v
     LORA_HIP(launch_set_adapter(reinterpret_cast<Unit *>(pool->slab), pool->d.n_layers, pool->d.n_adapters,
                                 per_adapter, adapter, rank, scale, static_cast<hipStream_t>(stream)));
     pool->arank[adapter] = rank;
+    pool->note_ranks();
     pool->scale[adapter] = scale;
     for (int l = 0; l < pool->d.n_layers; ++l)
         for (int k = 0; k < per_adapter; ++k) {

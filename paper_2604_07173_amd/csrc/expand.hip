@@ -225,9 +225,10 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
             w.tl[k] = tiles[w.tix[k]];
         }
 
+        const typename Tile::Lanes lanes = Tile::lanes_of(lane, R);
         typename Tile::B b;
         int b_key = w.tl[0].key;
-        Tile::template load_b<false>(units[(int64_t)b_key * p.n_proj + p.proj0 + pj].B, chunk, lane, b);
+        Tile::template load_b<false, false>(units[(int64_t)b_key * p.n_proj + p.proj0 + pj].B, chunk, lanes, b);
 
         typename Wave::Rows rows[3];
         typename Wave::Data data[2];
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
             const int key = w.tl[q >> 1].key;
             if (key != b_key) {                                   // wave-uniform, rare
                 b_key = key;
-                Tile::template load_b<false>(units[(int64_t)key * p.n_proj + p.proj0 + pj].B, chunk, lane, b);
+                Tile::template load_b<false, false>(units[(int64_t)key * p.n_proj + p.proj0 + pj].B, chunk, lanes, b);
             }
             w.compute_store(rows[q % 3], data[q & 1], b);
         }

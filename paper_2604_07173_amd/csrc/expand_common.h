@@ -38,11 +38,27 @@ struct ExpandTile {
         return (g & 1) * 4;
     }
 
-    template <bool NT>
-    // (the chunk's address is the same for every lane: a scalar base and the lane's 32-bit offset)
-    __device__ static inline void load_b(const uint16_t *Bp, int chunk, int lane, B &b)
+    // This lane's offsets into a chunk for a matrix of which only the first `rank` entries are not zero: the others are
+    // not fetched.
+    struct Lanes {
+        unsigned off[KS];
+    };
+
+    __device__ static inline Lanes lanes_of(int lane, int rank)
     {
-        [[maybe_unused]] const unsigned g = lane >> 4, i16 = lane & 15;
+        const int g = lane >> 4, i16 = lane & 15;
+        Lanes l;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            l.off[ks] = jbase(g, ks) >= rank ? kOffNone : R >= 32 ? lane * 16u : ((R == 16 ? g : (g & 1)) * 16u + i16) * 16u;
+        return l;
+    }
+
+    // (the chunk's address is the same for every lane)
+    // LOW: only what `l` says is fetched; else all of it, with plain loads
+    template <bool NT, bool LOW>
+    __device__ static inline void load_b(const uint16_t *Bp, int chunk, const Lanes &l, B &b)
+    {
         const char *base = reinterpret_cast<const char *>(Bp) + (int64_t)chunk * (128 * R * 2);
         if constexpr (R >= 32) {
 #pragma unroll
@@ -50,7 +66,8 @@ struct ExpandTile {
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
                     const int at = (blk * KS + ks) * 1024;
-                    b.r[blk][ks] = ld16<NT>(base + (at & ~4095) + (unsigned)lane * 16u + (at & 4095));
+                    if (LOW) b.r[blk][ks] = ld16_packed<NT>(base, l.off[ks], at);
+                    else b.r[blk][ks] = ld16<NT>(base + (at & ~4095) + l.off[ks] + (at & 4095));
                 }
         } else {
             // one 16-byte load per pair of sub-blocks; rank 8: lane groups 2,3 re-read the
@@ -58,7 +75,7 @@ struct ExpandTile {
             constexpr int G = R / 4;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const u32x4 v = ld16<NT>(base + ((R == 16 ? g : (g & 1)) * 16u + i16) * 16u + q * G * 256);
+                const u32x4 v = LOW ? ld16_packed<NT>(base, l.off[0], q * G * 256) : ld16<NT>(base + l.off[0] + q * G * 256);
                 b.r[2 * q][0] = u32x2{v[0], v[1]};
                 b.r[2 * q + 1][0] = u32x2{v[2], v[3]};
             }

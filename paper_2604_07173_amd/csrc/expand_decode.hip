@@ -12,7 +12,7 @@ namespace {
 // tiles, units and counts are passed again as restrict-qualified kernel arguments: with a
 // wave-uniform index the compiler then reads them through the scalar cache, which shortens
 // the dependent chain tile -> unit -> first data load.
-template <int R, bool F32, bool OVW, bool YNT, int D, bool HALVES>
+template <int R, bool F32, bool OVW, bool YNT, int D, bool HALVES, bool LOW>
 __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
                                                           const lora_tile *__restrict__ tiles,
                                                           const Unit *__restrict__ units,
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
             if (t.n_rows <= 0) continue;
         }
         const Unit unit = units[(int64_t)t.key * p.n_proj + p.proj0 + pj];
-        expand_tile_chunks<R, F32, OVW, YNT, D>(p, q, t, unit, c0, c1, lane);
+        expand_tile_chunks<R, F32, OVW, YNT, D, LOW>(p, q, t, unit, c0, c1, lane);
         // A wave's last item ends here: no decoding of a next one.  Before another item the loads that the last chunks
         // repeated come in (vmcnt(0)), so that the compiler does not wait for them in the middle of the next item's first loads.
         if (item + nw >= ((n_tiles + (1 << gs) - 1) >> gs) * (per_tile << gs)) break;
@@ -64,8 +64,12 @@ __global__ __launch_bounds__(256, 2) void expand16_kernel(ExpandParams p,
 template <int R, bool F32, bool OVW, bool YNT, int D, bool HALVES>
 void launch_d(const ExpandParams &p, hipStream_t s)
 {
-    hipLaunchKernelGGL((expand16_kernel<R, F32, OVW, YNT, D, HALVES>), dim3(p.grid), dim3(p.waves * 64), 0, s, p, p.tiles,
-                       p.units, p.counts);
+    if (p.lower_ranks)
+        hipLaunchKernelGGL((expand16_kernel<R, F32, OVW, YNT, D, HALVES, true>), dim3(p.grid), dim3(p.waves * 64), 0, s, p,
+                           p.tiles, p.units, p.counts);
+    else
+        hipLaunchKernelGGL((expand16_kernel<R, F32, OVW, YNT, D, HALVES, false>), dim3(p.grid), dim3(p.waves * 64), 0, s, p,
+                           p.tiles, p.units, p.counts);
 }
 
 // HALVES (rank 16 only): a kernel of its own, because looking at the tile height at run time cost the

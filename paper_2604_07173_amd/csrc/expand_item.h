@@ -38,9 +38,14 @@ namespace lora {
 // are not in a cache when the call starts, or are too large to be).
 // BNT: B is loaded with the streaming hint (it is read once), else left in the L2 for the other tiles
 // of the segment.
+// LOW: the pool has adapters of a lower rank than its own, whose zeros are not fetched: a buffer load beyond the
+// buffer's records returns zeros without an access.  Layer call in us, everything fetched / not, half of the adapters with half
+// the pool's rank: Mixtral shapes, 512 tokens, rank 16 102.4 / 88.4, rank 32 170 / 140, llama shapes, 256 rows,
+// rank 64 137 / 122, ragged fp32 rows at rank 32 58.3 / 56.4, rank 8 (half lines of A) 49.0 / 48.6.  With adapters of the
+// pool's rank only, plain loads are ahead (64 tokens with the combine 43.7 against 44.1, fine-grained MoE 133.3 / 134.3).
 // D: chunks in flight per wave, one or two.  Two take the registers of a fifth wave per SIMD at rank 16
 // (the third at rank 64); the host picks (three or four for the small rank-8 chunks measured no faster).
-template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1>
+template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1, bool LOW = true>
 struct ExpandWave {
     using Tile = ExpandTile<R>;
     static constexpr int KS = Tile::KS;
@@ -53,13 +58,14 @@ struct ExpandWave {
 
     int lane, g, i16, h_out;
     const uint16_t *Bp;
+    typename Tile::Lanes at_b;
     char *yrow[NI];          // y rows of result registers 0..NI-1 (a valid row even if unused)
     bool rok[NI];            // whether result register i belongs to a row of the tile
     typename Tile::A a;
 
     __device__ inline void load(int c, typename Tile::B &b, YBuf &y) const
     {
-        Tile::template load_b<BNT>(Bp, c, lane, b);
+        Tile::template load_b<BNT, LOW>(Bp, c, at_b, b);
         load_y(c, y);
     }
 
@@ -120,7 +126,7 @@ struct ExpandWave {
     __device__ inline void prefetch_b(int c0, int c1, Stage (&st)[D]) const
     {
 #pragma unroll
-        for (int k = 0; k < D; ++k) Tile::template load_b<BNT>(Bp, min(c0 + k, c1 - 1), lane, st[k].b);
+        for (int k = 0; k < D; ++k) Tile::template load_b<BNT, LOW>(Bp, min(c0 + k, c1 - 1), at_b, st[k].b);
     }
 
     __device__ inline void prefetch_y(int c0, int c1, Stage (&st)[D]) const
@@ -147,13 +153,13 @@ struct ExpandWave {
     }
 };
 
-template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1>
+template <int R, bool F32, int NI, bool OVW, bool YNT, bool BNT, int D, bool LOW>
 __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, const lora_tile &t,
                                    const Unit &unit, int c0, int c1, int lane)
 {
     using Tile = ExpandTile<R>;
     constexpr int KS = Tile::KS, KV = Tile::KV, ESZ = F32 ? 4 : 2;
-    using Wave = ExpandWave<R, F32, NI, OVW, YNT, BNT, D>;
+    using Wave = ExpandWave<R, F32, NI, OVW, YNT, BNT, D, LOW>;
     Wave w;
     asm volatile("" : "+v"(lane));               // keeps what follows from the lane out of registers of the item loop
     w.lane = lane;
@@ -221,6 +227,7 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
     // the first chunks' weights and base output, behind the loads of v: only the output rows wait for
     // the row indices
     auto prefetch = [&] {
+        w.at_b = Tile::lanes_of(lane, LOW && unit.b_rank ? unit.b_rank : R);
         w.prefetch_b(c0, c1, st);
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -275,20 +282,20 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
 
 // one wave, one tile, chunks [c0, c1) of projection pj; the specialisation on the number of row
 // quads is picked here (wave-uniform)
-template <int R, bool F32, bool OVW, bool YNT, int D>
+template <int R, bool F32, bool OVW, bool YNT, int D, bool LOW>
 __device__ inline void expand_tile_chunks(const ExpandParams &p, const ExpandProj &pe, const lora_tile &t,
                                           const Unit &unit, int c0, int c1, int lane)
 {
     switch ((t.n_rows + 3) >> 2) {
-    case 1: expand_item<R, F32, 1, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane); break;
-    case 2: expand_item<R, F32, 2, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane); break;
-    case 3: expand_item<R, F32, 3, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane); break;
+    case 1: expand_item<R, F32, 1, OVW, YNT, true, D, LOW>(p, pe, t, unit, c0, c1, lane); break;
+    case 2: expand_item<R, F32, 2, OVW, YNT, true, D, LOW>(p, pe, t, unit, c0, c1, lane); break;
+    case 3: expand_item<R, F32, 3, OVW, YNT, true, D, LOW>(p, pe, t, unit, c0, c1, lane); break;
     default:
         // a full tile is most likely one of several of its segment: its B is worth keeping in the L2
         if (p.share_b && t.n_rows == kDecodeTileRows)
-            expand_item<R, F32, 4, OVW, YNT, false, D>(p, pe, t, unit, c0, c1, lane);
+            expand_item<R, F32, 4, OVW, YNT, false, D, LOW>(p, pe, t, unit, c0, c1, lane);
         else
-            expand_item<R, F32, 4, OVW, YNT, true, D>(p, pe, t, unit, c0, c1, lane);
+            expand_item<R, F32, 4, OVW, YNT, true, D, LOW>(p, pe, t, unit, c0, c1, lane);
         break;
     }
 }

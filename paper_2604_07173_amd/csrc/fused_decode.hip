@@ -106,6 +106,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
         out.i16 = w.i16;
         out.h_out = pe.h_out;
         out.Bp = unit.B;
+        out.at_b = Tile::lanes_of(w.lane, unit.b_rank ? unit.b_rank : R);
+        w.set_rank(unit.a_rank ? unit.a_rank : R);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * i + w.g;

@@ -27,6 +27,19 @@ __device__ inline u32x4 ld16(const void *p)
     return NT ? __builtin_nontemporal_load(q) : *q;
 }
 
+// 16 bytes at byte `off` of a packed matrix (plus `at`, the same for every lane), or zeros, without a memory access,
+// where `off` is kOffNone: a buffer load beyond the buffer's records returns zeros.  `base` must be the same for
+// every lane, and so must `fetch`: zeros for all of them if it is false.
+constexpr unsigned kOffNone = 0xFFFFFF00u;
+
+template <bool NT>
+__device__ inline u32x4 ld16_packed(const char *base, unsigned off, int at, bool fetch = true)
+{
+    __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, fetch ? 0x7FFFFFFF : 0, 0x00027000);
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, at, NT ? 2 : 0));
+}
+
 template <bool NT>
 __device__ inline void st16(void *p, u32x4 v)
 {

@@ -17,7 +17,9 @@ struct Unit {
     const uint16_t *B;  // packed expand operand of the unit
     float scale;        // the adapter's scale
     int32_t rank;       // the adapter's own rank (<= pool rank; the rest is zero padding)
-    int32_t pad[2];
+    // Rank of the adapter that A and B were last loaded with (0: not loaded yet): entries from there on are zeros in
+    // memory and the decode kernels don't fetch them.  Not `rank`, which lora_pool_set_adapter changes ahead of a load.
+    int32_t a_rank, b_rank;
 };
 static_assert(sizeof(Unit) == 32, "table entry is 32 bytes");
 
@@ -128,6 +130,8 @@ struct PackParams {
     int h;                   // h_in (A) or h_out (B)
     int rank;                // pool rank
     int src_rank;            // rank of the source matrices (<= rank)
+    int32_t *rank_out;       // where the first unit's table entry notes src_rank (repacks into the pool only)
+    int rank_stride;         // 32-bit words between consecutive units' entries
 };
 
 // all A and B repacks of one (adapter, layer) in one launch: job 2j = A, 2j+1 = B of projection j
@@ -196,6 +200,7 @@ struct ShrinkParams {
     };
     int wave_per_tile;       // decode kernel: every wave takes a whole tile (no K split across waves)
     int build;               // decode kernel: the segments are built inside the launch, from `seg`
+    int lower_ranks;         // decode kernel: the pool has adapters of a lower rank than its own
     int x_stream;            // decode kernel, K-split form: x rows loaded with the streaming hint (ranks 8, 16: as whole lines)
     SegParams seg;
 };
@@ -240,6 +245,7 @@ struct ExpandParams {
     int out_f32;
     int overwrite;           // decode kernel, bf16 output: write the update, do not read the rows
     int deep;                // decode kernel: two chunks in flight per wave, else one
+    int lower_ranks;         // decode kernel: the pool has adapters of a lower rank than its own
     int share_b;             // decode kernel: B of full tiles loaded without the streaming hint
     int y_stream;            // decode kernel: output rows read and written with the streaming hint
     int rank;

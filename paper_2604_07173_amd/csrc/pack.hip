@@ -156,6 +156,7 @@ __global__ __launch_bounds__(256) void pack_layer_kernel(PackLayerParams ps)
     const PackParams &p = ps.job[job];
     const int wg = blockIdx.x - ps.wg0[job];
     const int64_t gid = (int64_t)wg * 256 + threadIdx.x;
+    if (gid == 0) p.rank_out[(int64_t)blockIdx.y * p.rank_stride] = p.src_rank;
     if (!ps.aligned) {
         if (job & 1) pack_B_body<0>(p, gid, blockIdx.y);
         else pack_A_body<0>(p, gid, blockIdx.y);

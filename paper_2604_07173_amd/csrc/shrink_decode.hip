@@ -40,13 +40,13 @@ namespace {
 // whole application; with inputs that stay cached (4096 wide, or few rows) it costs 5-10 %.  Rank 32,
 // Mixtral shapes, 1024 tokens, streamed inputs that were just written: 266.0 -> 257.8 us (258.5 unstreamed).
 template <int R, int NPROJ, bool NT, bool WPT, bool BUILD = false, bool XNT = false, bool LINES = false,
-          bool HALVES = false>
+          bool HALVES = false, bool LOW = true>
 __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
                                                           const lora_tile *__restrict__ tiles,
                                                           const Unit *__restrict__ units,
                                                           const int32_t *__restrict__ counts)
 {
-    using Wave = ShrinkWave<R, NPROJ, NT, XNT, LINES>;
+    using Wave = ShrinkWave<R, NPROJ, NT, XNT, LINES, LOW>;
     constexpr int NACC = Wave::NACC, KU = Wave::KU;
     static_assert(!(BUILD && WPT), "the build needs the whole workgroup");
     static_assert(!(XNT && (BUILD || WPT)), "streamed x rows: K-split form without the build only");
@@ -98,9 +98,14 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
                 if (t.n_rows <= 0) continue;          // uniform over everyone who shares the item
             }
         }
+        int rank = 0;
 #pragma unroll
-        for (int pj = 0; pj < NPROJ; ++pj)
-            w.Ap[pj] = units[(int64_t)t.key * p.n_proj + p.proj0 + pj].A;
+        for (int pj = 0; pj < NPROJ; ++pj) {
+            const Unit &unit = units[(int64_t)t.key * p.n_proj + p.proj0 + pj];
+            w.Ap[pj] = unit.A;
+            rank = max(rank, LOW && unit.a_rank ? unit.a_rank : R);
+        }
+        w.set_rank(rank);
         const bool row_ok = w.i16 < t.n_rows;
         // Row indices: asked for here, looked at behind the first loads of A.  (Loads return in order, so the second
         // look-up has to be in front of those.)
@@ -188,33 +193,33 @@ __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
     }
 }
 
-template <int R, int NPROJ, bool HALVES>
+template <int R, int NPROJ, bool HALVES, bool LOW>
 void launch_form(const ShrinkParams &p, hipStream_t s)
 {
     if (p.wave_per_tile)
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, true, false, false, false, HALVES>), dim3(p.grid), dim3(256), 0,
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, true, false, false, false, HALVES, LOW>), dim3(p.grid), dim3(256), 0,
                            s, p, p.tiles, p.units, p.counts);
     else if (p.x_stream)       // large inputs that are read once: streamed, as whole lines where a step is 256 bytes of a row
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, true, (R <= 32), HALVES>), dim3(p.grid),
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, true, (R <= 32), HALVES, LOW>), dim3(p.grid),
                            dim3(256), 0, s, p, p.tiles, p.units, p.counts);
     else
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, false, false, HALVES>), dim3(p.grid), dim3(256),
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, false, false, false, HALVES, LOW>), dim3(p.grid), dim3(256),
                            0, s, p, p.tiles, p.units, p.counts);
 }
 
-template <int R, int NPROJ>
+template <int R, int NPROJ, bool LOW>
 hipError_t launch_rn(const ShrinkParams &p, hipStream_t s)
 {
     if (p.build) {
         if (p.wave_per_tile || p.seg.P > kInlineMaxRows || p.seg.n_adapters * (int64_t)p.seg.n_experts > kInlineMaxKeys)
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, true>), dim3(p.grid), dim3(256), 0, s, p,
+        hipLaunchKernelGGL((shrink16_kernel<R, NPROJ, true, false, true, false, false, false, LOW>), dim3(p.grid), dim3(256), 0, s, p,
                            p.tiles, p.units, p.counts);
     } else if (p.tile_halves) {
-        if constexpr (R == 16) launch_form<R, NPROJ, true>(p, s);
+        if constexpr (R == 16) launch_form<R, NPROJ, true, LOW>(p, s);
         else return hipErrorInvalidValue;             // the other ranks' 32-row tiles have kernels of their own
     } else {
-        launch_form<R, NPROJ, false>(p, s);
+        launch_form<R, NPROJ, false, LOW>(p, s);
     }
     return hipGetLastError();
 }
@@ -223,9 +228,9 @@ template <int R>
 hipError_t launch_r(const ShrinkParams &p, hipStream_t s)
 {
     switch (p.n_fused) {
-    case 1: return launch_rn<R, 1>(p, s);
-    case 2: return launch_rn<R, 2>(p, s);
-    case 3: return launch_rn<R, 3>(p, s);
+    case 1: return p.lower_ranks ? launch_rn<R, 1, true>(p, s) : launch_rn<R, 1, false>(p, s);
+    case 2: return p.lower_ranks ? launch_rn<R, 2, true>(p, s) : launch_rn<R, 2, false>(p, s);
+    case 3: return p.lower_ranks ? launch_rn<R, 3, true>(p, s) : launch_rn<R, 3, false>(p, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -33,7 +33,7 @@ namespace lora {
 // the row-wise writes and the operand-wise reads both touch every bank once.  Fetched in the operand
 // layout directly, an instruction reads 16 rows x 64 bytes: half a line per row, and the other half by
 // the next instruction.
-template <int R, int NPROJ, bool NT, bool XNT = false, bool LINES = false>
+template <int R, int NPROJ, bool NT, bool XNT = false, bool LINES = false, bool LOW = true>
 struct ShrinkWave {
     static constexpr int NB = R >= 16 ? R / 16 : 1;            // weight tiles per K unit
     static constexpr int XN = R == 8 ? 2 : 1;                  // x operands per K unit
@@ -50,7 +50,16 @@ struct ShrinkWave {
     const uint16_t *xp;      // this lane's x row (a valid row even if the lane's row is not)
     const uint16_t *xq[LINES ? NQ : 1];  // LINES: rows RPI * q + lane / PPR of the tile (valid rows likewise)
     u32x4 *xt;               // LINES: the wave's LDS, NQ KiB
+    unsigned a_off;          // this lane's place in a block, or kOffNone: its rank entry is beyond the adapter's rank
+    int a_rank;
     f32x4 acc[NPROJ][NACC];
+
+    // LOW: rank entries from `rank` on are zeros in memory and are not fetched: lanes at ranks 8 and 16, blocks above.
+    __device__ inline void set_rank(int rank)
+    {
+        a_rank = rank;
+        a_off = R >= 32 || (R == 8 ? i16 & 7 : i16) < rank ? lane * 16u : kOffNone;
+    }
 
     struct Step {
         u32x4 w[NPROJ][KB][NB];
@@ -69,16 +78,18 @@ struct ShrinkWave {
 
     __device__ inline void load_a(int kb0, int kb_end, Step &s) const
     {
-        unsigned off = (unsigned)lane * 16u;
-        asm volatile("" : "+v"(off));        // a 32-bit offset on a scalar base: not widened ahead of time
+        unsigned off = LOW ? 0u : (unsigned)lane * 16u;
+        if (!LOW) asm volatile("" : "+v"(off));        // a 32-bit offset on a scalar base: not widened ahead of time
 #pragma unroll
-        for (int u = 0; u < KB; ++u) {
-            const int kb = min(kb0 + u, kb_end - 1);
+        for (int pj = 0; pj < NPROJ; ++pj) {
+            const char *base = reinterpret_cast<const char *>(Ap[pj]) + (int64_t)kb0 * (NB * 1024);
 #pragma unroll
-            for (int pj = 0; pj < NPROJ; ++pj) {
-                const char *base = reinterpret_cast<const char *>(Ap[pj]) + (int64_t)kb * (NB * 1024);
+            for (int u = 0; u < KB; ++u) {
+                const int at = min(u, kb_end - 1 - kb0) * (NB * 1024);
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) s.w[pj][u][nb] = ld16<NT>(base + off + nb * 1024);
+                for (int nb = 0; nb < NB; ++nb)
+                    if (LOW) s.w[pj][u][nb] = ld16_packed<NT>(base, a_off, at + nb * 1024, nb * 16 < a_rank);
+                    else s.w[pj][u][nb] = ld16<NT>(base + at + off + nb * 1024);
             }
         }
     }

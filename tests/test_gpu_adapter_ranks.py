@@ -1,0 +1,106 @@
+"""Adapters of a lower rank than their pool's: the kernels fetch only the entries that were loaded.  Against a pool that
+was loaded with the same matrices padded with zeros to the pool's rank, where everything is fetched: bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_07173_amd as L
+
+pytestmark = pytest.mark.gpu
+
+H = (328, 392)
+
+
+def pools(rank, ranks, h_in, h_out, E=1):
+    """The two pools (own ranks, padded) over the same random matrices, and the sources per adapter."""
+    n = len(ranks)
+    out, src = [], []
+    g = torch.Generator(device="cuda").manual_seed(rank)
+    for r in ranks:
+        parts, full = [], []
+        for _ in range(E):
+            for _ in range(2):
+                A = torch.randn(h_in, r, generator=g, device="cuda").bfloat16()
+                B = torch.randn(r, h_out, generator=g, device="cuda").bfloat16()
+                parts += [A.flatten(), B.flatten()]
+                full += [torch.nn.functional.pad(A, (0, rank - r)).flatten(),
+                         torch.nn.functional.pad(B, (0, 0, 0, rank - r)).flatten()]
+        src.append((torch.cat(parts), torch.cat(full)))
+    for k in range(2):
+        d = L.PoolDesc(n, 1, E, [(h_in, h_out)] * 2, rank, scale=[1.5] * n, adapter_rank=ranks if k == 0 else None)
+        slab = torch.empty(L.lora_pool_bytes(d), dtype=torch.uint8, device="cuda")
+        pool = L.lora_register_pool(d, slab)
+        for a in range(n):
+            L.lora_pool_load_adapter_layer(pool, a, 0, src[a][k])
+        out.append((pool, slab))
+    return out, src
+
+
+def call(pool, aid, x, h_out, build, f32=False):
+    P = aid.numel()
+    seg = L.Segments(P)
+    y = [torch.zeros(P, h_out, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda") for _ in range(2)]
+    ws = torch.empty(L.lora_group_ws_bytes(pool, 0, 2, P), dtype=torch.uint8, device="cuda")
+    dt = L.LORA_DTYPE_F32 if f32 else L.LORA_DTYPE_BF16
+    if build:
+        L.lora_build_apply_group(pool, 0, 0, x, x.shape[1], None, aid, None, P, seg, y, [h_out] * 2, ws, dt)
+    else:
+        L.lora_build_segments(pool, aid, None, P, seg)
+        L.lora_apply_group(pool, 0, 0, x, x.shape[1], None, seg, y, [h_out] * 2, ws, dt)
+    torch.cuda.synchronize()
+    return torch.stack(y)
+
+
+def batch(n, P, h_in):
+    g = torch.Generator(device="cuda").manual_seed(P)
+    return (torch.randint(0, n, (P,), generator=g, device="cuda", dtype=torch.int32),
+            torch.randn(P, h_in, generator=g, device="cuda").bfloat16())
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64])
+@pytest.mark.parametrize("P,h_in,h_out,build,policy", [
+    (9, 328, 392, True, L.LORA_ACT_AUTO),            # shrink and expand in one launch
+    (300, 328, 1032, True, L.LORA_ACT_AUTO), (300, 1032, 392, False, L.LORA_ACT_STREAMING),
+    (6000, 136, 264, False, L.LORA_ACT_AUTO),        # ranks 8 and 16: a wave per tile of thousands; above: long segments
+    (12000, 136, 264, False, L.LORA_ACT_AUTO)])
+def test_lower_ranks_equal_padded_sources(rank, P, h_in, h_out, build, policy):
+    ranks = sorted({rank, rank // 2, rank // 4, 1, 3, rank // 2 + 1, rank - 1})
+    (a, b), _ = pools(rank, ranks, h_in, h_out)
+    aid, x = batch(len(ranks), P, h_in)
+    for pool, _ in (a, b):
+        L.lora_pool_set_activation_policy(pool, policy)
+    for f32 in (False, True):
+        assert torch.equal(call(a[0], aid, x, h_out, build, f32), call(b[0], aid, x, h_out, build, f32))
+
+
+@pytest.mark.parametrize("rank", [16, 64])
+def test_a_slot_between_set_adapter_and_its_load(rank):
+    """lora_pool_set_adapter leaves the packed matrices alone: until the next load a call sees all of the old ones."""
+    ranks = [rank, rank // 2]
+    (a, _), src = pools(rank, ranks, *H)
+    pool = a[0]
+    aid, x = batch(2, 40, H[0])
+    before = call(pool, aid, x, H[1], True)
+    L.lora_pool_set_adapter(pool, 0, 1, 1.5)
+    L.lora_pool_set_adapter(pool, 1, rank, 1.5)
+    assert torch.equal(call(pool, aid, x, H[1], True), before)
+    # slot 0 takes the other adapter at its own rank, slot 1 the first one
+    L.lora_pool_set_adapter(pool, 0, rank // 2, 1.5)
+    L.lora_pool_load_adapter_layer(pool, 0, 0, src[1][0])
+    L.lora_pool_load_adapter_layer(pool, 1, 0, src[0][0])
+    assert torch.equal(call(pool, 1 - aid, x, H[1], True), before)
+
+
+def test_units_of_one_adapter_loaded_one_by_one():
+    """lora_pool_load_unit notes the rank of the one projection it loads."""
+    rank = 32
+    (a, b), src = pools(rank, [32, 16], *H)
+    aid, x = batch(2, 60, H[0])
+    n = H[0] * 16
+    A, B = src[1][0][:n].clone(), src[1][0][n:n + 16 * H[1]].clone()
+    for pool, r in ((a[0], 16), (b[0], 32)):
+        A1 = A if r == 16 else torch.nn.functional.pad(A.view(H[0], 16), (0, 16)).flatten().contiguous()
+        B1 = B if r == 16 else torch.nn.functional.pad(B.view(16, H[1]), (0, 0, 0, 16)).flatten().contiguous()
+        L.lora_pool_set_adapter(pool, 0, r, 1.5)
+        L.lora_pool_load_unit(pool, 0, 0, 0, 1, A1, B1)          # projection 1 of slot 0 only; projection 0 keeps rank 32
+    assert torch.equal(call(a[0], aid, x, H[1], False), call(b[0], aid, x, H[1], False))
