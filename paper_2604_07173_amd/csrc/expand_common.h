@@ -82,9 +82,12 @@ struct ExpandTile {
         }
     }
 
-    // KV fp32 values (already summed and scaled) -> this lane's part of the operand
+    // KV fp32 values (already summed and scaled) -> this lane's part of the operand.  Not contracted: where the
+    // caller's product with the scale is known to be used for every lane it would go into the difference below, and a full
+    // tile's rows would be rounded differently from those of a shorter one.
     __device__ static inline void make_a(const float (&s)[KV], int g, int ks, A &a)
     {
+#pragma clang fp contract(off)
         unsigned hi[KV / 2], lo[KV / 2];
 #pragma unroll
         for (int m = 0; m < KV / 2; ++m) {

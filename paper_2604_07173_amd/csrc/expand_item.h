@@ -182,11 +182,12 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
     // beyond the last re-reads the last one and counts as zero.
     //
     // Loads return in order, so parts that are fetched behind the first chunks wait for those as well:
-    // one round trip more for every batch after the first.  Therefore the eight parts a decode
-    // shrink has at most come in one batch at ranks 8 and 16 (in two for taller tiles above), and where a tile
-    // has at most four (eight) rows, the four (two) lanes of a quad whose row slots share the lane's tile row or are
-    // empty fetch a part each; their sums meet on the cross-lane data path.  The order of the sum is
-    // fixed: per lane in ascending order, then the lanes.
+    // one round trip more for every batch after the first.  Therefore a batch is PB * PQ parts: where a tile has at most
+    // four (eight) rows, the four (two) lanes of a quad whose row slots share the lane's tile row or are empty
+    // fetch a part each.  Batches that eight parts (a decode shrink has no more) come in: one for tiles of up to four rows;
+    // for up to eight rows one at ranks 8 to 32, two at rank 64 (four with fp32 output); above two, at rank 64 four (eight).
+    // Every lane of the quad adds all parts in ascending order through the cross-lane data path, so a row's sum is the
+    // same in tiles of every height.
     constexpr int PQ = NI == 1 ? 4 : NI == 2 ? 2 : 1;            // parts per round, one per lane of a row
     constexpr int PB = R <= 32 ? (NI == 1 ? 2 : 4) : NI == 1 ? 2 : (F32 ? 1 : 2);      // registers permitting
     const int slot = w.i16;
@@ -220,7 +221,13 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
 #pragma unroll
                 for (int h = 0; h < KV / 4; ++h)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) s[ks][4 * h + q] += in ? buf[u][ks][h][q] : 0.f;
+                    for (int q = 0; q < 4; ++q) {
+                        const float x = in ? buf[u][ks][h][q] : 0.f;
+                        float &to = s[ks][4 * h + q];
+                        if (PQ == 1) to += x;
+                        if (PQ == 2) to = (to + quad_lane<0x44>(x)) + quad_lane<0xEE>(x);
+                        if (PQ == 4) to = (((to + quad_lane<0x00>(x)) + quad_lane<0x55>(x)) + quad_lane<0xAA>(x)) + quad_lane<0xFF>(x);
+                    }
         }
     };
     typename Wave::Stage st[D];
@@ -262,13 +269,6 @@ __device__ inline void expand_item(const ExpandParams &p, const ExpandProj &pe, 
             load_v(part0, vbuf);
             add_v(part0, vbuf);
         }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int q = 0; q < KV; ++q) {
-                if (PQ >= 2) s[ks][q] += quad_lane<0x4E>(s[ks][q]);          // lane ^ 2
-                if (PQ == 4) s[ks][q] += quad_lane<0xB1>(s[ks][q]);          // lane ^ 1
-            }
     }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {

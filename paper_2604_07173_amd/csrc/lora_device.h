@@ -62,7 +62,7 @@ __device__ inline unsigned pack_bf16_rne(float lo, float hi)
 template <int CTRL>
 __device__ inline float quad_lane(float x)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
 }  // namespace lora

@@ -44,3 +44,33 @@ def test_parts_and_tile_heights(rank, parts):
         xa = W.bf16_bits_to_f32(b.inputs["x"][r]).astype(np.float64)
         bound = b.scale[a] * (2.0 ** -16 * np.abs(xa @ A) + 4 * h_in ** 0.5 * 2.0 ** -24 * (np.abs(xa) @ np.abs(A))) @ np.abs(B)
         assert (np.abs(got[r] - want[r]) <= bound).all()
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64])
+@pytest.mark.parametrize("parts", [2, 3, 5, 8])
+def test_bits_of_a_row_do_not_depend_on_its_tile(rank, parts):
+    """A row's update does not depend on the rows that travel with it: the same row under the same weights has the
+    same bits in tiles of every height, whichever lanes fetched its parts of v."""
+    h_in, h_out = parts * 4 * (64 if rank == 8 else 32), 264
+    n, P = len(HEIGHTS), sum(HEIGHTS)
+    g = torch.Generator(device="cuda").manual_seed(rank + parts)
+    weights = torch.randn((h_in + h_out) * rank, generator=g, device="cuda").bfloat16()
+    desc = L.PoolDesc(n, 1, 1, [(h_in, h_out)], rank, scale=[1.25] * n)
+    slab = torch.empty(L.lora_pool_bytes(desc), dtype=torch.uint8, device="cuda")
+    pool = L.lora_register_pool(desc, slab)
+    for a in range(n):
+        L.lora_pool_load_adapter_layer(pool, a, 0, weights)
+    aid = torch.from_numpy(np.random.default_rng(7).permutation(np.repeat(np.arange(n), HEIGHTS)).astype(np.int32)).cuda()
+    x = torch.randn(1, h_in, generator=g, device="cuda").bfloat16().repeat(P, 1)
+    seg = L.Segments(P)
+    L.lora_build_segments(pool, aid, None, P, seg)
+    size = L.lora_v_bytes(pool, 0, P)
+    assert size == -(-parts * P * rank * 4 // 256) * 256
+    v = torch.full((size // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    y = torch.zeros(P, h_out, dtype=torch.float32, device="cuda")
+    L.lora_shrink(pool, 0, 0, x, h_in, None, seg, v)
+    L.lora_expand(pool, 0, 0, v, seg, y, h_out, L.LORA_DTYPE_F32)
+    assert bool(y[0].any())
+    differ = (y != y[0]).any(dim=1).cpu().numpy()
+    heights = np.repeat(HEIGHTS, HEIGHTS)[np.argsort(np.argsort(aid.cpu().numpy(), kind="stable"), kind="stable")]
+    assert not differ.any(), sorted(set(heights[differ].tolist()))
