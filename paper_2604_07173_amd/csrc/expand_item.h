@@ -45,7 +45,7 @@ namespace lora {
 // pool's rank only, plain loads are ahead (64 tokens with the combine 43.7 against 44.1, fine-grained MoE 133.3 / 134.3).
 // D: chunks in flight per wave, one or two.  Two take the registers of a fifth wave per SIMD at rank 16
 // (the third at rank 64); the host picks (three or four for the small rank-8 chunks measured no faster).
-template <int R, bool F32, int NI, bool OVW, bool YNT = false, bool BNT = true, int D = 1, bool LOW = true>
+template <int R, bool F32, int NI, bool OVW, bool YNT, bool BNT, int D, bool LOW>
 struct ExpandWave {
     using Tile = ExpandTile<R>;
     static constexpr int KS = Tile::KS;

@@ -38,15 +38,16 @@ namespace {
 // BUILD: the segments are not there yet either; every workgroup sorts the batch for itself in LDS
 // first (segments_inline.h), workgroup 0 writes the segments out, and the whole layer call of a
 // small batch is this one launch.
-template <int R, bool BUILD>
+// LOW: as in the two-launch kernels, for pools with adapters of a lower rank than their own.
+template <int R, bool BUILD, bool LOW>
 __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p,
                                                          const lora_tile *__restrict__ tiles,
                                                          const Unit *__restrict__ units,
                                                          const int32_t *__restrict__ counts)
 {
     constexpr int NW = kFusedWaves;
-    using Wave = ShrinkWave<R, 1, false>;
-    using Out = ExpandWave<R, false, 4, false>;
+    using Wave = ShrinkWave<R, 1, false, false, false, LOW>;
+    using Out = ExpandWave<R, false, 4, false, false, true, 1, LOW>;
     using Tile = ExpandTile<R>;
     constexpr int NACC = Wave::NACC, KU = Wave::KU, KS = Tile::KS, KV = Tile::KV, ESZ = Out::ESZ;
     union Scratch {                   // the build's counts are dead before the first sums are added
@@ -106,8 +107,8 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
         out.i16 = w.i16;
         out.h_out = pe.h_out;
         out.Bp = unit.B;
-        out.at_b = Tile::lanes_of(w.lane, unit.b_rank ? unit.b_rank : R);
-        w.set_rank(unit.a_rank ? unit.a_rank : R);
+        out.at_b = Tile::lanes_of(w.lane, LOW && unit.b_rank ? unit.b_rank : R);
+        w.set_rank(LOW && unit.a_rank ? unit.a_rank : R);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int r = 4 * i + w.g;
@@ -161,17 +162,17 @@ __global__ __launch_bounds__(64 * kFusedWaves) void fused16_kernel(FusedParams p
     }
 }
 
-template <int R>
+template <int R, bool LOW>
 hipError_t launch_r(const FusedParams &p, hipStream_t s)
 {
     constexpr int kThreads = 64 * kFusedWaves;
     if (p.s.build) {
         if (p.s.seg.P > kInlineMaxRows || p.s.seg.n_adapters * (int64_t)p.s.seg.n_experts > kInlineMaxKeys)
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL((fused16_kernel<R, true>), dim3(p.s.grid), dim3(kThreads), 0, s, p, p.s.tiles,
+        hipLaunchKernelGGL((fused16_kernel<R, true, LOW>), dim3(p.s.grid), dim3(kThreads), 0, s, p, p.s.tiles,
                            p.s.units, p.s.counts);
     } else {
-        hipLaunchKernelGGL((fused16_kernel<R, false>), dim3(p.s.grid), dim3(kThreads), 0, s, p, p.s.tiles,
+        hipLaunchKernelGGL((fused16_kernel<R, false, LOW>), dim3(p.s.grid), dim3(kThreads), 0, s, p, p.s.tiles,
                            p.s.units, p.s.counts);
     }
     return hipGetLastError();
@@ -183,10 +184,10 @@ hipError_t launch_fused_decode(const FusedParams &p, hipStream_t s)
 {
     if (p.s.grid <= 0) return hipSuccess;
     switch (p.s.rank) {
-    case 8: return launch_r<8>(p, s);
-    case 16: return launch_r<16>(p, s);
-    case 32: return launch_r<32>(p, s);
-    case 64: return launch_r<64>(p, s);
+    case 8: return p.s.lower_ranks ? launch_r<8, true>(p, s) : launch_r<8, false>(p, s);
+    case 16: return p.s.lower_ranks ? launch_r<16, true>(p, s) : launch_r<16, false>(p, s);
+    case 32: return p.s.lower_ranks ? launch_r<32, true>(p, s) : launch_r<32, false>(p, s);
+    case 64: return p.s.lower_ranks ? launch_r<64, true>(p, s) : launch_r<64, false>(p, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -39,8 +39,7 @@ namespace {
 // rows of the Mixtral down projection 48.5 -> 41.7 us, of the Llama one 60.9 -> 51.0 us for the
 // whole application; with inputs that stay cached (4096 wide, or few rows) it costs 5-10 %.  Rank 32,
 // Mixtral shapes, 1024 tokens, streamed inputs that were just written: 266.0 -> 257.8 us (258.5 unstreamed).
-template <int R, int NPROJ, bool NT, bool WPT, bool BUILD = false, bool XNT = false, bool LINES = false,
-          bool HALVES = false, bool LOW = true>
+template <int R, int NPROJ, bool NT, bool WPT, bool BUILD, bool XNT, bool LINES, bool HALVES, bool LOW>
 __global__ __launch_bounds__(256, 2) void shrink16_kernel(ShrinkParams p,
                                                           const lora_tile *__restrict__ tiles,
                                                           const Unit *__restrict__ units,

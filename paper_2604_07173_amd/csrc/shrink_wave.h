@@ -33,7 +33,7 @@ namespace lora {
 // the row-wise writes and the operand-wise reads both touch every bank once.  Fetched in the operand
 // layout directly, an instruction reads 16 rows x 64 bytes: half a line per row, and the other half by
 // the next instruction.
-template <int R, int NPROJ, bool NT, bool XNT = false, bool LINES = false, bool LOW = true>
+template <int R, int NPROJ, bool NT, bool XNT, bool LINES, bool LOW>
 struct ShrinkWave {
     static constexpr int NB = R >= 16 ? R / 16 : 1;            // weight tiles per K unit
     static constexpr int XN = R == 8 ? 2 : 1;                  // x operands per K unit

@@ -104,3 +104,17 @@ def test_units_of_one_adapter_loaded_one_by_one():
         L.lora_pool_set_adapter(pool, 0, r, 1.5)
         L.lora_pool_load_unit(pool, 0, 0, 0, 1, A1, B1)          # projection 1 of slot 0 only; projection 0 keeps rank 32
     assert torch.equal(call(a[0], aid, x, H[1], False), call(b[0], aid, x, H[1], False))
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64])
+@pytest.mark.parametrize("P,h_in,h_out,build", [(9, 328, 392, True), (9, 328, 392, False), (300, 1032, 392, True),
+                                                (300, 1032, 392, False)])
+def test_pools_of_one_rank_do_not_look_at_the_notes(rank, P, h_in, h_out, build):
+    """Every adapter has the pool's rank: the kernels, that of shrink and expand in one launch included, are the
+    ones that load without asking which rank a unit was loaded with."""
+    (a, b), _ = pools(rank, [rank] * 5, h_in, h_out)
+    aid, x = batch(5, P, h_in)
+    words = a[1].view(torch.int32)[:5 * 2 * 8].view(-1, 8)       # the table's entries: A, B, scale, rank, a_rank, b_rank
+    assert bool((words[:, 5:] == rank).all())
+    words[:, 6:] = 1
+    assert torch.equal(call(a[0], aid, x, h_out, build), call(b[0], aid, x, h_out, build))
