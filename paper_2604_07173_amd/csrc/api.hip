@@ -6,13 +6,13 @@
 #include <string.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <mutex>
 #include <new>
 #include <string>
 #include <vector>
 
+#include "adapter_ranks.h"
 #include "lora_internal.h"
 
 using namespace lora;
@@ -115,7 +115,7 @@ struct lora_pool {
     uint32_t magic;
     lora_pool_desc d;
     std::vector<float> scale;
-    std::vector<int32_t> arank;
+    AdapterRanks arank;                   // the decode kernels look at the units' ranks if any is below the pool's
     char *slab;
     size_t slab_bytes;
     size_t table_bytes;
@@ -124,9 +124,6 @@ struct lora_pool {
     size_t B_off[LORA_MAX_PROJ], B_bytes[LORA_MAX_PROJ];
     std::vector<Unit> table;              // host mirror of the device table
     std::vector<hipEvent_t> ready;        // [adapter][layer], created at the first async load
-    // An adapter's rank is below the pool's: the decode kernels look at the ranks.  Atomic, because a call on one thread
-    // may read it while another gives a slot a new rank; results are the same either way.
-    std::atomic<bool> lower_ranks;
     int act_policy;                       // LORA_ACT_*: cache hints of the activation streams
 
     size_t unit_base(int layer, int adapter, int expert) const
@@ -137,12 +134,6 @@ struct lora_pool {
     size_t table_index(int layer, int adapter, int expert, int proj) const
     {
         return (((size_t)layer * d.n_adapters + adapter) * d.n_experts + expert) * d.n_proj + proj;
-    }
-    void note_ranks()
-    {
-        bool any = false;
-        for (int32_t r : arank) any = any || r < d.rank;
-        lower_ranks.store(any, std::memory_order_relaxed);
     }
     const Unit *device_table() const { return reinterpret_cast<const Unit *>(slab); }
     // a_rank or b_rank of a unit's entry in the device table
@@ -438,7 +429,7 @@ ShrinkParams shrink_params(const lora_pool *pool, int layer, const Group &g, con
     sp.parts = fast_div(ks.n_parts);
     sp.kb_per_part = ks.kb_per_part;
     sp.rank = pool->d.rank;
-    sp.lower_ranks = pool->lower_ranks.load(std::memory_order_relaxed);
+    sp.lower_ranks = pool->arank.any_lower();
     if (!long_kernels(pool, seg->P, seg->tile_rows)) {
         sp.tile_halves = seg->tile_rows == kTileRows;
         const int64_t items = ks.n_parts * (sp.tile_halves ? 2 * tiles_upper_bound(pool, seg->P, kTileRows)
@@ -532,7 +523,7 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     ep.counts = seg->counts;
     ep.out_f32 = out_dtype == LORA_DTYPE_F32;
     ep.rank = pool->d.rank;
-    ep.lower_ranks = pool->lower_ranks.load(std::memory_order_relaxed);
+    ep.lower_ranks = pool->arank.any_lower();
     const bool decode = !long_kernels(pool, seg->P, seg->tile_rows);
     const int64_t tub = std::max<int64_t>(1, tiles_upper_bound(pool, seg->P, decode ? kDecodeTileRows : kTileRows));
     if (decode) {
@@ -809,9 +800,7 @@ int lora_register_pool(const lora_pool_desc *d, void *slab, size_t slab_bytes,
     p->d = *d;
     p->scale.assign(d->n_adapters, 1.0f);
     if (d->scale) p->scale.assign(d->scale, d->scale + d->n_adapters);
-    p->arank.assign(d->n_adapters, d->rank);
-    if (d->adapter_rank) p->arank.assign(d->adapter_rank, d->adapter_rank + d->n_adapters);
-    p->note_ranks();
+    p->arank.init(d->rank, d->n_adapters, d->adapter_rank);
     p->d.scale = nullptr;
     p->d.adapter_rank = nullptr;
     p->slab = static_cast<char *>(slab);
@@ -959,8 +948,7 @@ int lora_pool_set_adapter(lora_pool *pool, int adapter, int rank, float scale, v
     const int per_adapter = pool->d.n_experts * pool->d.n_proj;
     LORA_HIP(launch_set_adapter(reinterpret_cast<Unit *>(pool->slab), pool->d.n_layers, pool->d.n_adapters,
                                 per_adapter, adapter, rank, scale, static_cast<hipStream_t>(stream)));
-    pool->arank[adapter] = rank;
-    pool->note_ranks();
+    pool->arank.set(adapter, rank);
     pool->scale[adapter] = scale;
     for (int l = 0; l < pool->d.n_layers; ++l)
         for (int k = 0; k < per_adapter; ++k) {
