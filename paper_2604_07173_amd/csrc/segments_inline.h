@@ -32,8 +32,11 @@ constexpr int kInlineMaxKeys = 256;
 constexpr int kInlineGroups = kInlineMaxRows / 64;
 constexpr int kInlineKeyWaves = kInlineMaxKeys / 64;             // waves whose threads own a key
 
+// rows of every key per group of 64 rows; cleared with 16-byte stores
 template <int GROUPS>
-using SortCounts = uint16_t[GROUPS][kInlineMaxKeys];
+struct alignas(16) SortCounts {
+    uint16_t n[GROUPS][kInlineMaxKeys];
+};
 typedef SortCounts<kInlineGroups> InlineCounts;                   // 16 KiB, free again after the build
 
 // TILES: room for the tile records, which otherwise go straight to the caller's segments
@@ -60,6 +63,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, Counts &coun
     constexpr int GPW = (G + NW - 1) / NW;              // groups per wave; those beyond the batch are empty
     static_assert(NW >= kInlineKeyWaves, "a thread per key");
     static_assert(G % NW == 0 || G < NW, "the waves' groups are the first G");
+    static_assert(alignof(Counts) >= sizeof(u32x4), "cleared with 16-byte stores");
 
     // ids of this wave's groups (wave w takes groups w, w + NW, ...): all loads first
     int a[GPW], e[GPW];
@@ -73,7 +77,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, Counts &coun
     }
     {
         const u32x4 zero = {0u, 0u, 0u, 0u};
-        u32x4 *c4 = reinterpret_cast<u32x4 *>(&counts[0][0]);
+        u32x4 *c4 = reinterpret_cast<u32x4 *>(&counts.n[0][0]);
         for (int i = tid; i < G * (kInlineMaxKeys * 2 / 16); i += 64 * NW) c4[i] = zero;
         if (tid == 0) L.status = 0;
     }
@@ -106,7 +110,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, Counts &coun
     for (int u = 0; u < GPW; ++u) {
         const int g = w + NW * u;                           // wave-uniform
         below[u] = lanes_below(m[u]);
-        if (key[u] != kNoKey && below[u] == 0) counts[g][key[u]] = (uint16_t)(__popc(m[u].lo) + __popc(m[u].hi));
+        if (key[u] != kNoKey && below[u] == 0) counts.n[g][key[u]] = (uint16_t)(__popc(m[u].lo) + __popc(m[u].hi));
     }
     if (bad) atomicOr(&L.status, bad);                      // OR is order-independent
     __syncthreads();
@@ -117,10 +121,10 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, Counts &coun
     if (owner) {
         unsigned c[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) c[g] = counts[g][tid];
+        for (int g = 0; g < G; ++g) c[g] = counts.n[g][tid];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            counts[g][tid] = (uint16_t)total;
+            counts.n[g][tid] = (uint16_t)total;
             total += c[g];
         }
         my_tiles = (total + TR - 1) / TR;
@@ -198,7 +202,7 @@ __device__ inline void build_segments_inline_n(const SegParams &sp, Counts &coun
     for (int u = 0; u < GPW; ++u) {
         const int g = w + NW * u;
         if (key[u] != kNoKey)
-            L.perm[L.key_start[key[u]] + counts[g][key[u]] + below[u]] = (uint16_t)(g * 64 + lane);
+            L.perm[L.key_start[key[u]] + counts.n[g][key[u]] + below[u]] = (uint16_t)(g * 64 + lane);
     }
     __syncthreads();
 
