@@ -203,8 +203,10 @@ int lora_pool_unit_layout(const lora_pool *pool, int adapter, int layer, int exp
                           size_t *A_offset, size_t *A_bytes, size_t *B_offset, size_t *B_bytes,
                           int32_t *rank, float *scale);
 
-/* Device address of the table (entries of 32 bytes: A*, B*, float scale, int32 rank, pad),
- * ordered [layer][adapter][expert][proj]. */
+/* Device address of the table (entries of 32 bytes: A*, B*, float scale, int32 rank, int32 a_rank, int32 b_rank),
+ * ordered [layer][adapter][expert][proj].  a_rank, b_rank: the rank the load calls last filled the unit's A and B with,
+ * 0 before the first load.  Where a pool has adapters of a lower rank than its own, the kernels take the entries from
+ * there on for zeros without reading them.  So only the load calls may fill a unit, as they alone write the slab. */
 const void *lora_pool_device_table(const lora_pool *pool);
 
 int lora_pool_destroy(lora_pool *pool);

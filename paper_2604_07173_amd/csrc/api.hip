@@ -578,11 +578,11 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         ep.waves = 4;
         // with many rows per (adapter, expert) a segment spans several tiles: let neighbouring
         // waves take neighbouring tiles, so that they share the segment's B through the L2
-        static const int tile_group = tune_int("LORA_DEC_EXPAND_TILE_GROUP", 0, 0, 4);     // 1, 2 or 4
+        static const int tile_group = tune_int("LORA_DEC_EXPAND_TILE_GROUP", 0, 0, 4);     // 1, 2 (also for 3) or 4
         const int64_t n_keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
         const bool long_segments = seg->P >= 8 * n_keys;
-        const int group = tile_group ? tile_group : (long_segments ? 2 : 1);
-        ep.group_shift = group / 2;
+        ep.group_shift = (tile_group ? tile_group : (long_segments ? 2 : 1)) / 2;
+        const int group = 1 << ep.group_shift;
         ep.group_items = fast_div(ep.per_tile << ep.group_shift);
         // ... and keep the B of full tiles in the L2 (the other tiles' is read once and streamed):
         // Mixtral shapes, 2048 tokens, 255.2 -> 247.2 us at rank 16, 375 -> 355 at rank 32; llama shapes,
