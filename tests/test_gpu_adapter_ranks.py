@@ -17,15 +17,10 @@ def pools(rank, ranks, h_in, h_out, E=1):
     out, src = [], []
     g = torch.Generator(device="cuda").manual_seed(rank)
     for r in ranks:
-        parts, full = [], []
-        for _ in range(E):
-            for _ in range(2):
-                A = torch.randn(h_in, r, generator=g, device="cuda").bfloat16()
-                B = torch.randn(r, h_out, generator=g, device="cuda").bfloat16()
-                parts += [A.flatten(), B.flatten()]
-                full += [torch.nn.functional.pad(A, (0, rank - r)).flatten(),
-                         torch.nn.functional.pad(B, (0, 0, 0, rank - r)).flatten()]
-        src.append((torch.cat(parts), torch.cat(full)))
+        A = torch.randn(E, 2, h_in, r, generator=g, device="cuda").bfloat16()
+        B = torch.randn(E, 2, r, h_out, generator=g, device="cuda").bfloat16()
+        full = (torch.nn.functional.pad(A, (0, rank - r)), torch.nn.functional.pad(B, (0, 0, 0, rank - r)))
+        src.append(tuple(torch.cat([m.flatten(2) for m in two], 2).flatten() for two in ((A, B), full)))
     for k in range(2):
         d = L.PoolDesc(n, 1, E, [(h_in, h_out)] * 2, rank, scale=[1.5] * n, adapter_rank=ranks if k == 0 else None)
         slab = torch.empty(L.lora_pool_bytes(d), dtype=torch.uint8, device="cuda")
@@ -36,16 +31,16 @@ def pools(rank, ranks, h_in, h_out, E=1):
     return out, src
 
 
-def call(pool, aid, x, h_out, build, f32=False):
+def call(pool, aid, x, h_out, build, f32=False, eid=None):
     P = aid.numel()
     seg = L.Segments(P)
     y = [torch.zeros(P, h_out, dtype=torch.float32 if f32 else torch.bfloat16, device="cuda") for _ in range(2)]
     ws = torch.empty(L.lora_group_ws_bytes(pool, 0, 2, P), dtype=torch.uint8, device="cuda")
     dt = L.LORA_DTYPE_F32 if f32 else L.LORA_DTYPE_BF16
     if build:
-        L.lora_build_apply_group(pool, 0, 0, x, x.shape[1], None, aid, None, P, seg, y, [h_out] * 2, ws, dt)
+        L.lora_build_apply_group(pool, 0, 0, x, x.shape[1], None, aid, eid, P, seg, y, [h_out] * 2, ws, dt)
     else:
-        L.lora_build_segments(pool, aid, None, P, seg)
+        L.lora_build_segments(pool, aid, eid, P, seg)
         L.lora_apply_group(pool, 0, 0, x, x.shape[1], None, seg, y, [h_out] * 2, ws, dt)
     torch.cuda.synchronize()
     return torch.stack(y)
@@ -61,8 +56,8 @@ def batch(n, P, h_in):
 @pytest.mark.parametrize("P,h_in,h_out,build,policy", [
     (9, 328, 392, True, L.LORA_ACT_AUTO),            # shrink and expand in one launch
     (300, 328, 1032, True, L.LORA_ACT_AUTO), (300, 1032, 392, False, L.LORA_ACT_STREAMING),
-    (6000, 136, 264, False, L.LORA_ACT_AUTO),        # ranks 8 and 16: a wave per tile of thousands; above: long segments
-    (12000, 136, 264, False, L.LORA_ACT_AUTO)])
+    (6000, 136, 264, False, L.LORA_ACT_AUTO),        # ranks 8 and 16: hundreds of full tiles; above: long segments
+    (12000, 136, 264, False, L.LORA_ACT_AUTO)])      # rank 16: halves of 32-row tiles
 def test_lower_ranks_equal_padded_sources(rank, P, h_in, h_out, build, policy):
     ranks = sorted({rank, rank // 2, rank // 4, 1, 3, rank // 2 + 1, rank - 1})
     (a, b), _ = pools(rank, ranks, h_in, h_out)
@@ -71,6 +66,20 @@ def test_lower_ranks_equal_padded_sources(rank, P, h_in, h_out, build, policy):
         L.lora_pool_set_activation_policy(pool, policy)
     for f32 in (False, True):
         assert torch.equal(call(a[0], aid, x, h_out, build, f32), call(b[0], aid, x, h_out, build, f32))
+
+
+@pytest.mark.parametrize("rank", [8, 16, 32, 64])
+@pytest.mark.parametrize("E,P,h_out", [(3, 60, 392), (700, 9000, 136)])      # 700: 4900 cells, a wave per tile of thousands
+def test_lower_ranks_of_every_expert(rank, E, P, h_out):
+    """The experts of one adapter, loaded in one launch, note the adapter's rank, and so do both projections."""
+    ranks, h_in = [rank, 1, rank // 2, rank, 3, rank // 2 + 1, rank - 1], 136
+    (a, b), _ = pools(rank, ranks, h_in, h_out, E)
+    words = a[1].view(torch.int32)[:7 * E * 2 * 8].view(7, E, 2, 8).cpu()         # A, B, scale, rank, a_rank, b_rank
+    assert bool((words[..., 5:] == torch.tensor(ranks, dtype=torch.int32).view(7, 1, 1, 1)).all())
+    aid, x = batch(7, P, h_in)
+    eid = torch.randint(0, E, (P,), generator=torch.Generator(device="cuda").manual_seed(E), device="cuda", dtype=torch.int32)
+    for f32 in (False, True):
+        assert torch.equal(call(a[0], aid, x, h_out, False, f32, eid), call(b[0], aid, x, h_out, False, f32, eid))
 
 
 @pytest.mark.parametrize("rank", [16, 64])
