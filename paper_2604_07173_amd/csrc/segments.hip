@@ -5,10 +5,11 @@
 // feeds kernels that run right after it, so latency matters, not bandwidth; gfx950 has
 // 160 KiB of LDS per workgroup).  Global memory is only read for the ids and only written for
 // the results.  One CU issues one wave instruction per four cycles and SIMD, so the time of
-// either path below is essentially its instruction count.
+// any path below is essentially its instruction count.
 //
-// Three paths with identical results (rows ordered by key, original order inside a key), one of them for at most
-// kSmallMaxRows rows over 256 keys (segments_small_kernel) and:
+// Three paths with identical results (rows ordered by key, original order inside a key):
+//
+// * At most 4096 rows over at most 256 keys (segments_small_kernel): described at the kernel.
 //
 // * Radix path (segments_kernel; long segments, or key spaces too large for LDS counters).
 //   LDS holds key[row] for the whole batch and two 16-bit row-index arrays that the radix
@@ -667,10 +668,8 @@ hipError_t launch_segments(const SegParams &p_in, void *ws, hipStream_t s)
     SegParams p = p_in;
     // long batches of few keys: several workgroups (segments_large.hip)
     if (segments_large_handles(p)) return launch_segments_large(p, ws, s);
-    // short segments on average and counters that fit LDS beside the radix path's static
-    // arrays: bucket path
     const unsigned n_keys = (unsigned)p.n_adapters * (unsigned)p.n_experts;
-    // LORA_SEGMENT_PATH=radix forces the radix path (both give the same result)
+    // LORA_SEGMENT_PATH=radix forces the radix path (all give the same result)
     static const bool force_radix = [] {
         const char *e = getenv("LORA_SEGMENT_PATH");
         return e && e[0] == 'r';
@@ -683,10 +682,11 @@ hipError_t launch_segments(const SegParams &p_in, void *ws, hipStream_t s)
         else launch_small<kSmallGroups, kDecodeTileRows>(p, s);
         return hipGetLastError();
     }
-    // one radix pass (at most 256 keys) is as fast as the counting path and has no bucket
-    // limit: prefer it once there are enough rows per key for long buckets to be likely
-    const bool radix_is_cheap = p.passes == 1 && (int64_t)p.P >= 8 * (int64_t)n_keys;
-    if (!force_radix && !radix_is_cheap && (int64_t)p.P < 64 * (int64_t)n_keys && n_keys <= 0x10000u &&
+    // Counting path: short segments on average and counters that fit LDS beside the radix path's static arrays.
+    // Few keys with more rows than that (up to 5119, where several workgroups begin) have long buckets: one radix pass.
+    // (An empty batch takes either.)
+    const bool few_keys = n_keys <= kInlineMaxKeys && p.P > 0;
+    if (!force_radix && !few_keys && (int64_t)p.P < 64 * (int64_t)n_keys && n_keys <= 0x10000u &&
         bucket_lds_bytes(p.P, n_keys) <= kBucketLdsMax) {
         const size_t dyn = bucket_lds_bytes(p.P, n_keys);
         const int shift = bucket_shift_of(n_keys);

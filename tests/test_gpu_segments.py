@@ -87,10 +87,12 @@ def test_segments_match_oracle(seed, P, n, E, drop):
 
 
 @pytest.mark.parametrize("P,n,E,hot", [(2000, 64, 1, 0.7), (8192, 128, 8, 0.2), (1024, 256, 1, 1.0),
-                                       (300, 5, 1, 0.95)])
+                                       (300, 5, 1, 0.95), (300, 300, 1, 0.95), (1500, 40, 8, 0.5),
+                                       (2000, 300, 1, 0.7), (4096, 257, 1, 0.9)])
 def test_one_hot_key_among_many(P, n, E, hot):
-    """Many keys but one of them holds a large share of the rows (the counting path hands
-    such a batch over to the radix path inside the kernel)."""
+    """Many keys but one of them holds a large share of the rows (with more than 256 keys the
+    counting path hands such a batch over to the radix path inside the kernel, from one workgroup
+    or, from 2048 rows on, several)."""
     rng = np.random.default_rng(P + n)
     aid = rng.integers(0, n, size=P).astype(np.int32)
     eid = rng.integers(0, E, size=P).astype(np.int32) if E > 1 else None
@@ -165,11 +167,12 @@ def test_radix_path_forced_by_environment_gives_the_same_segments():
 
 
 def digest_of_cases():
-    """Digest of the segment arrays of a few batches that take the counting path by default."""
+    """Digest of the segment arrays of a few batches that take the counting path by default, and of two that
+    take the builder of up to 4096 rows over up to 256 keys (1024 rows of 256 keys, 65 of 4)."""
     import hashlib
     h = hashlib.sha256()
     for seed, P, n, E, drop in [(5, 1024, 32, 8, 0.0), (8, 8192, 256, 128, 0.0), (2, 65, 4, 1, 0.3),
-                                (10, 5000, 300, 100, 0.2)]:
+                                (10, 5000, 300, 100, 0.2), (31, 65, 65, 4, 0.3), (32, 1024, 300, 1, 0.0)]:
         rng = np.random.default_rng(seed)
         aid = rng.integers(0, n, size=P).astype(np.int32)
         aid[rng.random(P) < drop] = -1
