@@ -4,9 +4,9 @@
 // contiguous runs.  Sources that are 16-byte aligned (every matrix of a window is, if the window is)
 // are packed that way: a wave carries 32 rows of A (64 at rank 8) through LDS, a thread carries an
 // 8 x 8 piece of B through its registers.  One Mixtral-shaped layer of an adapter (14.2 MB in, 14.2
-// MB out): 13.1 -> 7.7 us (3.7 TB/s, against a floor of 4 us for any launch).  Sources at odd
-// addresses, and the way back, move one value at a time: one thread per 16-byte group of the packed
-// side (eight values that differ only in their K offset t).
+// MB out): 13.1 -> 7.7 us (3.7 TB/s; 5.6 us at the rate of a large copy, and an empty launch
+// takes 1.6).  Sources at odd addresses, and the way back, move one value at a time: one thread per
+// 16-byte group of the packed side (eight values that differ only in their K offset t).
 #include <algorithm>
 
 #include "lora_device.h"

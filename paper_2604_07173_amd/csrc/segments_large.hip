@@ -37,8 +37,8 @@ namespace lora {
 namespace {
 
 constexpr int kChunk = 2048;                        // rows per workgroup
-// Shorter batches stay with the single workgroup.  Measured on MI355X, 8 and 256 keys: one
-// workgroup takes 9.5 / 10.8 us at 4096 rows, 10.9 / 13.6 at 6144, 12.8 / 16.5 at 8192 and
+// Shorter batches stay with the single workgroup.  Measured on MI355X, 8 and 256 keys: its radix path takes 9.5 /
+// 10.8 us at 4096 rows (up to there segments.hip has a faster builder), 10.9 / 13.6 at 6144, 12.8 / 16.5 at 8192 and
 // 20.7 / 28.1 at 16384; the two launches here take 10.0-11.8 us at every one of those sizes.
 constexpr int kLargeMinRows = 5120;
 constexpr int kGroups = kChunk / kSegThreads;       // 64-row groups per wave
