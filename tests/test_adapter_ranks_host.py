@@ -47,4 +47,6 @@ def test_slots_set_from_several_threads(tmp_path, flags):
     csrc = os.path.join(ROOT, "paper_2604_07173_amd", "csrc")
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-pthread", *flags, "-I", csrc, str(src), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    if "unexpected memory mapping" in out.stderr:
+        pytest.skip("the sanitizer cannot run under this kernel's address layout")
     assert out.returncode == 0, out.stderr[-2000:]
