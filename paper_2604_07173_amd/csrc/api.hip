@@ -481,11 +481,15 @@ int do_shrink(const lora_pool *pool, int layer, const Group &g, const void *x, i
         // Short segments (less than three tiles on average) leave most waves of a block of one segment
         // without rows: groups of four tiles then, but for one projection only, because with two a wave has
         // no registers to fetch enough of its own A ahead.  Layer call in us, blocks / groups: one projection
-        // at rank 32 and 1024 inputs, 4096 adapters with 32 rows each 371 / 336, 256 of them 44.2 / 41.5; two,
-        // rank 64 and 4096 inputs, 128 adapters 91 / 123; 128 rows per adapter 219 / 233.
+        // at rank 32 and 1024 inputs, 4096 adapters with 32 rows each 349 / 334, at rank 64 456 / 445; Mixtral shapes,
+        // 4096 tokens (groups for the down projection), rank 32 402 / 394, rank 64 500 / 497; at rank 64 and 4096 inputs
+        // blocks are ahead (256 adapters with 32 rows 116 / 122); two projections, rank 64 and 4096 inputs, 128 adapters
+        // 91 / 123; 128 rows per adapter 219 / 233.
         static const int by_tiles = tune_int("LORA_SHRINK_BY_TILES", -1, -1, 1);
         const int64_t keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
         sp.by_tiles = by_tiles >= 0 ? by_tiles : sp.n_fused == 1 && seg->P < 96 * keys;
+        // The kernel of blocks only holds kLongListedSegs segments.
+        sp.blocks = !sp.by_tiles && std::min<int64_t>(keys, seg->P) <= kLongListedSegs;
         sp.v[0] = g.v[j];
         sp.v[1] = sp.n_fused == 2 ? g.v[j + 1] : nullptr;
         LORA_HIP(launch_shrink(sp, st));

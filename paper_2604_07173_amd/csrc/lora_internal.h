@@ -25,6 +25,7 @@ static_assert(sizeof(Unit) == 32, "table entry is 32 bytes");
 
 constexpr int kTileRows = 32;        // rows per tile of the long-segment kernels
 constexpr int kLongRows = 128;       // rows of one segment per work item of the long-segment shrink
+constexpr int kLongListedSegs = 64 * 64;    // segments that its waves hold in registers
 constexpr int kDecodeTileRows = 16;  // rows per tile of the decode kernels
 constexpr int kKBlock = 32;          // K elements per MFMA step (v_mfma_f32_16x16x32_bf16)
 constexpr int kColChunk = 128;       // output columns one wave owns in expand
@@ -198,7 +199,10 @@ struct ShrinkParams {
         int tile_halves;     // decode kernel: the tiles have up to 32 rows and are taken in halves
         int by_tiles;        // long-segment kernel: work items are groups of four tiles, else blocks of one segment
     };
-    int wave_per_tile;       // decode kernel: every wave takes a whole tile (no K split across waves)
+    union {
+        int wave_per_tile;   // decode kernel: every wave takes a whole tile (no K split across waves)
+        int blocks;          // long-segment kernel: blocks of one segment, at most kLongListedSegs segments
+    };
     int build;               // decode kernel: the segments are built inside the launch, from `seg`
     int lower_ranks;         // decode kernel: the pool has adapters of a lower rank than its own
     int x_stream;            // decode kernel, K-split form: x rows loaded with the streaming hint (ranks 8, 16: as whole lines)
