@@ -595,15 +595,15 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         // is streamed at every length (cached: 255 -> 264 us for 2048 tokens).
         ep.share_b = long_segments;
         const int64_t wave_items = (tub + group - 1) / group * group * ep.per_tile;
-        // Chunks in flight per wave: two, but one where the launch is a few rounds of the chip's waves
-        // long and its tiles are tall (more waves fit then, which shortens the rounds), or where an item is
-        // one chunk anyway.  Layer call in us, two / one: llama shapes, 1024 rows 116.3 / 111.5, at rank 64
-        // 284 / 261, 333 ragged fp32 rows at rank 32 70.6 / 66.3, llama shapes with 8 rows (one chunk) 31.6 /
-        // 31.0; but 256 rows (short tiles) 62.6 / 63.7, and Mixtral shapes with 2048 tokens (57 k items)
-        // 244.9 / 247.1, with 512 at rank 32 (36 k) 178.2 / 180.5.
+        // Chunks in flight per wave: two, but one where an item is one chunk anyway, and at ranks 8 and 64 where the launch
+        // is a few rounds of the chip's waves long and its tiles are tall (more waves fit then, which shortens the
+        // rounds).  Layer call in us, two / one: llama shapes, 1024 rows, rank 64 254.5 / 253.1, rank 8 89.7 / 89.1, 512 rows,
+        // rank 64 186.2 / 184.6, with 8 rows (one chunk) 31.6 / 31.0; but 2048 rows, rank 32 230.5 / 232.0, rank 16 158.7 /
+        // 160.0, of which 1792 share an adapter 145.7 / 147.9, 1024 rows, rank 16 106.4 / 106.4, rank 32 158.2 / 158.5, 256
+        // rows (short tiles) 57.4 / 58.8, and Mixtral shapes with 2048 tokens (57 k items) at rank 16 244.9 / 247.1.
         static const int shallow = tune_int("LORA_DEC_SHALLOW_ITEMS", 24576, 0, 1 << 30);
-        static const int shallow_all = tune_int("LORA_DEC_SHALLOW_ALL", 0, 0, 1);
-        ep.deep = cpi > 1 && !((long_segments || shallow_all) && wave_items <= shallow);
+        const bool few_rounds = long_segments && wave_items <= shallow && (pool->d.rank == 8 || pool->d.rank == 64);
+        ep.deep = cpi > 1 && !few_rounds;
         // The hardware hands workgroups out as others finish, which evens out tiles of different heights
         // better than a workgroup's walk over several items, and costs a launch of its own each: worth it
         // where an item is long.  16 / 32 / 64 workgroups per CU: rank 64, 1024 tokens over 512 adapters
