@@ -99,17 +99,17 @@ __device__ inline void block_scan3(int cnt, int last, int first, ScanLds *s,
 // key_of[i] for all rows; `each(i, key)` is called once per row.  The id loads of up to eight
 // rows are issued before the first is used (the ids come from HBM; one round trip per row
 // would otherwise dominate large batches).
-template <int NT = kThreads, class F>
+template <class F>
 __device__ inline void all_row_keys(const SegParams &p, unsigned *key_of, unsigned &bad, F each)
 {
     constexpr int U = 8;
     const int tid = threadIdx.x;
 #pragma unroll 1
-    for (int i0 = tid; i0 < p.P; i0 += U * NT) {
+    for (int i0 = tid; i0 < p.P; i0 += U * kThreads) {
         int a[U], e[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * NT;
+            const int i = i0 + u * kThreads;
             a[u] = -1;
             e[u] = 0;
             if (i < p.P) {
@@ -119,7 +119,7 @@ __device__ inline void all_row_keys(const SegParams &p, unsigned *key_of, unsign
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * NT;
+            const int i = i0 + u * kThreads;
             if (i < p.P) {
                 const unsigned k = row_key(p, a[u], e[u], bad);
                 key_of[i] = k;
@@ -395,172 +395,189 @@ void launch_small(const SegParams &p, hipStream_t s)
 // ---- bucket path ---------------------------------------------------------------------------
 // For batches of many short segments (decode): one LDS counter per key instead of radix
 // passes over the key bits.
-//   1. count the rows of every key with LDS adds (a sum: the order of the adds is immaterial);
-//   2. thread t owns a contiguous range of keys: an exclusive scan over the counts gives
-//      every key its start; the keys that occur are the segments, so they are listed in LDS
+//   1. count the rows of every key with fetching LDS adds; what an add returns is the row's place among its key's
+//      rows, which depends on the order the adds execute in (hence step 4);
+//   2. thread t owns a contiguous range of keys: an exclusive scan over the counts gives every range its first row, segment
+//      and tile; the keys that occur are the segments, so they are listed in LDS
 //      and the segment records and tiles are then written one segment per thread;
-//   3. every row takes a place inside its key's range with a fetching LDS add; which place
-//      depends on the order the adds execute in, so
+//   3. every row goes to its place in its key's range;
 //   4. every row is re-ranked inside its bucket by the number of rows of the bucket with a
 //      smaller row index: the final order is by (key, row index), unique, hence bit-identical
 //      run to run and identical to the stable sort of the radix path.
-// Step 4 costs bucket length per row; if one key holds more than kMaxBucket rows the
+// Step 4 costs bucket length per row, and a counter has 8 bits: if one key holds more than 255 rows the
 // workgroup drops this attempt and runs the radix path (a workgroup-uniform decision).
 //
-// Longer batches are launched with several workgroups.  Step 1 and the sums of step 2 are
-// repeated by every one of them (a workgroup cannot hand anything to another inside a launch,
-// and repeating costs no time); the list of segments with the keys' starts, the segment records
-// and tiles, step 3 and step 4 are shared out by segment index: workgroup g of G takes the
-// segments [S g / G, S (g + 1) / G), which are a contiguous range of keys and of sorted
-// positions.  Measured on the fine-grained MoE shapes (8192 rows, 32768 keys), kernel time in a
-// rocprofv3 trace: one workgroup 17.1 us, eight workgroups 13.6 us (the steps that every
-// workgroup repeats are about 6 us of it).  If the radix path has to run, workgroup 0 runs it.
+// Longer batches are launched with several workgroups.  Step 1 and the sums of step 2 are repeated by every one of them
+// (a workgroup cannot hand anything to another inside a launch, and repeating costs no time); the records and steps 3 and 4
+// are shared out by threads of step 2: workgroup g of G takes those whose first row is in the g-th part of the sorted
+// rows, a contiguous range of keys and of sorted positions.  If the radix path has to run, workgroup 0 runs it.
 //
-// Two 16-bit counters share a 32-bit LDS word (a batch has at most 16384 rows, so neither
-// half overflows and positions fit 16 bits).  The words are skewed by one word per
-// thread-owned range so that the threads' range walks hit different banks.
-constexpr int kMaxBucket = 256;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+// Bound by the latency of one workgroup: ids from memory, then its instructions.  So a row's key and place stay in
+// registers from step 1 to step 3, four 8-bit counters share a word, and a thread sums a word's four counts with one
+// instruction, its segments and tiles with a few.  (With two 16-bit counters per word, a second round of adds for
+// the places, fine-grained MoE shapes over 32768 keys, layer call before / now: 1024 tokens 133.3 / 130.4 us (this kernel 13.3 /
+// 10.7), 256 tokens 60.4 / 59.1, 64 tokens 33.0 / 31.8.  Of its time at 1024 tokens, by clock stamps: ids 1.8, counts 1.8,
+// sums 1.6, list 1.9, records 0.4, places 1.5, order 1.3; records written by the threads that own the keys took 5.)
+//
+// W: counter words per thread (up to 4096 W keys); R: rows per thread (up to 1024 R rows).
+// Occupied keys of a thread up to which its wave lists them one after the other: at 1024 tokens of the fine-grained shapes
+// dense and sparse key ranges are alike either way, at 64 and 256 tokens a wave has two or three (59.1 and 31.8 us; all
+// keys without a branch 59.9 and 32.8; a branch per key 59.6 and 32.3).
+constexpr unsigned kFewOccupied = 6;
 
-// SHIFT = log2 of the counter words a thread owns (1 .. 32 words: up to 65536 keys); a
-// compile-time constant so that a thread's words live in registers between the scan and the
-// passes that need them again, and every loop over them is unrolled with its LDS reads in
-// flight together.
-template <int NT, int SHIFT>
-__global__ __launch_bounds__(NT) void segments_bucket_kernel(SegParams p)
+template <int W, int R>
+__global__ __launch_bounds__(kThreads) void segments_bucket_kernel(SegParams p)
 {
-    constexpr int WPT = 1 << SHIFT;                   // counter words per thread
-    constexpr int n_cnt = (NT << SHIFT) + NT;         // counter words incl. the skew
-    constexpr int NW = NT / 64;
-    constexpr bool kFallback = NT == kThreads;        // the radix path is written for kThreads
-    __shared__ unsigned wave_sums[NW][2];
-    __shared__ unsigned status_bits;
-    __shared__ int n_active_total;
-    __shared__ unsigned longest;
+    constexpr int KPT = 4 * W;                        // keys per thread
+    __shared__ unsigned wave_sums[kWaves][2];
+    __shared__ unsigned status_bits, overflow;
+    __shared__ int own_lo, own_hi, pos_lo_s, pos_hi_s, seg_lo_s, seg_hi_s;
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_lds[];
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int G = gridDim.x, wg = blockIdx.x;         // workgroups that share steps 2b to 4
+    const int G = gridDim.x, wg = blockIdx.x;         // workgroups that share the records and steps 3 and 4
     const int P = p.P;
-    const int P_pad = (P + 63) & ~63;
-    unsigned *key_of = reinterpret_cast<unsigned *>(dyn_lds);           // [P_pad]
-    unsigned *cnt = key_of + P_pad;                                     // [n_cnt]
-    unsigned *tmp = cnt + n_cnt;                                        // [P_pad] row | key << 16
+    unsigned *cnt = reinterpret_cast<unsigned *>(dyn_lds);              // [kThreads * W] four counts per word
+    uint16_t *start = reinterpret_cast<uint16_t *>(cnt + kThreads * W); // [kThreads * W] first position of a word's keys
+    unsigned *tmp = reinterpret_cast<unsigned *>(start + kThreads * W); // [P, padded to 64, and 64] row | key << 16
     unsigned *seglist = tmp;               // key | first tile << 16 per segment, before tmp is used
-    auto slot = [&](unsigned word) { return word + (SHIFT ? word >> SHIFT : 0u); };
-    auto half_of = [&](unsigned key) { return (cnt[slot(key >> 1)] >> ((key & 1u) * 16u)) & 0xFFFFu; };
+    auto count_of = [&](unsigned key) { return (cnt[key >> 2] >> ((key & 3u) * 8u)) & 0xFFu; };
+    auto start_of = [&](unsigned key) {
+        return (unsigned)start[key >> 2] +
+               __builtin_amdgcn_sad_u8(cnt[key >> 2] & ((1u << ((key & 3u) * 8u)) - 1u), 0u, 0u);
+    };
 
+    // ---- 1. keys, counts and places --------------------------------------------------------
+    int a[R], e[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {                     // unconditional loads (P >= 1), then selects
+        const int i = tid + u * kThreads, r = min(i, P - 1);
+        a[u] = p.adapter_id[r];
+        e[u] = p.expert_id ? p.expert_id[r] : 0;
+        if (i >= P) a[u] = -1;
+    }
     if (tid == 0) {
         status_bits = 0;
-        n_active_total = 0;
-        longest = 0;
+        overflow = 0;
+        own_lo = kThreads;
+        pos_lo_s = seg_lo_s = P;
+        own_hi = pos_hi_s = seg_hi_s = 0;
     }
 #pragma unroll
-    for (int j = 0; j < WPT + 1; ++j) cnt[tid + j * NT] = 0;
+    for (int j = 0; j < W; ++j) cnt[tid + j * kThreads] = 0;
     __syncthreads();
-
-    // ---- 1. keys and counts --------------------------------------------------------------
+    unsigned mine[R];                                 // key | place << 16, or kNoKey
     {
-        int n_active = 0;
-        unsigned bad = 0;
-        all_row_keys<NT>(p, key_of, bad, [&](int, unsigned k) {
-            if (k != kNoKey) {
-                ++n_active;
-                atomicAdd(&cnt[slot(k >> 1)], 1u << ((k & 1u) * 16u));
+        unsigned bad = 0, old[R];
+        bool over = false;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            mine[u] = row_key(p, a[u], e[u], bad);
+            old[u] = mine[u] != kNoKey ? atomicAdd(&cnt[mine[u] >> 2], 1u << ((mine[u] & 3u) * 8u)) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (mine[u] != kNoKey) {
+                const unsigned place = (old[u] >> ((mine[u] & 3u) * 8u)) & 0xFFu;
+                over = over || place == 0xFFu;        // the counter has run into its neighbour
+                mine[u] |= place << 16;
             }
-        });
         if (bad) atomicOr(&status_bits, bad);
-#pragma unroll 1
-        for (int o = 32; o > 0; o >>= 1) n_active += __shfl_xor(n_active, o, 64);
-        if (lane == 0 && n_active) atomicAdd(&n_active_total, n_active);
+        if (over) overflow = 1;
     }
     __syncthreads();
+    if (overflow) {                                   // every workgroup has seen the same counts
+        __syncthreads();
+        if (wg == 0) radix_body(p);
+        return;
+    }
 
-    // ---- 2. scan over the keys; segments and tiles ----------------------------------------
-    const int TR = p.tile_rows;                       // a power of two
+    // ---- 2. scan over the keys; segment records and tiles ----------------------------------
+    const int TR = p.tile_rows;                       // a power of two, 16 or 32
     const int tr_shift = 31 - __clz(TR);
-    const unsigned w0 = (unsigned)tid << SHIFT;       // my counter words: w0 .. w0 + WPT - 1
-    unsigned rs_before, rs_total, t_before, t_total;  // rows | segments << 16, and tiles
-    unsigned cw[WPT];                                 // my words (two 16-bit counts each)
-    unsigned segs_mine;                               // occupied keys among mine
+    unsigned cw[W];                                   // my words
+    unsigned rows = 0, segs = 0, rs_before, rs_total, t_before, t_total;          // rows | segments << 16, and tiles
     {
-        unsigned rows = 0, tiles = 0, mx = 0, segs = 0;
+        unsigned tiles = 0;
 #pragma unroll
-        for (int j = 0; j < WPT; ++j) cw[j] = cnt[slot(w0 + j)];
+        for (int j = 0; j < W; ++j) cw[j] = cnt[tid * W + j];
+        // bytes that are not zero: the sum with 0x7F carries into the top bit, of each byte on its own
+        auto occupied = [](unsigned x) { return (unsigned)__popc((((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u); };
+        const unsigned whole = (0xFFu >> tr_shift) * 0x01010101u, rest = (unsigned)(TR - 1) * 0x01010101u;
 #pragma unroll
-        for (int j = 0; j < WPT; ++j) {
-            const unsigned lo = cw[j] & 0xFFFFu, hi = cw[j] >> 16;
-            rows += lo + hi;
-            tiles += ((lo + TR - 1) >> tr_shift) + ((hi + TR - 1) >> tr_shift);
-            mx = max(mx, max(lo, hi));
-            segs += (lo ? 1u : 0u) + (hi ? 1u : 0u);
+        for (int j = 0; j < W; ++j) {
+            rows = __builtin_amdgcn_sad_u8(cw[j], 0u, rows);
+            segs += occupied(cw[j]);
+            tiles = __builtin_amdgcn_sad_u8((cw[j] >> tr_shift) & whole, 0u, tiles) + occupied(cw[j] & rest);
         }
-        segs_mine = segs;
-        if (kFallback && mx > kMaxBucket) atomicMax(&longest, mx);
         // a batch has at most 16384 rows, so rows and segments share a word
-        block_excl_sum2<NW>(rows | (segs << 16), tiles, wave_sums, &rs_before, &t_before, &rs_total,
-                        &t_total);
+        block_excl_sum2<kWaves>(rows | (segs << 16), tiles, wave_sums, &rs_before, &t_before, &rs_total, &t_total);
     }
-    if constexpr (kFallback) {
-        if (longest > kMaxBucket) {    // same value in every thread: read after the scan's barrier
-            __syncthreads();
-            if (wg == 0) radix_body(p);               // every workgroup has seen the same counts
-            return;
+    const int P_act = (int)(rs_total & 0xFFFFu), S = (int)(rs_total >> 16);
+    const int first = (int)(rs_before & 0xFFFFu);
+    const bool here = rows && first * G / P_act == wg;
+    if (here) {
+        // my keys' starts, and a list of those that occur with the first tile of each
+        unsigned at = (unsigned)first, sidx = rs_before >> 16, tix = t_before;
+        unsigned long long occ = 0;                   // which of my keys occur
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            start[tid * W + j] = (uint16_t)at;
+            at = __builtin_amdgcn_sad_u8(cw[j], 0u, at);
+            const unsigned top = ((((cw[j] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | cw[j]) & 0x80808080u) >> 7;
+            occ |= (unsigned long long)((top * 0x01020408u) >> 24 & 0xFu) << (4 * j);
+        }
+        if (!__any(segs > kFewOccupied)) {            // a wave with few of them takes one after the other,
+            for (; occ; occ &= occ - 1) {
+                const unsigned key = (unsigned)tid * KPT + (unsigned)__ffsll((long long)occ) - 1;
+                seglist[sidx++] = key | (tix << 16);
+                tix += (count_of(key) + TR - 1) >> tr_shift;
+            }
+        } else {                                      // one with many all keys without a branch
+            const int nowhere = ((P + 63) & ~63) + lane;
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const unsigned n = (cw[j] >> (8 * q)) & 0xFFu;
+                    seglist[n ? sidx : (unsigned)nowhere] = (unsigned)((tid * W + j) * 4 + q) | (tix << 16);
+                    sidx += n ? 1u : 0u;
+                    tix += (n + TR - 1) >> tr_shift;
+                }
         }
     }
-    const int P_act = (int)(rs_total & 0xFFFFu);
-    const int S = (int)(rs_total >> 16);
-    const int n_tiles = (int)t_total;
-    // From here on workgroup wg takes the segments [s0, s1), i.e. the keys [key_lo, key_hi) and the
-    // sorted positions [pos_lo, pos_hi); up to here every workgroup has done the same.
-    const int s0 = (int)((int64_t)S * wg / G), s1 = (int)((int64_t)S * (wg + 1) / G);
-    // Only the threads whose keys lie in or next to that range go on: the others' segments are
-    // listed, and their keys' counts turned into starts, by the workgroups that need them.
-    const int seg_first = (int)(rs_before >> 16);
-    if (seg_first <= s1 && seg_first + (int)segs_mine >= s0) {
-        // list of the occupied keys with the first tile of each, and the start of every key in
-        // place of its count (all from the words in registers: nothing is read back)
-        int sidx = (int)(rs_before >> 16);
-        unsigned tix = t_before;
-        unsigned at = rs_before & 0xFFFFu;
-#pragma unroll
-        for (int j = 0; j < WPT; ++j) {
-            const unsigned lo = cw[j] & 0xFFFFu, hi = cw[j] >> 16;
-            if (cw[j]) {                               // most words of a large key space are empty
-                if (lo) {
-                    seglist[sidx++] = (w0 + j) * 2 | (tix << 16);
-                    tix += (lo + TR - 1) >> tr_shift;
-                }
-                if (hi) {
-                    seglist[sidx++] = ((w0 + j) * 2 + 1) | (tix << 16);
-                    tix += (hi + TR - 1) >> tr_shift;
-                }
+    {
+        const unsigned long long who = __ballot(here);
+        if (who) {
+            const int l0 = __ffsll((long long)who) - 1, l1 = 63 - __clzll((long long)who);
+            if (lane == l0) {
+                atomicMin(&own_lo, tid);
+                atomicMin(&pos_lo_s, first);
+                atomicMin(&seg_lo_s, (int)(rs_before >> 16));
             }
-            cnt[slot(w0 + j)] = at | ((at + lo) << 16);
-            at += lo + hi;
+            if (lane == l1) {
+                atomicMax(&own_hi, tid + 1);
+                atomicMax(&pos_hi_s, first + (int)rows);
+                atomicMax(&seg_hi_s, (int)(rs_before >> 16) + (int)segs);
+            }
         }
     }
     __syncthreads();
-    const unsigned key_lo = s0 < S ? seglist[s0] & 0xFFFFu : 0x10000u;
-    const unsigned key_hi = s1 < S ? seglist[s1] & 0xFFFFu : 0x10000u;
-    const int pos_lo = s0 < S ? (int)half_of(key_lo) : P_act;
-    const int pos_hi = s1 < S ? (int)half_of(key_hi) : P_act;
+    const unsigned lo = (unsigned)own_lo, hi = (unsigned)own_hi;        // this workgroup's threads of step 2
+    const int pos_lo = pos_lo_s, pos_hi = pos_hi_s;
     // segment records and tiles, one segment per thread and turn
 #pragma unroll 1
-    for (int sidx = s0 + tid; sidx < s1; sidx += NT) {
-        const unsigned me = seglist[sidx];
-        const unsigned next = seglist[min(sidx + 1, S - 1)];
-        const int key = (int)(me & 0xFFFFu);
-        const int pos = (int)half_of(me & 0xFFFFu);
-        const int n = (sidx + 1 < S ? (int)half_of(next & 0xFFFFu) : P_act) - pos;
-        int tix = (int)(me >> 16);
-        p.seg_start[sidx] = pos;
-        p.seg_key[sidx] = key;
+    for (int sidx = seg_lo_s + tid; sidx < seg_hi_s; sidx += kThreads) {
+        const unsigned it = seglist[sidx], key = it & 0xFFFFu;
+        const int at = (int)start_of(key), n = (int)count_of(key);
+        int tix = (int)(it >> 16);
+        p.seg_start[sidx] = at;
+        p.seg_key[sidx] = (int32_t)key;
 #pragma unroll 1
         for (int r = 0; r < n; r += TR) {
             lora_tile t;
-            t.key = key;
-            t.row0 = pos + r;
+            t.key = (int32_t)key;
+            t.row0 = at + r;
             t.n_rows = min(TR, n - r);
             t.seg = sidx;
             p.tiles[tix++] = t;
@@ -568,55 +585,50 @@ __global__ __launch_bounds__(NT) void segments_bucket_kernel(SegParams p)
     }
     __syncthreads();
 
-    // ---- 3. a place in the key's range for every row --------------------------------------
-    // four rows per turn: their key reads, fetching adds and stores overlap
-#pragma unroll 1
-    for (int i0 = tid; i0 < P; i0 += 4 * NT) {
-        unsigned k[4], old[4];
+    // ---- 3. every row to its place in its key's range ---------------------------------------
+    {
+        unsigned to[R];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            k[u] = i0 + u * NT < P ? key_of[i0 + u * NT] : kNoKey;
-            if (k[u] < key_lo || k[u] >= key_hi) k[u] = kNoKey;     // another workgroup's key
+        for (int u = 0; u < R; ++u) {                 // all look-ups before the first store
+            const unsigned k = mine[u] & 0xFFFFu, owner = k / KPT;
+            const bool yes = mine[u] != kNoKey && owner >= lo && owner < hi;
+            to[u] = kNoKey;
+            if (yes) to[u] = start_of(k) + (mine[u] >> 16);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (k[u] != kNoKey) old[u] = atomicAdd(&cnt[slot(k[u] >> 1)], 1u << ((k[u] & 1u) * 16u));
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (k[u] != kNoKey)
-                tmp[(old[u] >> ((k[u] & 1u) * 16u)) & 0xFFFFu] = (unsigned)(i0 + u * NT) | (k[u] << 16);
+        for (int u = 0; u < R; ++u)
+            if (to[u] != kNoKey) tmp[to[u]] = (unsigned)(tid + u * kThreads) | (mine[u] << 16);
     }
     // filler around this workgroup's positions: step 4 reads aligned groups of four words
-    if (tid < 4 && (pos_lo & ~3) + tid < pos_lo) tmp[(pos_lo & ~3) + tid] = 0xFFFFFFFFu;
-    if (tid >= 4 && tid < 8 && pos_hi + tid - 4 < ((pos_hi + 3) & ~3)) tmp[pos_hi + tid - 4] = 0xFFFFFFFFu;
+    if (pos_lo < pos_hi) {
+        if (tid < 4 && (pos_lo & ~3) + tid < pos_lo) tmp[(pos_lo & ~3) + tid] = 0xFFFFFFFFu;
+        if (tid >= 4 && tid < 8 && pos_hi + tid - 4 < ((pos_hi + 3) & ~3)) tmp[pos_hi + tid - 4] = 0xFFFFFFFFu;
+    }
     __syncthreads();
 
     // ---- 4. order inside the bucket by row index -------------------------------------------
-    // after step 3 a key's counter holds the end of its range = the start of the next key's
     // The bucket is read in aligned groups of four words; words of other keys (and the
     // filler around the workgroup's positions) fall outside [key << 16, mine) and count as not
     // smaller.
 #pragma unroll 1
-    for (int pos = pos_lo + tid; pos < pos_hi; pos += NT) {
-        const unsigned mine = tmp[pos];
-        const unsigned k = mine >> 16, row = mine & 0xFFFFu, base = mine & 0xFFFF0000u;
-        const int e = (int)half_of(k);
-        // the key before this workgroup's first one is another's: its counter still holds its start
-        const int b = k == key_lo ? pos_lo : (int)half_of(k - 1);
+    for (int pos = pos_lo + tid; pos < pos_hi; pos += kThreads) {
+        const unsigned me = tmp[pos];
+        const unsigned k = me >> 16, row = me & 0xFFFFu, base = me & 0xFFFF0000u;
+        const int b0 = (int)start_of(k), b1 = b0 + (int)count_of(k);
         int rank = 0;
 #pragma unroll 1
-        for (int j = b & ~3; j < e; j += 4) {
+        for (int j = b0 & ~3; j < b1; j += 4) {
             const u32x4 t = *reinterpret_cast<const u32x4 *>(tmp + j);
             rank += (t[0] - base < row ? 1 : 0) + (t[1] - base < row ? 1 : 0) +
                     (t[2] - base < row ? 1 : 0) + (t[3] - base < row ? 1 : 0);
         }
-        p.perm[b + rank] = (int32_t)row;
+        p.perm[b0 + rank] = (int32_t)row;
     }
     if (tid == 0 && wg == 0) {
         p.seg_start[S] = P_act;
         p.counts[0] = S;
         p.counts[1] = P_act;
-        p.counts[2] = n_tiles;
+        p.counts[2] = (int32_t)t_total;
         p.counts[3] = 0;
         p.status[0] = status_bits;
     }
@@ -629,38 +641,44 @@ size_t segments_lds_bytes(int P)
     return P_pad * 4 + 2 * P_pad * 2;
 }
 
-// log2 of the counter words a thread of the bucket path owns
-static int bucket_shift_of(unsigned n_keys)
+// counter words a thread of the bucket path owns, four keys each: a power of two
+static int bucket_words_of(unsigned n_keys)
 {
-    const unsigned n_words = (n_keys + 1) / 2;
-    int shift = 0;
-    while (((unsigned)kThreads << shift) < n_words) ++shift;
-    return shift;
+    int words = 1;
+    while ((unsigned)(4 * kThreads * words) < n_keys) words *= 2;
+    return words;
 }
 
 // dynamic LDS of the bucket path (it may fall back to the radix path inside the kernel)
 static size_t bucket_lds_bytes(int P, unsigned n_keys)
 {
     const size_t P_pad = ((size_t)P + 63) & ~(size_t)63;
-    const size_t n_cnt = ((size_t)kThreads << bucket_shift_of(n_keys)) + kThreads;
-    const size_t need = P_pad * 4 + n_cnt * 4 + P_pad * 4;
+    const size_t need = (size_t)kThreads * bucket_words_of(n_keys) * (4 + 2) + (P_pad + 64) * 4;
     return need > segments_lds_bytes(P) ? need : segments_lds_bytes(P);
 }
 
 constexpr size_t kBucketLdsMax = 140 * 1024;
 constexpr int kBucketWorkgroups = 8;
 
-template <int NT, int SHIFT>
-static hipError_t launch_bucket(const SegParams &p, size_t dyn, hipStream_t s)
+template <int W, int R>
+static hipError_t launch_bucket_wr(const SegParams &p, size_t dyn, hipStream_t s)
 {
-    static hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(segments_bucket_kernel<NT, SHIFT>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBucketLdsMax);
+    static hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(segments_bucket_kernel<W, R>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBucketLdsMax);
     if (attr != hipSuccess) return attr;
     // the counting and the scan over the keys are done by every workgroup, the rest is shared out
     const int wgs = std::max(1, std::min(kBucketWorkgroups, p.P / 1024));
-    hipLaunchKernelGGL((segments_bucket_kernel<NT, SHIFT>), dim3(wgs), dim3(NT), dyn, s, p);
+    hipLaunchKernelGGL((segments_bucket_kernel<W, R>), dim3(wgs), dim3(kThreads), dyn, s, p);
     return hipGetLastError();
+}
+
+template <int W>
+static hipError_t launch_bucket(const SegParams &p, size_t dyn, hipStream_t s)
+{
+    static_assert(16 * kThreads == LORA_MAX_ROWS, "the last form takes the longest batch");
+    if (p.P <= 4 * kThreads) return launch_bucket_wr<W, 4>(p, dyn, s);
+    if (p.P <= 8 * kThreads) return launch_bucket_wr<W, 8>(p, dyn, s);
+    return launch_bucket_wr<W, 16>(p, dyn, s);
 }
 
 hipError_t launch_segments(const SegParams &p_in, void *ws, hipStream_t s)
@@ -684,19 +702,17 @@ hipError_t launch_segments(const SegParams &p_in, void *ws, hipStream_t s)
     }
     // Counting path: short segments on average and counters that fit LDS beside the radix path's static arrays.
     // Few keys with more rows than that (up to 5119, where several workgroups begin) have long buckets: one radix pass.
-    // (An empty batch takes either.)
-    const bool few_keys = n_keys <= kInlineMaxKeys && p.P > 0;
-    if (!force_radix && !few_keys && (int64_t)p.P < 64 * (int64_t)n_keys && n_keys <= 0x10000u &&
+    // An empty batch takes the radix path.
+    const bool few_keys = n_keys <= kInlineMaxKeys;
+    if (!force_radix && p.P > 0 && p.P <= LORA_MAX_ROWS && !few_keys && (int64_t)p.P < 64 * (int64_t)n_keys && n_keys <= 0x10000u &&
         bucket_lds_bytes(p.P, n_keys) <= kBucketLdsMax) {
         const size_t dyn = bucket_lds_bytes(p.P, n_keys);
-        const int shift = bucket_shift_of(n_keys);
-        switch (shift) {
-        case 0: return launch_bucket<kThreads, 0>(p, dyn, s);
-        case 1: return launch_bucket<kThreads, 1>(p, dyn, s);
-        case 2: return launch_bucket<kThreads, 2>(p, dyn, s);
-        case 3: return launch_bucket<kThreads, 3>(p, dyn, s);
-        case 4: return launch_bucket<kThreads, 4>(p, dyn, s);
-        default: return launch_bucket<kThreads, 5>(p, dyn, s);
+        switch (bucket_words_of(n_keys)) {
+        case 1: return launch_bucket<1>(p, dyn, s);
+        case 2: return launch_bucket<2>(p, dyn, s);
+        case 4: return launch_bucket<4>(p, dyn, s);
+        case 8: return launch_bucket<8>(p, dyn, s);
+        default: return launch_bucket<16>(p, dyn, s);
         }
     }
     const size_t dyn = segments_lds_bytes(p.P);
