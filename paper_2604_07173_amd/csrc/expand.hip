@@ -14,13 +14,19 @@
 //    (sub-tile, column chunk).
 //
 // 2. the product: every wave works on its own, no LDS and no barriers.  Work item (per
-//    wave) = (group of kLongGroup consecutive tiles, projection, 128-column chunk).  The
-//    wave keeps the chunk's packed B in MFMA operand registers for as long as the tiles
-//    belong to the same (adapter, expert) and walks over the group's 16-row sub-tiles,
-//    software-pipelined three deep: while sub-tile q is multiplied and written back, the
-//    operand image and the base-output rows of sub-tile q+1 are in flight, and the row
-//    indices of sub-tile q+2 are being fetched.  All loads are unconditional (rows beyond a
+//    wave) = (group of two consecutive tiles, one with fp32 output; projection; 128-column chunk).  The
+//    wave asks for everything at once - the rows' indices, the chunk's packed B in MFMA operand registers,
+//    all of the item's base output - and then multiplies sub-tile after sub-tile, the next one's operand image in
+//    flight, and writes it back.  All loads are unconditional (rows beyond a
 //    tile re-read a valid row and are not stored), so the code is straight-line.
+//
+// What bounds it is the read-modify-write of y in HBM, and that runs the faster the more of it a wave reads before it
+// writes, and the less far down a strip of 256-byte pieces it goes.  Layer call in us, two projections of 4096
+// inputs unless stated, by tiles per item and sub-tiles of y in flight, 4 and 1 / 2 and 1 / 2 and 2 / 2 and all 4 (now): 16384
+// rows of 8 uneven requests, rank 64 286.5 / 282.8 / 278.4 / 270.9, 4096 rows of 8 requests 93.4 / 90.9 / 90.3 / 89.4,
+// 16384 rows, rank 16 266.4 / 251.2 / 242.9 / 241.7, 12000 rows of 7 requests, rank 32 206.7 / 193.0 / 191.0 / 190.2;
+// the first is 5.6 TB/s of y and B.  More tiles (3, all in flight: 312, registers spill) or fewer (1: 309, B is fetched
+// for every 32 rows) are slower at rank 64; 8 tiles with one in flight 294.
 //
 // The base-output rows are read and written with nontemporal accesses: every byte of y is touched
 // once, and keeping it out of the caches leaves them to the B tiles and operand images that many
@@ -39,7 +45,6 @@ namespace lora {
 
 namespace {
 
-constexpr int kLongGroup = 4;        // tiles one wave item walks over (128 rows)
 
 // vec elements of one sub-tile's operand image
 template <int R>
@@ -104,14 +109,12 @@ struct LongWave {
     static constexpr int KS = Tile::KS;
     static constexpr int NY = F32 ? 2 : 1;
     static constexpr int ESZ = F32 ? 4 : 2;
-    static constexpr int NSLOT = 2 * kLongGroup;
+    static constexpr int GROUP = expand_long_group(F32);
+    static constexpr int NSLOT = 2 * GROUP;
 
-    struct Rows {                 // stage 1: where the sub-tile's rows live
-        char *y[4];
+    struct Rows {                 // where a sub-tile's rows live, and its base output
+        char *at[4];
         bool ok[4];
-    };
-    struct Data {                 // stage 2: the sub-tile's operand and base output
-        typename Tile::A a;
         u32x4 y[4][NY];
     };
 
@@ -121,9 +124,9 @@ struct LongWave {
     int64_t ld_bytes;
     bool col_ok;
     const LORA_GLOBAL vec *img;
-    lora_tile tl[kLongGroup];
-    int tix[kLongGroup];
-    bool live[kLongGroup];
+    lora_tile tl[GROUP];
+    int tix[GROUP];
+    bool live[GROUP];
 
     __device__ inline void rows_of(int q, Rows &r) const
     {
@@ -134,55 +137,61 @@ struct LongWave {
             const int row = sub * 16 + 4 * i + g;
             r.ok[i] = col_ok && row < n;
             const int dst = perm[tl[k].row0 + min(row, tl[k].n_rows - 1)];
-            r.y[i] = ybase + (int64_t)dst * ld_bytes;
+            r.at[i] = ybase + (int64_t)dst * ld_bytes;
         }
     }
 
-    __device__ inline void load(int q, const Rows &r, Data &d) const
+    __device__ inline void load_y(Rows &r) const
     {
-        const int k = q >> 1, sub = q & 1;
-        const LORA_GLOBAL vec *im = img + (int64_t)(tix[k] * 2 + sub) * image_vecs<R>();
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            d.a.hi[ks] = im[(ks * 2 + 0) * 64 + lane];
-            d.a.lo[ks] = im[(ks * 2 + 1) * 64 + lane];
-        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int h = 0; h < NY; ++h) d.y[i][h] = ld16<true>(r.y[i] + 16 * h);     // touched once: nontemporal
+            for (int h = 0; h < NY; ++h) r.y[i][h] = ld16<true>(r.at[i] + 16 * h);     // touched once: nontemporal
     }
 
-    __device__ inline void compute_store(const Rows &r, const Data &d, const typename Tile::B &b) const
+    __device__ inline void load_image(int q, typename Tile::A &a) const
+    {
+        const LORA_GLOBAL vec *im = img + (int64_t)(tix[q >> 1] * 2 + (q & 1)) * image_vecs<R>();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            a.hi[ks] = im[(ks * 2 + 0) * 64 + lane];
+            a.lo[ks] = im[(ks * 2 + 1) * 64 + lane];
+        }
+    }
+
+    // the base output becomes the output
+    __device__ inline void compute(Rows &r, const typename Tile::A &a, const typename Tile::B &b) const
     {
         f32x4 acc[8];
-        Tile::mma(d.a, b, acc);
-        // the sums are formed for every lane; only the store itself is predicated
+        Tile::mma(a, b, acc);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (F32) {
-                u32x4 o0, o1;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    o0[q] = __float_as_uint(__uint_as_float(d.y[i][0][q]) + acc[q][i]);
-                    o1[q] = __float_as_uint(__uint_as_float(d.y[i][NY - 1][q]) + acc[4 + q][i]);
-                }
-                if (r.ok[i]) {
-                    st16<true>(r.y[i], o0);
-                    st16<true>(r.y[i] + 16, o1);
+                    r.y[i][0][q] = __float_as_uint(__uint_as_float(r.y[i][0][q]) + acc[q][i]);
+                    r.y[i][NY - 1][q] = __float_as_uint(__uint_as_float(r.y[i][NY - 1][q]) + acc[4 + q][i]);
                 }
             } else {
-                u32x4 o;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const unsigned u = d.y[i][0][q];
+                    const unsigned u = r.y[i][0][q];
                     const float f0 = __uint_as_float(u << 16) + acc[2 * q][i];
                     const float f1 = __uint_as_float(u & 0xFFFF0000u) + acc[2 * q + 1][i];
-                    o[q] = pack_bf16_rne(f0, f1);
+                    r.y[i][0][q] = pack_bf16_rne(f0, f1);
                 }
-                if (r.ok[i]) st16<true>(r.y[i], o);
             }
         }
+    }
+
+    __device__ inline void store(const Rows &r) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (r.ok[i]) {
+#pragma unroll
+                for (int h = 0; h < NY; ++h) st16<true>(r.at[i] + 16 * h, r.y[i][h]);
+            }
     }
 };
 
@@ -194,11 +203,11 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
 {
     using Wave = LongWave<R, F32>;
     using Tile = ExpandTile<R>;
-    constexpr int NSLOT = Wave::NSLOT;
+    constexpr int NSLOT = Wave::NSLOT, GROUP = Wave::GROUP;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave), nw = gridDim.x * 4;
     const int n_tiles = counts[2];
-    const int n_groups = (n_tiles + kLongGroup - 1) / kLongGroup;
+    const int n_groups = (n_tiles + GROUP - 1) / GROUP;
     const int per_group = p.per_tile;                               // chunks of all projections
     const int n_items = n_groups * per_group;
 
@@ -219,32 +228,39 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
         w.ld_bytes = p.proj[pj].ldy * Wave::ESZ;
         w.img = (const LORA_GLOBAL typename Wave::vec *)p.proj[pj].img;
 #pragma unroll
-        for (int k = 0; k < kLongGroup; ++k) {
-            w.live[k] = tg * kLongGroup + k < n_tiles;
-            w.tix[k] = min(tg * kLongGroup + k, n_tiles - 1);
+        for (int k = 0; k < GROUP; ++k) {
+            w.live[k] = tg * GROUP + k < n_tiles;
+            w.tix[k] = min(tg * GROUP + k, n_tiles - 1);
             w.tl[k] = tiles[w.tix[k]];
         }
 
-        const typename Tile::Lanes lanes = Tile::lanes_of(lane, R);
+        typename Wave::Rows rows[NSLOT];
+        typename Tile::A a[2];
         typename Tile::B b;
+#pragma unroll
+        for (int q = 0; q < NSLOT; ++q) w.rows_of(q, rows[q]);
+        const typename Tile::Lanes lanes = Tile::lanes_of(lane, R);
         int b_key = w.tl[0].key;
         Tile::template load_b<false, false>(units[(int64_t)b_key * p.n_proj + p.proj0 + pj].B, chunk, lanes, b);
-
-        typename Wave::Rows rows[3];
-        typename Wave::Data data[2];
-        w.rows_of(0, rows[0]);
-        w.rows_of(1, rows[1]);
-        w.load(0, rows[0], data[0]);
+        w.load_image(0, a[0]);
+#pragma unroll
+        for (int q = 0; q < NSLOT; ++q) w.load_y(rows[q]);
 #pragma unroll
         for (int q = 0; q < NSLOT; ++q) {
-            if (q + 2 < NSLOT) w.rows_of(q + 2, rows[(q + 2) % 3]);
-            if (q + 1 < NSLOT) w.load(q + 1, rows[(q + 1) % 3], data[(q + 1) & 1]);
+            if (q + 1 < NSLOT) w.load_image(q + 1, a[(q + 1) & 1]);
             const int key = w.tl[q >> 1].key;
             if (key != b_key) {                                   // wave-uniform, rare
                 b_key = key;
                 Tile::template load_b<false, false>(units[(int64_t)key * p.n_proj + p.proj0 + pj].B, chunk, lanes, b);
             }
-            w.compute_store(rows[q % 3], data[q & 1], b);
+            w.compute(rows[q], a[q & 1], b);
+            if constexpr (R > 16) w.store(rows[q]);
+            else __builtin_amdgcn_sched_barrier(0);               // one sub-tile's products at a time
+        }
+        // rank 16, whose B leaves the registers for it: 241.7 -> 238.7 us for the call named above
+        if constexpr (R == 16) {
+#pragma unroll
+            for (int q = 0; q < NSLOT; ++q) w.store(rows[q]);
         }
     }
 }
@@ -273,8 +289,6 @@ size_t expand_image_bytes(int rank, int64_t n_tiles)
     const size_t vec_bytes = rank <= 16 ? 8 : 16;
     return (size_t)n_tiles * 2 * ks * 2 * 64 * vec_bytes;
 }
-
-int expand_long_group() { return kLongGroup; }
 
 hipError_t launch_expand(const ExpandParams &p, hipStream_t s)
 {

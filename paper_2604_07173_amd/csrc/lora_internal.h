@@ -292,7 +292,8 @@ int segments_large_launches(const SegParams &p);    // kernels it enqueues for i
 hipError_t launch_shrink(const ShrinkParams &p, hipStream_t s);
 hipError_t launch_expand(const ExpandParams &p, hipStream_t s);
 size_t expand_image_bytes(int rank, int64_t n_tiles);   // operand images of n_tiles 32-row tiles
-int expand_long_group();                                 // tiles per wave item of launch_expand
+// tiles per wave item of launch_expand: 16 KiB of output rows, all of which a wave has in registers
+__host__ __device__ constexpr int expand_long_group(bool f32) { return f32 ? 1 : 2; }
 hipError_t launch_shrink_decode(const ShrinkParams &p, hipStream_t s);   // tiles of <= 16 rows
 hipError_t launch_expand_decode(const ExpandParams &p, hipStream_t s);
 hipError_t launch_fused_decode(const FusedParams &p, hipStream_t s);
