@@ -78,8 +78,8 @@ constexpr int shrink_wave_units(int rank) { return rank == 8 ? 2 : rank == 16 ? 
 // as long, so a second round that is nearly empty costs a whole one: as many K parts as one round of the
 // chip takes.  Few items need less than a full round (more parts are more fp32 sums to write and read);
 // many take several rounds, by how well those fill.  The tiles are counted, four to a full block: 16384 rows in 8 uneven requests (130
-// fours and more), rank 64, 3 parts 290 us, 4 parts (two rounds) 305, 2 parts 298; in 8 equal ones (128)
-// 4 parts 284, 3 parts 288; 4096 rows, 5 parts 106, 13 parts 115.  The tiles, and not a bound from the
+// fours and more), rank 64, 3 parts 270.5 us, 4 parts (two rounds) 278.7 (2 parts, with the kernels before these, 298 against
+// 290 for 3); in 8 equal ones (128) 4 parts 284, 3 parts 288 (likewise); 4096 rows, 6 parts 93.5, 9 parts 96.6.  The tiles, and not a bound from the
 // number of rows, because that cannot tell the equal requests from the uneven ones.  `most`: what the
 // workspace has room for.  Whole numbers only: the shrink and the kernel that adds its parts both call it and
 // have to come to the same result.
