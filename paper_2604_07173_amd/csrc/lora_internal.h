@@ -265,8 +265,8 @@ struct CombineParams {
     int T, top_k;
     int n_adapters, n_experts;
     int h_out;
-    int n_pieces;            // waves per token; these two are filled by launch_combine
-    FastDiv pieces_div;
+    int waves;               // waves per token; these two are filled by launch_combine
+    FastDiv waves_div;
     uint16_t *y;             // bf16 [T][ldy] token rows, updated in place
     int64_t ldy;
 };
