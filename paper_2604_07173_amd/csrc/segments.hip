@@ -96,14 +96,14 @@ __device__ inline void block_scan3(int cnt, int last, int first, ScanLds *s,
     *first_after = lane < 63 ? min(mn, nmin) : mn;
 }
 
-// key_of[i] for all rows; `each(i, key)` is called once per row.  The id loads of up to eight
+// key_of[i] for the calling thread's rows; returns how many have a key.  The id loads of up to eight
 // rows are issued before the first is used (the ids come from HBM; one round trip per row
 // would otherwise dominate large batches).
-template <class F>
-__device__ inline void all_row_keys(const SegParams &p, unsigned *key_of, unsigned &bad, F each)
+__device__ inline int all_row_keys(const SegParams &p, unsigned *key_of, unsigned &bad)
 {
     constexpr int U = 8;
     const int tid = threadIdx.x;
+    int n_active = 0;
 #pragma unroll 1
     for (int i0 = tid; i0 < p.P; i0 += U * kThreads) {
         int a[U], e[U];
@@ -123,14 +123,17 @@ __device__ inline void all_row_keys(const SegParams &p, unsigned *key_of, unsign
             if (i < p.P) {
                 const unsigned k = row_key(p, a[u], e[u], bad);
                 key_of[i] = k;
-                each(i, k);
+                n_active += k != kNoKey ? 1 : 0;
             }
         }
     }
+    return n_active;
 }
 
-// The radix path, whole: keys, passes, boundaries, tiles, counts.
-__device__ __forceinline__ void radix_body(const SegParams &p)
+// The radix path, whole: passes, boundaries, tiles, counts.  put_keys(key_of, bad) writes the keys of the calling thread's
+// rows and returns how many have one.
+template <class PutKeys>
+__device__ __forceinline__ void radix_body(const SegParams &p, PutKeys put_keys)
 {
     __shared__ unsigned hist[kWaves][kBins];
     __shared__ ScanLds scan;
@@ -157,11 +160,10 @@ __device__ __forceinline__ void radix_body(const SegParams &p)
     for (int b = tid; b < kWaves * kBins; b += kThreads) (&hist[0][0])[b] = 0;
     __syncthreads();
 
-    // ---- key of every row (independent loads, four in flight per thread) -----------------
+    // ---- key of every row ------------------------------------------------------------------
     {
-        int n_active = 0;
         unsigned bad = 0;
-        all_row_keys(p, key_of, bad, [&](int, unsigned k) { n_active += k != kNoKey ? 1 : 0; });
+        int n_active = put_keys(key_of, bad);
         if (bad) atomicOr(&status_bits, bad);          // OR and + are order-independent
 #pragma unroll 1
         for (int o = 32; o > 0; o >>= 1) n_active += __shfl_xor(n_active, o, 64);
@@ -365,7 +367,7 @@ __device__ __forceinline__ void radix_body(const SegParams &p)
 
 __global__ __launch_bounds__(kThreads) void segments_kernel(SegParams p)
 {
-    radix_body(p);
+    radix_body(p, [&](unsigned *key_of, unsigned &bad) { return all_row_keys(p, key_of, bad); });
 }
 
 // ---- few keys, a few thousand rows -----------------------------------------------------------
@@ -405,7 +407,10 @@ void launch_small(const SegParams &p, hipStream_t s)
 //      smaller row index: the final order is by (key, row index), unique, hence bit-identical
 //      run to run and identical to the stable sort of the radix path.
 // Step 4 costs bucket length per row, and a counter has 8 bits: if one key holds more than 255 rows the
-// workgroup drops this attempt and runs the radix path (a workgroup-uniform decision).
+// workgroup drops this attempt and runs the radix path on the keys it has (a workgroup-uniform decision).  What a dropped attempt costs
+// is seen only where the radix path was taken at once before the counters had 8 bits (65536 keys and 1025 to 11200 rows,
+// 32768 keys from 8960, 16384 from 12800 on): a zipf batch of 4097 rows over 65536 keys 21.1 -> 23.1 us, 290 of 12288 rows
+// on one of 32768 keys 49.0 -> 51.1, all of them 35.5 -> 45.9; against that 23.1 -> 11.1 and 49.5 -> 11.4 where the counts do.
 //
 // Longer batches are launched with several workgroups.  Step 1 and the sums of step 2 are repeated by every one of them
 // (a workgroup cannot hand anything to another inside a launch, and repeating costs no time); the records and steps 3 and 4
@@ -419,7 +424,12 @@ void launch_small(const SegParams &p, hipStream_t s)
 // 10.7), 256 tokens 60.4 / 59.1, 64 tokens 33.0 / 31.8.  Of its time at 1024 tokens, by clock stamps: ids 1.8, counts 1.8,
 // sums 1.6, list 1.9, records 0.4, places 1.5, order 1.3; records written by the threads that own the keys took 5.)
 //
-// W: counter words per thread (up to 4096 W keys); R: rows per thread (up to 1024 R rows).
+// W: counter words per thread (up to 4096 W keys); R: rows per thread (up to 1024 R rows).  A row is some 60 instructions, so a thread
+// has a form with about as many as it needs, and in the forms of 8 and 16 the last pairs are left out.  Within a pair there
+// is no branch: a row without a key adds zero to a word that nobody reads and goes to a place behind the last.  Kernel alone in
+// us, forms of 4, 8 and 16 with a branch per row / with a wave-uniform one, rows left out one by one / now: 4096 keys, 1024
+// rows 6.7 / 6.5 / 6.1, 4096 rows 6.7 / 7.1 / 6.5, 8192 rows 8.1 / 8.8 / 7.9, 8193 rows 10.6 / 10.4 / 8.7, 16384 rows
+// 12.3 / 13.2 / 11.7; 32768 keys, 8192 rows 9.5 / 10.1 / 9.3.
 // Occupied keys of a thread up to which its wave lists them one after the other: at 1024 tokens of the fine-grained shapes
 // dense and sparse key ranges are alike either way, at 64 and 256 tokens a wave has two or three (59.1 and 31.8 us; all
 // keys without a branch 59.9 and 32.8; a branch per key 59.6 and 32.3).
@@ -429,6 +439,8 @@ template <int W, int R>
 __global__ __launch_bounds__(kThreads) void segments_bucket_kernel(SegParams p)
 {
     constexpr int KPT = 4 * W;                        // keys per thread
+    constexpr int GRP = R <= 4 ? R : 2;               // rows that are left out together
+    constexpr unsigned kNowhere = kThreads * W * 3 / 2;        // for rows without a key: the front of tmp, as a counter word
     __shared__ unsigned wave_sums[kWaves][2];
     __shared__ unsigned status_bits, overflow;
     __shared__ int own_lo, own_hi, pos_lo_s, pos_hi_s, seg_lo_s, seg_hi_s;
@@ -448,14 +460,21 @@ __global__ __launch_bounds__(kThreads) void segments_bucket_kernel(SegParams p)
     };
 
     // ---- 1. keys, counts and places --------------------------------------------------------
-    int a[R], e[R];
+    auto each_group = [&](auto body) {
 #pragma unroll
-    for (int u = 0; u < R; ++u) {                     // unconditional loads (P >= 1), then selects
-        const int i = tid + u * kThreads, r = min(i, P - 1);
-        a[u] = p.adapter_id[r];
-        e[u] = p.expert_id ? p.expert_id[r] : 0;
-        if (i >= P) a[u] = -1;
-    }
+        for (int u0 = 0; u0 < R; u0 += GRP)
+            if (u0 <= R / 2 || kThreads * u0 < P) body(u0);
+    };
+    int a[R], e[R];
+    each_group([&](int u0) {
+#pragma unroll
+        for (int u = u0; u < u0 + GRP; ++u) {
+            const int i = tid + u * kThreads, r = min(i, P - 1);
+            a[u] = p.adapter_id[r];
+            e[u] = p.expert_id ? p.expert_id[r] : 0;
+            if (i >= P) a[u] = -1;
+        }
+    });
     if (tid == 0) {
         status_bits = 0;
         overflow = 0;
@@ -467,28 +486,47 @@ __global__ __launch_bounds__(kThreads) void segments_bucket_kernel(SegParams p)
     for (int j = 0; j < W; ++j) cnt[tid + j * kThreads] = 0;
     __syncthreads();
     unsigned mine[R];                                 // key | place << 16, or kNoKey
+    unsigned bad = 0;
     {
-        unsigned bad = 0, old[R];
+        unsigned old[R];
         bool over = false;
 #pragma unroll
-        for (int u = 0; u < R; ++u) {
-            mine[u] = row_key(p, a[u], e[u], bad);
-            old[u] = mine[u] != kNoKey ? atomicAdd(&cnt[mine[u] >> 2], 1u << ((mine[u] & 3u) * 8u)) : 0u;
-        }
+        for (int u = 0; u < R; ++u) mine[u] = kNoKey;
+        each_group([&](int u0) {
 #pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (mine[u] != kNoKey) {
-                const unsigned place = (old[u] >> ((mine[u] & 3u) * 8u)) & 0xFFu;
+            for (int u = u0; u < u0 + GRP; ++u) {
+                mine[u] = row_key(p, a[u], e[u], bad);
+                const bool yes = mine[u] != kNoKey;
+                old[u] = atomicAdd(&cnt[yes ? mine[u] >> 2 : kNowhere + lane], yes ? 1u << ((mine[u] & 3u) * 8u) : 0u);
+            }
+        });
+        each_group([&](int u0) {
+#pragma unroll
+            for (int u = u0; u < u0 + GRP; ++u) {
+                const bool yes = mine[u] != kNoKey;
+                const unsigned place = yes ? (old[u] >> ((mine[u] & 3u) * 8u)) & 0xFFu : 0u;
                 over = over || place == 0xFFu;        // the counter has run into its neighbour
                 mine[u] |= place << 16;
             }
+        });
         if (bad) atomicOr(&status_bits, bad);
         if (over) overflow = 1;
     }
     __syncthreads();
     if (overflow) {                                   // every workgroup has seen the same counts
         __syncthreads();
-        if (wg == 0) radix_body(p);
+        if (wg == 0)
+            radix_body(p, [&](unsigned *key_of, unsigned &bad_rows) {
+                int n_active = 0;
+#pragma unroll
+                for (int u = 0; u < R; ++u) {
+                    const int i = tid + u * kThreads;
+                    if (i < P) key_of[i] = mine[u] == kNoKey ? kNoKey : mine[u] & 0xFFFFu;
+                    n_active += mine[u] != kNoKey ? 1 : 0;
+                }
+                bad_rows = bad;
+                return n_active;
+            });
         return;
     }
 
@@ -588,16 +626,19 @@ __global__ __launch_bounds__(kThreads) void segments_bucket_kernel(SegParams p)
     // ---- 3. every row to its place in its key's range ---------------------------------------
     {
         unsigned to[R];
+        each_group([&](int u0) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) {                 // all look-ups before the first store
-            const unsigned k = mine[u] & 0xFFFFu, owner = k / KPT;
-            const bool yes = mine[u] != kNoKey && owner >= lo && owner < hi;
-            to[u] = kNoKey;
-            if (yes) to[u] = start_of(k) + (mine[u] >> 16);
-        }
+            for (int u = u0; u < u0 + GRP; ++u) {       // all look-ups before the first store
+                const unsigned k = mine[u] & 0xFFFFu, owner = k / KPT;
+                const bool yes = mine[u] != kNoKey && owner >= lo && owner < hi;
+                const unsigned at = start_of(yes ? k : 0u) + (mine[u] >> 16);
+                to[u] = yes ? at : (unsigned)((P + 63) & ~63) + lane;
+            }
+        });
+        each_group([&](int u0) {
 #pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (to[u] != kNoKey) tmp[to[u]] = (unsigned)(tid + u * kThreads) | (mine[u] << 16);
+            for (int u = u0; u < u0 + GRP; ++u) tmp[to[u]] = (unsigned)(tid + u * kThreads) | (mine[u] << 16);
+        });
     }
     // filler around this workgroup's positions: step 4 reads aligned groups of four words
     if (pos_lo < pos_hi) {
@@ -676,6 +717,8 @@ template <int W>
 static hipError_t launch_bucket(const SegParams &p, size_t dyn, hipStream_t s)
 {
     static_assert(16 * kThreads == LORA_MAX_ROWS, "the last form takes the longest batch");
+    if (p.P <= kThreads) return launch_bucket_wr<W, 1>(p, dyn, s);
+    if (p.P <= 2 * kThreads) return launch_bucket_wr<W, 2>(p, dyn, s);
     if (p.P <= 4 * kThreads) return launch_bucket_wr<W, 4>(p, dyn, s);
     if (p.P <= 8 * kThreads) return launch_bucket_wr<W, 8>(p, dyn, s);
     return launch_bucket_wr<W, 16>(p, dyn, s);
