@@ -638,7 +638,16 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     ep.slice2 = g.n > 2 ? ep.proj[2].slice0 : ep.per_tile;
     ep.waves = 4;
     const int64_t groups = (tub + expand_long_group(ep.out_f32) - 1) / expand_long_group(ep.out_f32);
-    const int64_t wave_items = groups * ep.per_tile;
+    // Neighbouring waves take neighbouring chunks of the same rows, but with narrow fp32 outputs the rows of four tiles: the
+    // short rows of equal segments lie a power of two apart, and waves that all start with the first rows of a tile meet in the
+    // same memory channels.  lora_expand in us, chunks first / rows first: 16384 rows in eight equal requests, rank 16,
+    // 1024 columns 43.0 / 32.4, 2048 columns 77.8 / 56.5 (rows of 1088 columns 31.8 / 31.9); rank 32, 1024 columns 42.5 / 36.1,
+    // eight uneven requests 37.3 / 38.8, 64 segments of 256 rows 40.0 / 39.7, at rank 64 43.2 / 44.5; 4096 columns, rank 16
+    // 98.6 / 100.9, rank 32 107 / 109; bf16 output, rank 16, 1024 columns 18.6 / 19.0, 2048 columns 34.1 / 31.7, at rank 64
+    // 23.7 / 27.5 and 40.9 / 39.5, 14336 columns 172 / 192.
+    static const int shift = tune_int("LORA_EXPAND_ITEM_SHIFT", -1, -1, 4);
+    ep.item_shift = shift >= 0 ? shift : ep.out_f32 && ep.per_tile <= 2048 / kColChunk ? 2 : 0;
+    const int64_t wave_items = (((groups - 1) >> ep.item_shift) + 1) * (ep.per_tile << ep.item_shift);
     ep.grid = (int)std::min<int64_t>((wave_items + 3) / 4, (int64_t)cu_count() * per_cu);
     ep.image_grid = (int)std::min<int64_t>((tub * 2 * g.n + 3) / 4, (int64_t)cu_count() * 8);
     return LORA_OK;

@@ -26,7 +26,10 @@
 // rows of 8 uneven requests, rank 64 286.5 / 282.8 / 278.4 / 270.9, 4096 rows of 8 requests 93.4 / 90.9 / 90.3 / 89.4,
 // 16384 rows, rank 16 266.4 / 251.2 / 242.9 / 241.7, 12000 rows of 7 requests, rank 32 206.7 / 193.0 / 191.0 / 190.2;
 // the first is 5.6 TB/s of y and B.  More tiles (3, all in flight: 312, registers spill) or fewer (1: 309, B is fetched
-// for every 32 rows) are slower at rank 64; 8 tiles with one in flight 294.
+// for every 32 rows) are slower at rank 64; 8 tiles with one in flight 294.  Where four tiles were ahead of two: one narrow
+// projection of segments that are whole multiples of 128 rows, of which they fetched B half as often and crossed into the
+// next never (lora_expand, 64 segments of 256 rows, rank 64, 1024 columns 23.3 / 27.8, 4096 columns 65.4 / 67.8; of 128 rows, 2048 columns
+// 23.0 / 27.6; but 64 uneven ones of 256 on average, whole call 1024 columns 8 % less, q, k and v together 5 % less).
 //
 // The base-output rows are read and written with nontemporal accesses: every byte of y is touched
 // once, and keeping it out of the caches leaves them to the B tiles and operand images that many
@@ -208,12 +211,14 @@ __global__ __launch_bounds__(256, 2) void expand_long_kernel(ExpandParams p,
     const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + wave), nw = gridDim.x * 4;
     const int n_tiles = counts[2];
     const int n_groups = (n_tiles + GROUP - 1) / GROUP;
-    const int per_group = p.per_tile;                               // chunks of all projections
-    const int n_items = n_groups * per_group;
+    const int shift = p.item_shift;                                 // tile groups in runs of 2^shift
+    const int per_run = p.per_tile << shift;                        // per_tile: chunks of all projections
+    const int n_items = ((n_groups + (1 << shift) - 1) >> shift) * per_run;
 
     for (int item = gw; item < n_items; item += nw) {
-        const int tg = item / per_group;
-        const int rem = item - tg * per_group;
+        const int run = item / per_run, at = item - run * per_run;
+        const int tg = (run << shift) + (at & ((1 << shift) - 1)), rem = at >> shift;
+        if (tg >= n_groups) continue;
         const int pj = (rem >= p.slice1 ? 1 : 0) + (rem >= p.slice2 ? 1 : 0);
         const int chunk = rem - p.proj[pj].slice0;
 

@@ -246,6 +246,7 @@ struct ExpandParams {
         int group_shift;     // decode kernel: consecutive wave items walk over 2^group_shift tiles
         int kblocks;         // long-segment kernels: K-blocks of the input
     };
+    int item_shift;          // long-segment kernel: consecutive wave items take the tile groups of a run of 2^item_shift, then chunks
     int out_f32;
     int overwrite;           // decode kernel, bf16 output: write the update, do not read the rows
     int deep;                // decode kernel: two chunks in flight per wave, else one
