@@ -595,14 +595,17 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
         // is streamed at every length (cached: 255 -> 264 us for 2048 tokens).
         ep.share_b = long_segments;
         const int64_t wave_items = (tub + group - 1) / group * group * ep.per_tile;
-        // Chunks in flight per wave: two, but one where an item is one chunk anyway, and at ranks 8 and 64 where the launch
-        // is a few rounds of the chip's waves long and its tiles are tall (more waves fit then, which shortens the
-        // rounds).  Layer call in us, two / one: llama shapes, 1024 rows, rank 64 254.5 / 253.1, rank 8 89.7 / 89.1, 512 rows,
-        // rank 64 186.2 / 184.6, with 8 rows (one chunk) 31.6 / 31.0; but 2048 rows, rank 32 230.5 / 232.0, rank 16 158.7 /
-        // 160.0, of which 1792 share an adapter 145.7 / 147.9, 1024 rows, rank 16 106.4 / 106.4, rank 32 158.2 / 158.5, 256
-        // rows (short tiles) 57.4 / 58.8, and Mixtral shapes with 2048 tokens (57 k items) at rank 16 244.9 / 247.1.
+        // Chunks in flight per wave: two, but one where an item is one chunk anyway, and at ranks 32 and 64 where the launch
+        // is a few rounds of the chip's waves long and its tiles are tall (more waves fit then, which shortens the rounds; an
+        // item with fp32 output counts for two).  Two against one, geometric mean and range of the calls of one group (4096,
+        // 4096 + 2 x 1024 and 2 x 14336 columns; 4 to 64 adapters, 128 to 3072 rows, zipf ids or one prompt), up to 12288 and
+        // 12288 to 24576 items: bf16 output, rank 8 0.97 and 0.99, rank 16 0.97 and 0.98, rank 32 1.01 (0.92 to 1.06) and
+        // 1.01 (0.98 to 1.06), rank 64 1.01 (0.92 to 1.08) and 1.02 (0.99 to 1.08); fp32 output, rank 8 0.95 and 0.95, rank 16 0.98
+        // and 0.97, rank 32 1.00 (0.94 to 1.07) and 0.97 (0.90 to 1.03), rank 64 0.99 (0.92 to 1.10) and 0.99 (0.98 to 1.03).  Llama layer with
+        // 8 rows (one chunk) 31.6 / 31.0 us; 256 rows (short tiles) 57.4 / 58.8; Mixtral shapes, 2048 tokens (57 k items), rank 16
+        // 244.9 / 247.1.
         static const int shallow = tune_int("LORA_DEC_SHALLOW_ITEMS", 24576, 0, 1 << 30);
-        const bool few_rounds = long_segments && wave_items <= shallow && (pool->d.rank == 8 || pool->d.rank == 64);
+        const bool few_rounds = long_segments && pool->d.rank >= 32 && (ep.out_f32 ? 2 : 1) * wave_items <= shallow;
         ep.deep = cpi > 1 && !few_rounds;
         // The hardware hands workgroups out as others finish, which evens out tiles of different heights
         // better than a workgroup's walk over several items, and costs a launch of its own each: worth it
