@@ -480,14 +480,17 @@ int do_shrink(const lora_pool *pool, int layer, const Group &g, const void *x, i
         sp.n_fused = std::min(2, g.n - j);
         // Short segments (less than three tiles on average) leave most waves of a block of one segment
         // without rows: groups of four tiles then, but for one projection only, because with two a wave has
-        // no registers to fetch enough of its own A ahead.  Layer call in us, blocks / groups: one projection
-        // at rank 32 and 1024 inputs, 4096 adapters with 32 rows each 349 / 334, at rank 64 456 / 445; Mixtral shapes,
-        // 4096 tokens (groups for the down projection), rank 32 402 / 394, rank 64 500 / 497; at rank 64 and 4096 inputs
-        // blocks are ahead (256 adapters with 32 rows 116 / 122); two projections, rank 64 and 4096 inputs, 128 adapters
-        // 91 / 123; 128 rows per adapter 219 / 233.
+        // no registers to fetch enough of its own A ahead.  Which is ahead is decided by how unequal the segments are, which is
+        // not known here, and the line is drawn for skewed ids.  lora_shrink in us, blocks / groups, rows per segment by zipf
+        // ids (and between half and one and a half times the mean): 4096 segments of 33 rows on average, 1024 inputs, rank 32
+        // 169 / 89 (108 / 96), rank 64 240 / 166 (177 / 174); 256 of 33, 14336 inputs, 99 / 82 (76 / 79) and 154 / 138 (132 / 129),
+        // 4096 inputs, rank 64 43.8 / 38.3 (35.9 / 39.7); 512 of 64, 4096 inputs, rank 32 101 / 84 (69 / 91); 128 of 95, rank 64 36.8 /
+        // 37.4.  Up to 64 segments blocks are ahead from 48 rows on: 64 of 64, 2048 inputs, rank 32 9.5 / 10.5 (7.8 / 10.0); of
+        // 48, 4096 inputs, rank 64 16.1 / 18.2; of 95 23.5 / 22.9; of 33 16.9 / 13.9.  Two projections, layer call, rank 64
+        // and 4096 inputs, 128 adapters with 32 rows 91 / 123; 128 rows per adapter 219 / 233.
         static const int by_tiles = tune_int("LORA_SHRINK_BY_TILES", -1, -1, 1);
         const int64_t keys = (int64_t)pool->d.n_adapters * pool->d.n_experts;
-        sp.by_tiles = by_tiles >= 0 ? by_tiles : sp.n_fused == 1 && seg->P < 96 * keys;
+        sp.by_tiles = by_tiles >= 0 ? by_tiles : sp.n_fused == 1 && seg->P < (keys <= 64 ? 48 : 96) * keys;
         // The kernel of blocks only holds kLongListedSegs segments.
         sp.blocks = !sp.by_tiles && std::min<int64_t>(keys, seg->P) <= kLongListedSegs;
         sp.v[0] = g.v[j];
