@@ -352,14 +352,19 @@ __global__ __launch_bounds__(256, 2) void shrink_long_kernel(ShrinkParams p,
 // ---- blocks of one segment ---------------------------------------------------------------------------
 
 // 16 bytes per lane from memory straight into LDS, lane l's at lds_at + 16 l (lds_at: a byte address, the same for every
-// lane).  Counts as a vector-memory load that the compiler does not know of; it is in LDS once wait_loads says so.
+// lane).  Counts as a vector-memory load that the compiler does not know of; it is in LDS once wait_loads says so.  m0, which
+// holds the address, is named as clobbered, so that no value of the compiler's own lives in it across the statement; that
+// nothing saves a reserved register, of which the compiler warns, is what is wanted here.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <bool NT>
 __device__ inline void load_to_lds(const void *src, unsigned lds_at)
 {
-    const unsigned m0 = __builtin_amdgcn_readfirstlane(lds_at);
-    if (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(m0), "v"(src) : "memory");
-    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(src) : "memory");
+    const unsigned at = __builtin_amdgcn_readfirstlane(lds_at);
+    if (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(at), "v"(src) : "memory", "m0");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // until at most N of this wave's vector-memory operations are outstanding
 template <int N>
