@@ -24,7 +24,10 @@
 // uneven requests, 4096 inputs, rank 64, two projections 44.4 / 42.2 / 40.3 (as much x alone, without A, takes 32), 8 requests of
 // exactly 2048 rows 42.7 / 34.4 / 34.1, 8192 rows in 8 requests 31.4 / 29.1 / 25.6, 4096 rows in 8 requests
 // 25.1 / 18.7 / 18.2, 8192 rows in 64 segments at rank 32 31.6 / 30.2 / 28.0.  Three stages of A at rank 64 with two
-// projections leave room for one workgroup per CU only: 45.4 for the first.
+// projections leave room for one workgroup per CU only: 45.4 for the first.  Over 10 layouts of 4096 to 32768 rows and 2048 to
+// 28672 inputs the kernel takes 0.92 of shrink_long_kernel's time (geometric mean); where it is behind, it is by 2 to 5 %: 14336
+// inputs and more, 16384 rows and more of few requests (rank 64, one projection, one request 79.7 / 83.4; with two stages of A
+// 80.3, which costs 3 to 6 % at 8192 inputs).
 //
 // shrink_long_kernel: per stage of four K blocks the
 // workgroup copies the packed A blocks of the segment's (adapter, expert) into one of two LDS
