@@ -649,10 +649,17 @@ int expand_params(const lora_pool *pool, int layer, const Group &g, const lora_s
     // same memory channels.  lora_expand in us, chunks first / rows first: 16384 rows in eight equal requests, rank 16,
     // 1024 columns 43.0 / 32.4, 2048 columns 77.8 / 56.5 (rows of 1088 columns 31.8 / 31.9); rank 32, 1024 columns 42.5 / 36.1,
     // eight uneven requests 37.3 / 38.8, 64 segments of 256 rows 40.0 / 39.7, at rank 64 43.2 / 44.5; 4096 columns, rank 16
-    // 98.6 / 100.9, rank 32 107 / 109; bf16 output, rank 16, 1024 columns 18.6 / 19.0, 2048 columns 34.1 / 31.7, at rank 64
-    // 23.7 / 27.5 and 40.9 / 39.5, 14336 columns 172 / 192.
+    // 98.6 / 100.9, rank 32 107 / 109; bf16 output, rank 16, 1024 columns 18.6 / 19.0, at rank 64
+    // 23.7 / 27.5, 14336 columns 172 / 192.  bf16 outputs meet like that in one place only, where a call covers rows of 4 KiB whole,
+    // so that the waves' chunks and their rows both repeat with a power of two: runs of two pairs of tiles there (lora_expand, 16384 rows of
+    // eight equal requests, rank 64 45.8 / 40.4, rank 32 40.4 / 34.9, 128 segments of 128 rows 43.3 / 35.9; uneven requests 41.4 / 40.7 and
+    // 35.0 / 35.1, 64 uneven segments 41.7 / 43.0 and 35.1 / 35.8; 1024 + 1024 columns of such rows, apply, equal 46.0 / 42.4, uneven 41.4 /
+    // 42.5, 8192 uneven rows at rank 64 32.4 / 34.5).  Not narrower (1920 columns 36.6 / 37.8), wider (2 x 2048 64.0 / 64.6) or with longer
+    // rows (2176 columns apart 38.0 / 38.6, 6144 39.8 / 41.0).
     static const int shift = tune_int("LORA_EXPAND_ITEM_SHIFT", -1, -1, 4);
-    ep.item_shift = shift >= 0 ? shift : ep.out_f32 && ep.per_tile <= 2048 / kColChunk ? 2 : 0;
+    bool rows_of_4k = !ep.out_f32 && ep.per_tile == 2048 / kColChunk;
+    for (int j = 0; j < g.n; ++j) rows_of_4k = rows_of_4k && ep.proj[j].ldy == 2048;
+    ep.item_shift = shift >= 0 ? shift : ep.out_f32 && ep.per_tile <= 2048 / kColChunk ? 2 : rows_of_4k ? 1 : 0;
     const int64_t wave_items = (((groups - 1) >> ep.item_shift) + 1) * (ep.per_tile << ep.item_shift);
     ep.grid = (int)std::min<int64_t>((wave_items + 3) / 4, (int64_t)cu_count() * per_cu);
     ep.image_grid = (int)std::min<int64_t>((tub * 2 * g.n + 3) / 4, (int64_t)cu_count() * 8);

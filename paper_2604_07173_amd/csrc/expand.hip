@@ -29,8 +29,8 @@
 // alone in steady state, 212 us = 5.7 TB/s of y and B.  More tiles (3, all in flight: 312, registers spill) or fewer (1: 309, B is fetched
 // for every 32 rows) are slower at rank 64; 8 tiles with one in flight 294.  Where four tiles were ahead of two: one narrow
 // projection of segments that are whole multiples of 128 rows, of which they fetched B half as often and crossed into the
-// next never (lora_expand, 64 segments of 256 rows, rank 64, 1024 columns 23.3 / 27.8, 4096 columns 65.4 / 67.8; of 128 rows, 2048 columns
-// 23.0 / 27.6; but 64 uneven ones of 256 on average, whole call 1024 columns 8 % less, q, k and v together 5 % less).
+// next never (lora_expand, 64 segments of 256 rows, rank 64, 1024 columns 25.7 / 28.1, 4096 columns 64.7 / 62.2; of 128 rows, 1024 columns
+// 25.8 / 28.6, at rank 32 20.3 / 21.3; but 64 uneven ones of 256 on average, whole call 1024 columns 8 % less, q, k and v together 5 % less).
 //
 // The base-output rows are read and written with nontemporal accesses: every byte of y is touched
 // once, and keeping it out of the caches leaves them to the B tiles and operand images that many
