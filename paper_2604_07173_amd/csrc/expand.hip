@@ -26,7 +26,7 @@
 // rows of 8 uneven requests, rank 64 286.5 / 282.8 / 278.4 / 270.9, 4096 rows of 8 requests 93.4 / 90.9 / 90.3 / 89.4,
 // 16384 rows, rank 16 266.4 / 251.2 / 242.9 / 241.7, 12000 rows of 7 requests, rank 32 206.7 / 193.0 / 191.0 / 190.2;
 // eight equal requests at rank 64, kernel
-// alone in steady state, 212 us = 5.7 TB/s of y and B.  More tiles (3, all in flight: 312, registers spill) or fewer (1: 309, B is fetched
+// alone in steady state, 212 to 214 us = 5.7 TB/s of y and B.  More tiles (3, all in flight: 312, registers spill) or fewer (1: 309, B is fetched
 // for every 32 rows) are slower at rank 64; 8 tiles with one in flight 294.  Where four tiles were ahead of two: one narrow
 // projection of segments that are whole multiples of 128 rows, of which they fetched B half as often and crossed into the
 // next never (lora_expand, 64 segments of 256 rows, rank 64, 1024 columns 25.7 / 28.1, 4096 columns 64.7 / 62.2; of 128 rows, 1024 columns
